@@ -5,10 +5,15 @@
 //   mu_m = m0 + s k*_m . alpha,   var_m = s^2 (amp - |X k*_m|^2),
 //   gamma = (J_best - mu - xi) / sigma,  EI = sigma (gamma Phi(gamma) + phi(gamma)).
 // |X k*_m|^2 for all m is a triangular matrix product Z = X K*^T (n x M) reduced over its rows:
+// Up to kGpFuseMax observations one kernel does all of it per 16 queries (k_gp_fused, after k_gp_pack has
+// put X into the matrix cores' operand order); above that, where K* of 16 queries does not fit in LDS:
 //   k_gp_kstar  K* [M][npad] (zero past n)
 //   k_gp_zsq    per (64-row block of X, 64-query block): the Z block over j <= i on the FP64 matrix
 //               cores, squared and summed over its rows -> part [n/64][M] (fixed order, no atomics)
 //   k_gp_ei     one wave per query: k* . alpha, sum of the row-block partials, EI
+// Both paths add in the same order and give the same bits.
+#include <algorithm>
+
 #include "launch.h"
 
 namespace boac {
@@ -89,6 +94,29 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Mean, deviation and EI of query m from a = k* . alpha and q = |X k*|^2.
+__device__ __forceinline__ void gp_emit(const GpEiArgs &A, int m, double a, double q) {
+    const double mu = A.m0 + A.s * a;
+    const double var = A.amp - q;
+    const double sd = A.s * sqrt(var > 0.0 ? var : 0.0);
+    const double imp = A.best - mu - A.xi;
+    double ei;
+    if (sd > 0.0) {
+        const double g = imp / sd;
+        const double cdf = 0.5 * erfc(-g * 0.70710678118654752440);
+        const double pdf = 0.39894228040143267794 * exp(-0.5 * g * g);
+        // g Phi(g) + phi(g) > 0, but for g far below 0 its two terms cancel and rounding can leave a
+        // tiny negative: EI, the mean of a non-negative improvement, is clamped at 0
+        ei = sd * fma(g, cdf, pdf);
+        if (!(ei > 0.0)) ei = 0.0;
+    } else {
+        ei = imp > 0.0 ? imp : 0.0;
+    }
+    if (A.mu) A.mu[m] = mu;
+    if (A.sd) A.sd[m] = sd;
+    A.ei[m] = ei;
+}
+
 __global__ __launch_bounds__(256) void k_gp_ei(GpEiArgs A) {
     const int lane = threadIdx.x & 63;
     const int m = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -99,27 +127,184 @@ __global__ __launch_bounds__(256) void k_gp_ei(GpEiArgs A) {
     double q = 0.0;
     for (int t = lane; t < A.nti; t += 64) q += A.part[(size_t)t * A.M + m];
     q = wave_sum(q);
-    if (lane == 0) {
-        const double mu = A.m0 + A.s * a;
-        const double var = A.amp - q;
-        const double sd = A.s * sqrt(var > 0.0 ? var : 0.0);
-        const double imp = A.best - mu - A.xi;
-        double ei;
-        if (sd > 0.0) {
-            const double g = imp / sd;
-            const double cdf = 0.5 * erfc(-g * 0.70710678118654752440);
-            const double pdf = 0.39894228040143267794 * exp(-0.5 * g * g);
-            // g Phi(g) + phi(g) > 0, but for g far below 0 its two terms cancel and rounding can leave a
-            // tiny negative: EI, the mean of a non-negative improvement, is clamped at 0
-            ei = sd * fma(g, cdf, pdf);
-            if (!(ei > 0.0)) ei = 0.0;
-        } else {
-            ei = imp > 0.0 ? imp : 0.0;
+    if (lane == 0) gp_emit(A, m, a, q);
+}
+
+// ------------------------------------------------------------------ fused acquisition
+// X in operand order: the 16-row tile rt, 16-column chunk ch holds, for its 4 matrix steps s = 2 p + h
+// (columns 16 ch + 4 s + l / 16 of row 16 rt + l % 16 in lane l), the doubles [p][lane][h]: a wave loads two
+// steps of a tile with one 16-byte load per lane, 1 KB contiguous. Zero past n.
+__global__ __launch_bounds__(256) void k_gp_pack(const double *__restrict__ linv, int n, int npad,
+                                                 double *__restrict__ xp) {
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    if (t >= (size_t)npad * npad) return;
+    const int h = t & 1, l = (t >> 1) & 63, p = (t >> 7) & 1;
+    const int tile = (int)(t >> 8), nch = npad / 16;
+    const int i = 16 * (tile / nch) + (l & 15), j = 16 * (tile % nch) + 4 * (2 * p + h) + (l >> 4);
+    xp[t] = (i < n && j < n) ? linv[(size_t)i * n + j] : 0.0;
+}
+
+constexpr int kFuseQ = 16;          // queries per workgroup (one matrix tile)
+constexpr int kFuseP = kFuseQ + 1;  // LDS row of K*: the odd pitch spreads a column's rows over the banks
+
+// One workgroup (4 waves) per 16 queries: K* of the queries into LDS ([j][query]), Z = X K*^T by 64-row
+// blocks on the FP64 matrix cores (X from L2 in operand order, 16 columns ahead in registers; a wave takes
+// whole blocks, dealt back and forth so that the triangle's long rows spread evenly), the blocks' row
+// sums of squares, then k* . alpha and EI. K* never goes to memory and X passes through no LDS. The sums run
+// in k_gp_kstar's, k_gp_zsq's and k_gp_ei's order, so the values are theirs bit for bit. Bound by the
+// matrix cores: a 16 x 16 x 4 FP64 step takes 64 cycles of a SIMD.
+// LOCAL: the queries are a round's points of the local search, formed here (GpLocalArgs): the centre moves
+// to the first best point of its previous round, the points are set around it, the chains step.
+template <bool LOCAL>
+__global__ __launch_bounds__(256) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
+    extern __shared__ double sm[];
+    double *Ks = sm;                            // [npad][kFuseP]
+    double *part = Ks + A.npad * kFuseP;        // [nti][kFuseQ]
+    double *Qs = part + A.nti * kFuseQ;         // [kFuseQ][d]
+    double *fin = Qs + kFuseQ * A.d;            // [2][kFuseQ]
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int m0 = blockIdx.x * kFuseQ, d = A.d;
+    if constexpr (LOCAL) {
+        // 32 lanes per query
+        const int hl = tid & 31;
+        for (int qi = tid >> 5; qi < kFuseQ; qi += 8) {
+            const int m = m0 + qi;
+            if (m >= A.M) {
+                for (int k = hl; k < d; k += 32) Qs[qi * d + k] = 0.0;
+                continue;
+            }
+            const int c = m / L.per;
+            double bv = -INFINITY;
+            int bi = 0;
+            if (L.e_prev) {
+                for (int k = hl; k < L.per; k += 32) {
+                    const double v = L.e_prev[(size_t)c * L.per + k];
+                    if (v > bv) {
+                        bv = v;
+                        bi = k;
+                    }
+                }
+#pragma unroll
+                for (int off = 16; off > 0; off >>= 1) {
+                    const double ov = __shfl_xor(bv, off);
+                    const int oi = __shfl_xor(bi, off);
+                    if (ov > bv || (ov == bv && oi < bi)) {
+                        bv = ov;
+                        bi = oi;
+                    }
+                }
+            }
+            const double ce = L.Ce_src[c];
+            const bool better = L.e_prev && bv > ce;
+            const bool owner = L.C_dst && m == c * L.per;
+            for (int k = hl; k < d; k += 32) {
+                const double base = better ? L.U_prev[((size_t)c * L.per + bi) * d + k] : L.C_src[(size_t)c * d + k];
+                const double z = L.z[(size_t)m * d + k];
+                const double wz = 2.0 * z - 1.0;
+                const double v = base + L.r * wz;
+                const double lo = v > 0.0 ? v : 0.0;  // clip to [0, 1] as max then min, comparisons only
+                const double u = lo < 1.0 ? lo : 1.0;
+                Qs[qi * d + k] = u;
+                L.U[(size_t)m * d + k] = u;
+                L.z[(size_t)m * d + k] = (4.0 * z) * (1.0 - z);
+                if (owner) L.C_dst[(size_t)c * d + k] = base;
+            }
+            if (owner && hl == 0) L.Ce_dst[c] = better ? bv : ce;
         }
-        if (A.mu) A.mu[m] = mu;
-        if (A.sd) A.sd[m] = sd;
-        A.ei[m] = ei;
+        // chains past the last centre's step too
+        if (blockIdx.x == gridDim.x - 1)
+            for (int t = A.M * d + tid; t < L.P * d; t += blockDim.x) {
+                const double z = L.z[t];
+                L.z[t] = (4.0 * z) * (1.0 - z);
+            }
+    } else {
+        for (int t = tid; t < kFuseQ * d; t += blockDim.x) {
+            const size_t o = (size_t)m0 * d + t;
+            Qs[t] = o < (size_t)A.M * d ? A.q[o] : 0.0;
+        }
     }
+    __syncthreads();
+    // K*: 4 queries of one observation per thread and step
+    for (int e = tid; e < 4 * A.npad; e += blockDim.x) {
+        const int j = e >> 2, q0 = 4 * (e & 3);
+        double k[4] = {0.0, 0.0, 0.0, 0.0};
+        if (j < A.n) {
+            double d2[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int c = 0; c < d; ++c) {
+                const double u = A.u[(size_t)j * d + c];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double t = Qs[(q0 + i) * d + c] - u;
+                    d2[i] = fma(t, t, d2[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) k[i] = A.amp * exp(-d2[i] * A.inv2l2);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) Ks[j * kFuseP + q0 + i] = k[i];
+    }
+    __syncthreads();
+    const int lr = lane & 15, lk = lane >> 4;
+    const int nchunks = A.npad / 16;
+    for (int r = 0; r < A.nti; ++r) {
+        if (((r & 4) ? 3 - (r & 3) : (r & 3)) != w) continue;
+        const int b = A.nti - 1 - r;
+        const int nch = (min(64 * b + 64, A.n) + 15) / 16;
+        const double2 *x[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            x[t] = reinterpret_cast<const double2 *>(A.xp) + (size_t)(4 * b + t) * nchunks * 128 + lane;
+        v4d acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
+        double2 cur[4][2], nxt[4][2];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) cur[t][p] = x[t][64 * p];
+        for (int ch = 0; ch < nch; ++ch) {
+            const int cn = min(ch + 1, nch - 1);  // the last chunk reloads itself: no branch around the loads
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) nxt[t][p] = x[t][(size_t)cn * 128 + 64 * p];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double bq = Ks[(16 * ch + 4 * s + lk) * kFuseP + lr];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const double2 v = cur[t][s >> 1];
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((s & 1) ? v.y : v.x, bq, acc[t], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) cur[t][p] = nxt[t][p];
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s = fma(acc[t][v], acc[t][v], s);
+        const double s0 = __shfl(s, lr), s1 = __shfl(s, lr + 16), s2 = __shfl(s, lr + 32), s3 = __shfl(s, lr + 48);
+        if (lane < 16) part[b * kFuseQ + lane] = ((s0 + s1) + s2) + s3;
+    }
+    __syncthreads();
+    for (int qi = w; qi < kFuseQ; qi += 4) {
+        double a = 0.0, q = 0.0;
+        for (int j = lane; j < A.n; j += 64) a = fma(Ks[j * kFuseP + qi], A.alpha[j], a);
+        a = wave_sum(a);
+        for (int t = lane; t < A.nti; t += 64) q += part[t * kFuseQ + qi];
+        q = wave_sum(q);
+        if (lane == 0) {
+            fin[qi] = a;
+            fin[kFuseQ + qi] = q;
+        }
+    }
+    __syncthreads();
+    if (tid < kFuseQ && m0 + tid < A.M) gp_emit(A, m0 + tid, fin[tid], fin[kFuseQ + tid]);
 }
 
 // ------------------------------------------------------------------ acquisition search, local stage
@@ -138,9 +323,10 @@ __global__ __launch_bounds__(256) void k_chaos_points(const double *__restrict__
     U[t] = m < 1.0 ? m : 1.0;
 }
 
+// The centres after a round: from (C_src, Ce_src) to (C, Ce), which may be the same buffers.
 __global__ __launch_bounds__(256) void k_chaos_centres(const double *__restrict__ U, const double *__restrict__ e,
-                                                       int per, int nc, int d, double *__restrict__ C,
-                                                       double *__restrict__ Ce) {
+                                                       int per, int nc, int d, const double *C_src,
+                                                       const double *Ce_src, double *C, double *Ce) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= nc) return;
     const double *ec = e + (size_t)c * per;
@@ -151,10 +337,11 @@ __global__ __launch_bounds__(256) void k_chaos_centres(const double *__restrict_
             best = ec[k];
             j = k;
         }
-    if (best > Ce[c]) {
-        Ce[c] = best;
-        for (int k = 0; k < d; ++k) C[(size_t)c * d + k] = U[((size_t)c * per + j) * d + k];
-    }
+    const double ce = Ce_src[c];
+    const bool better = best > ce;
+    Ce[c] = better ? best : ce;
+    for (int k = 0; k < d; ++k)
+        C[(size_t)c * d + k] = better ? U[((size_t)c * per + j) * d + k] : C_src[(size_t)c * d + k];
 }
 
 __global__ __launch_bounds__(256) void k_chaos_step(double *__restrict__ z, int count) {
@@ -164,73 +351,153 @@ __global__ __launch_bounds__(256) void k_chaos_step(double *__restrict__ z, int 
     z[t] = (4.0 * v) * (1.0 - v);
 }
 
+// The global stage's points: rounds [count] copies of the chains at z0, each a step on from the one before;
+// z receives the chains after the last.
+__global__ __launch_bounds__(256) void k_chaos_rounds(const double *__restrict__ z0, int count, int rounds,
+                                                      double *__restrict__ pts, double *__restrict__ z) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= count) return;
+    double v = z0[t];
+    for (int r = 0; r < rounds; ++r) {
+        pts[(size_t)r * count + t] = v;
+        v = (4.0 * v) * (1.0 - v);
+    }
+    z[t] = v;
+}
+
 // ------------------------------------------------------------------ pools and greedy choice
 // The order of the search's selections: larger value first, lower index on ties (as a stable sort in
 // decreasing value). Values are taken to be finite.
 __device__ __forceinline__ bool ranks_before(double va, int ia, double vb, int ib) {
     return va > vb || (va == vb && ia < ib);
 }
+// Unsigned key of the same order as the values (-0 as 0)
+__device__ __forceinline__ unsigned long long rank_key(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v + 0.0);
+    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+}
 
-// Bitonic sort of n = 2^k (value, index) pairs in LDS by ranks_before (by_index: indices ascending).
-__device__ void lds_bitonic(double *sv, int *si, int n, bool by_index) {
-    for (int k = 2; k <= n; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = threadIdx.x; t < n; t += blockDim.x) {
-                const int u = t ^ j;
-                if (u <= t) continue;
-                const bool asc = (t & k) == 0;  // this pair's run is ordered ascending in rank
-                const bool ut = by_index ? si[u] < si[t] : ranks_before(sv[u], si[u], sv[t], si[t]);
-                const bool tu = by_index ? si[t] < si[u] : ranks_before(sv[t], si[t], sv[u], si[u]);
-                if (asc ? ut : tu) {
-                    const double v = sv[t];
-                    sv[t] = sv[u];
-                    sv[u] = v;
-                    const int i = si[t];
-                    si[t] = si[u];
-                    si[u] = i;
-                }
-            }
-            __syncthreads();
-        }
+// Exclusive prefix sum of v over the block's 1024 threads (thread order); total: the sum. scratch: 16 ints.
+__device__ __forceinline__ int block_scan_1024(int v, int *scratch, int &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
+    }
+    __syncthreads();
+    if (lane == 63) scratch[wave] = inc;
+    __syncthreads();
+    int base = 0;
+    total = 0;
+    for (int i = 0; i < 16; ++i) {
+        if (i < wave) base += scratch[i];
+        total += scratch[i];
+    }
+    return base + inc - v;
 }
 
 // One workgroup per round: the `keep` highest-ranked of the round's M values, written in index order
 // (values and their points) to the round's pool slot of min(M, keep) entries. M <= kPoolMax.
+// A radix select, 8 bits of the key a pass, finds the keep-th rank; it ends as soon as the keys that share
+// the prefix are all wanted. Each thread holds kPoolMax / 1024 consecutive values, so two prefix sums (the
+// wanted ties, then all chosen) give index order. A sort of the round took 125 us at M = 4096.
 __global__ __launch_bounds__(1024) void k_pool_top(const double *__restrict__ pts, const double *__restrict__ vals,
                                                    int M, int d, int keep, double *__restrict__ pool_pts,
                                                    double *__restrict__ pool_vals) {
-    __shared__ double sv[kPoolMax];
-    __shared__ int si[kPoolMax];
-    const int r = blockIdx.x;
+    constexpr int V = kPoolMax / 1024;
+    __shared__ int hist[256];
+    __shared__ int scratch[16];
+    __shared__ int found[2];
+    const int r = blockIdx.x, tid = threadIdx.x;
     const int kept = M < keep ? M : keep;
     const double *v = vals + (size_t)r * M;
     const double *p = pts + (size_t)r * M * d;
     double *ov = pool_vals + (size_t)r * kept;
     double *op = pool_pts + (size_t)r * kept * d;
-    if (M > keep) {
-        int n = 1;
-        while (n < M) n <<= 1;
-        for (int t = threadIdx.x; t < n; t += blockDim.x) {
-            sv[t] = t < M ? v[t] : -INFINITY;
-            si[t] = t < M ? t : 0x7fffffff;
+    if (M <= keep) {
+        for (int t = tid; t < M * d; t += blockDim.x) op[t] = p[t];
+        for (int t = tid; t < M; t += blockDim.x) ov[t] = v[t];
+        return;
+    }
+    const int per = (M + 1023) / 1024, first = tid * per;
+    unsigned long long key[V];
+    double val[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const bool in = i < per && first + i < M;
+        val[i] = in ? v[first + i] : 0.0;
+        key[i] = in ? rank_key(val[i]) : 0;  // 0 ranks below every finite value
+    }
+    // rank `need` (1-based) among the keys whose bits above `shift` equal prefix
+    unsigned long long prefix = 0;
+    int need = keep, shift = 64;
+    while (shift > 0) {
+        shift -= 8;
+        if (tid < 256) hist[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+            if (i < per && first + i < M && (shift == 56 || (key[i] >> (shift + 8)) == prefix))
+                atomicAdd(&hist[(int)((key[i] >> shift) & 255)], 1);
+        __syncthreads();
+        if (tid < 64) {
+            // 4 bins a lane, the highest bins in lane 0: the bin that holds the rank
+            int h[4], sum = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[i] = hist[255 - (4 * tid + i)];
+                sum += h[i];
+            }
+            int inc = sum;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(inc, off);
+                if (tid >= off) inc += o;
+            }
+            int above = inc - sum;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (above < need && need <= above + h[i]) {
+                    found[0] = 255 - (4 * tid + i);
+                    found[1] = above;
+                }
+                above += h[i];
+            }
         }
         __syncthreads();
-        lds_bitonic(sv, si, n, false);
-        // the first `keep` are the selection; put them back in index order
-        int m = 1;
-        while (m < keep) m <<= 1;
-        for (int t = keep + threadIdx.x; t < m; t += blockDim.x) si[t] = 0x7fffffff;
-        __syncthreads();
-        lds_bitonic(sv, si, m, true);
-    } else {
-        for (int t = threadIdx.x; t < M; t += blockDim.x) si[t] = t;
-        __syncthreads();
+        const int bin = found[0];
+        prefix = (prefix << 8) | (unsigned)bin;
+        need -= found[1];
+        if (hist[bin] == need) break;  // every key with this prefix is wanted
+        __syncthreads();               // hist and found are read
     }
-    for (int t = threadIdx.x; t < kept * d; t += blockDim.x) {
-        const int row = t / d, k = t - row * d;
-        op[t] = p[(size_t)si[row] * d + k];
+    int ties = 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        if (i < per && first + i < M && (key[i] >> shift) == prefix) ++ties;
+    int total;
+    int tie = block_scan_1024(ties, scratch, total);
+    int chosen = 0;
+    bool take[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const unsigned long long h = key[i] >> shift;
+        take[i] = i < per && first + i < M && (h > prefix || (h == prefix && tie < need));
+        if (i < per && first + i < M && h == prefix) ++tie;
+        chosen += take[i] ? 1 : 0;
     }
-    for (int t = threadIdx.x; t < kept; t += blockDim.x) ov[t] = v[si[t]];
+    int pos = block_scan_1024(chosen, scratch, total);
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+        if (take[i]) {
+            ov[pos] = val[i];
+            const double *src = p + (size_t)(first + i) * d;
+            double *dst = op + (size_t)pos * d;
+            for (int k = 0; k < d; ++k) dst[k] = src[k];
+            ++pos;
+        }
 }
 
 // Squared distance of two d-vectors, in coordinate order.
@@ -243,45 +510,76 @@ __device__ __forceinline__ double dist2(const double *a, const double *b, int d)
     return s;
 }
 
-// One workgroup: up to q pool entries in rank order, each at least sqrt(ex2) from the rows of `taken`
-// and from the entries chosen before it (a greedy choice: the best remaining entry is chosen and every
-// entry nearer than the exclusion to it is dropped). idx[0..count) receive the choices in order; *vmax
-// the largest pool value. N <= kGreedyMax.
+// alive[i] = 0 where entry i is nearer than sqrt(ex2) to a row of `taken`, else 1: four lanes per entry, a
+// quarter of the rows each, over the whole GPU (one workgroup took 8 ms for 12288 entries and 384 rows).
+__global__ __launch_bounds__(256) void k_screen(const double *__restrict__ pts, int N, int d,
+                                                const double *__restrict__ taken, int T, double ex2,
+                                                unsigned char *__restrict__ alive) {
+    const int i = blockIdx.x * 64 + (threadIdx.x >> 2), part = threadIdx.x & 3;
+    int near = 0;
+    if (i < N)
+        for (int t = part; !near && t < T; t += 4) near = dist2(pts + (size_t)i * d, taken + (size_t)t * d, d) < ex2;
+    near |= __shfl_xor(near, 1);
+    near |= __shfl_xor(near, 2);
+    if (i < N && part == 0) alive[i] = near ? 0 : 1;
+}
+
+// One workgroup: up to q pool entries in rank order, each at least sqrt(ex2) from the entries chosen before
+// it (a greedy choice: the best remaining entry is chosen and every entry nearer than the exclusion to it is
+// dropped), out of those alive (null: all). idx[0..count) receive the choices in order; *vmax the largest pool
+// value. N <= 1024 E. Thread t holds the values of entries t, t + 1024, ... in registers with its own best
+// one, renewed only when that one is dropped; the entries' first coordinates sit in LDS as floats, and a
+// distance is formed only where they are near enough for it to matter (a margin covers their rounding).
+// One barrier per choice: about 1.5 us each, against 10 us reading every entry's coordinates for each.
+template <int E>
 __global__ __launch_bounds__(1024) void k_greedy(const double *__restrict__ pts, const double *__restrict__ vals,
-                                                 int N, int d, const double *__restrict__ taken, int T, int q,
+                                                 int N, int d, const unsigned char *__restrict__ live, int q,
                                                  double ex2, int *__restrict__ idx, int *__restrict__ count,
                                                  double *__restrict__ vmax) {
-    __shared__ unsigned char alive[kGreedyMax];
-    __shared__ double wv[32];
-    __shared__ int wi[32];
-    __shared__ int pick;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+    extern __shared__ float first[];  // [N] first coordinates
+    __shared__ double wv[2][16];
+    __shared__ int wi[2][16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float reach = sqrtf((float)ex2) * 1.00001f;
+    double val[E];  // -infinity: dropped, or past the end
+    unsigned alive = 0xffffffffu;
     double mx = -INFINITY;
-    for (int i = tid; i < N; i += blockDim.x) {
-        const double *pi = pts + (size_t)i * d;
-        bool ok = true;
-        for (int t = 0; ok && t < T; ++t) ok = !(dist2(pi, taken + (size_t)t * d, d) < ex2);
-        alive[i] = ok ? 1 : 0;
-        mx = fmax(mx, vals[i]);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = tid + 1024 * e, ic = min(i, N - 1);
+        const double v = vals[ic];
+        const bool in = i < N;
+        if (in) first[i] = (float)pts[(size_t)i * d];
+        mx = in ? fmax(mx, v) : mx;
+        val[e] = in && (!live || live[ic]) ? v : -INFINITY;
     }
     for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-    if (lane == 0) wv[wave] = mx;
+    if (lane == 0) wv[1][wave] = mx;
     __syncthreads();
     if (tid == 0) {
-        double m = wv[0];
-        for (int w = 1; w < nw; ++w) m = fmax(m, wv[w]);
+        double m = wv[1][0];
+        for (int w = 1; w < 16; ++w) m = fmax(m, wv[1][w]);
         *vmax = m;
     }
     int n = 0;
+    bool renew = true;
+    double own = -INFINITY;
+    int own_i = 0x7fffffff;
     for (int it = 0; it < q; ++it) {
-        __syncthreads();  // alive[] updated, wv[] free
-        double bv = -INFINITY;
-        int bi = 0x7fffffff;
-        for (int i = tid; i < N; i += blockDim.x)
-            if (alive[i] && ranks_before(vals[i], i, bv, bi)) {
-                bv = vals[i];
-                bi = i;
-            }
+        if (renew) {
+            own = -INFINITY;
+            own_i = 0x7fffffff;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (val[e] > own) {  // ties keep the lower index
+                    own = val[e];
+                    own_i = tid + 1024 * e;
+                }
+            renew = false;
+        }
+        double bv = own;
+        int bi = own_i;
+#pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             const double ov = __shfl_xor(bv, off);
             const int oi = __shfl_xor(bi, off);
@@ -290,29 +588,51 @@ __global__ __launch_bounds__(1024) void k_greedy(const double *__restrict__ pts,
                 bi = oi;
             }
         }
+        const int s = it & 1;
         if (lane == 0) {
-            wv[wave] = bv;
-            wi[wave] = bi;
+            wv[s][wave] = bv;
+            wi[s][wave] = bi;
         }
-        __syncthreads();
-        if (tid == 0) {
-            double v = wv[0];
-            int i = wi[0];
-            for (int w = 1; w < nw; ++w)
-                if (ranks_before(wv[w], wi[w], v, i)) {
-                    v = wv[w];
-                    i = wi[w];
-                }
-            pick = (i == 0x7fffffff) ? -1 : i;
-            if (i != 0x7fffffff) idx[n] = i;
+        __syncthreads();  // the other slot is written only after the next barrier's predecessors read this one
+        bv = wv[s][lane & 15];
+        bi = wi[s][lane & 15];
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) {
+            const double ov = __shfl_xor(bv, off);
+            const int oi = __shfl_xor(bi, off);
+            if (ranks_before(ov, oi, bv, bi)) {
+                bv = ov;
+                bi = oi;
+            }
         }
-        __syncthreads();
-        const int pk = pick;
-        if (pk < 0) break;
+        if (bi == 0x7fffffff) break;
+        if (tid == 0) idx[n] = bi;
         ++n;
-        const double *pp = pts + (size_t)pk * d;
-        for (int i = tid; i < N; i += blockDim.x)
-            if (alive[i] && (i == pk || dist2(pts + (size_t)i * d, pp, d) < ex2)) alive[i] = 0;
+        const double *pp = pts + (size_t)bi * d;
+        const float p0 = first[bi];
+        unsigned close = 0;
+#pragma unroll 4
+        for (int e = 0; e < E; ++e) {
+            const float f = first[min(tid + 1024 * e, N - 1)];
+            const float margin = reach + 1e-6f * (fabsf(f) + fabsf(p0));
+            if (!(fabsf(f - p0) > margin)) close |= 1u << e;
+        }
+        close &= alive;
+        unsigned drop = 0;
+        while (close) {
+            const int e = __ffs(close) - 1;
+            close &= close - 1;
+            const int i = tid + 1024 * e;
+            if (i < N && (i == bi || dist2(pts + (size_t)i * d, pp, d) < ex2)) {
+                drop |= 1u << e;
+                renew |= i == own_i;
+            }
+        }
+        alive &= ~drop;
+        if (drop) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) val[e] = (drop >> e & 1u) ? -INFINITY : val[e];
+        }
     }
     if (tid == 0) *count = n;
 }
@@ -329,11 +649,6 @@ __global__ __launch_bounds__(256) void k_take_rows(const double *__restrict__ sr
     if (vdst && k == 0) vdst[r] = vsrc[idx[r]];
 }
 
-__global__ __launch_bounds__(256) void k_copy_f64(const double *__restrict__ src, double *__restrict__ dst, int n) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) dst[t] = src[t];
-}
-
 hipError_t launch_pool_top(const double *pts, const double *vals, int rounds, int M, int d, int keep, double *pool_pts,
                            double *pool_vals, hipStream_t st) {
     if (M > kPoolMax || keep < 1) return hipErrorInvalidValue;
@@ -342,10 +657,22 @@ hipError_t launch_pool_top(const double *pts, const double *vals, int rounds, in
     return hipGetLastError();
 }
 
-hipError_t launch_greedy(const double *pts, const double *vals, int N, int d, const double *taken, int T, int q,
+hipError_t launch_screen(const double *pts, int N, int d, const double *taken, int T, double ex2,
+                         unsigned char *alive, hipStream_t st) {
+    hipLaunchKernelGGL(k_screen, dim3((unsigned)((N + 63) / 64)), dim3(256), 0, st, pts, N, d, taken, T, ex2, alive);
+    return hipGetLastError();
+}
+
+hipError_t launch_greedy(const double *pts, const double *vals, int N, int d, const unsigned char *alive, int q,
                          double ex2, int *idx, int *count, double *vmax, hipStream_t st) {
     if (N > kGreedyMax) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_greedy, dim3(1), dim3(1024), 0, st, pts, vals, N, d, taken, T, q, ex2, idx, count, vmax);
+    const size_t lds = sizeof(float) * (size_t)std::max(N, 1);
+    if (N <= 4 * 1024)
+        hipLaunchKernelGGL(k_greedy<4>, dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count, vmax);
+    else if (N <= 16 * 1024)
+        hipLaunchKernelGGL(k_greedy<16>, dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count, vmax);
+    else
+        hipLaunchKernelGGL(k_greedy<32>, dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count, vmax);
     return hipGetLastError();
 }
 
@@ -358,8 +685,9 @@ hipError_t launch_take_rows(const double *src, const double *vsrc, const int *id
     return hipGetLastError();
 }
 
-hipError_t launch_copy_f64(const double *src, double *dst, int n, hipStream_t st) {
-    hipLaunchKernelGGL(k_copy_f64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, dst, n);
+hipError_t launch_chaos_rounds(const double *z0, int count, int rounds, double *pts, double *z, hipStream_t st) {
+    hipLaunchKernelGGL(k_chaos_rounds, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, z0, count, rounds, pts,
+                       z);
     return hipGetLastError();
 }
 
@@ -371,10 +699,10 @@ hipError_t launch_chaos_points(const double *z, const double *C, double r, int p
     return hipGetLastError();
 }
 
-hipError_t launch_chaos_centres(const double *U, const double *e, int per, int nc, int d, double *C, double *Ce,
-                                hipStream_t st) {
-    hipLaunchKernelGGL(k_chaos_centres, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, U, e, per, nc, d, C,
-                       Ce);
+hipError_t launch_chaos_centres(const double *U, const double *e, int per, int nc, int d, const double *C_src,
+                                const double *Ce_src, double *C, double *Ce, hipStream_t st) {
+    hipLaunchKernelGGL(k_chaos_centres, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, U, e, per, nc, d, C_src,
+                       Ce_src, C, Ce);
     return hipGetLastError();
 }
 
@@ -383,7 +711,29 @@ hipError_t launch_chaos_step(double *z, int count, hipStream_t st) {
     return hipGetLastError();
 }
 
+static size_t fused_lds(const GpEiArgs &a) {
+    return sizeof(double) * ((size_t)a.npad * kFuseP + (size_t)a.nti * kFuseQ + (size_t)kFuseQ * a.d + 2 * kFuseQ);
+}
+
+hipError_t launch_gp_pack(const GpEiArgs &a, double *xp, hipStream_t st) {
+    const size_t count = (size_t)a.npad * a.npad;
+    hipLaunchKernelGGL(k_gp_pack, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, a.linv, a.n, a.npad, xp);
+    return hipGetLastError();
+}
+
+hipError_t launch_gp_local(const GpEiArgs &a, const GpLocalArgs &l, hipStream_t st) {
+    if (!a.xp) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gp_fused<true>, dim3((unsigned)((a.M + kFuseQ - 1) / kFuseQ)), dim3(256), fused_lds(a), st, a,
+                       l);
+    return hipGetLastError();
+}
+
 hipError_t launch_gp_ei(const GpEiArgs &a, hipStream_t st) {
+    if (a.xp) {
+        hipLaunchKernelGGL(k_gp_fused<false>, dim3((unsigned)((a.M + kFuseQ - 1) / kFuseQ)), dim3(256), fused_lds(a),
+                           st, a, GpLocalArgs{});
+        return hipGetLastError();
+    }
     size_t blocks = ((size_t)a.M * a.npad + 255) / 256;
     if (blocks > 16384) blocks = 16384;
     hipLaunchKernelGGL(k_gp_kstar, dim3((unsigned)blocks), dim3(256), 0, st, a);

@@ -149,10 +149,27 @@ struct GpEiArgs {
     int npad;             // K* row stride (n rounded up to 64)
     int nti;              // row blocks of 64 in X
     double inv2l2, amp, m0, s, best, xi;
+    const double *xp;     // X in operand order (launch_gp_pack) for the fused kernel, null: the kernels below
     double *ks;           // scratch [M][npad]
     double *part;         // scratch [nti][M]
     double *mu, *sd;      // [M] or NULL
     double *ei;           // [M]
+};
+
+// Observations up to which the fused acquisition kernel runs: K* of 16 queries (136 bytes an observation)
+// then takes at most 136 KB of LDS.
+constexpr int kGpFuseMax = 1024;
+
+// One round of the acquisition search's local stage in the fused kernel (the queries are formed there):
+// query m belongs to centre m / per.
+struct GpLocalArgs {
+    double *z;                     // [P][d] chains, stepped in place
+    int P, per;
+    double r;                      // radius of this round
+    const double *U_prev, *e_prev; // previous round's points and EI (null: first round, no move)
+    const double *C_src, *Ce_src;  // centres before that move
+    double *C_dst, *Ce_dst;        // centres after it (other buffers; null: not wanted)
+    double *U;                     // [nc * per][d] out: this round's points
 };
 
 // Raster-adjoint components per candidate: c_0..c_5, mu_b, mu_c, dR.
@@ -258,22 +275,26 @@ hipError_t launch_adj_elem(const AdjElemArgs &a, hipStream_t st);
 hipError_t launch_grad_finish(const float *grad, int C, int ncomp, float *d_grad, uint32_t *status, hipStream_t st);
 hipError_t launch_mul_copy(const float *a, const float *b, float *out, size_t count, hipStream_t st);
 hipError_t launch_copy(const float *src, float *dst, size_t count, hipStream_t st);
+hipError_t launch_gp_pack(const GpEiArgs &a, double *xp, hipStream_t st);
+hipError_t launch_gp_local(const GpEiArgs &a, const GpLocalArgs &l, hipStream_t st);
 hipError_t launch_gp_ei(const GpEiArgs &a, hipStream_t st);
+hipError_t launch_chaos_rounds(const double *z0, int count, int rounds, double *pts, double *z, hipStream_t st);
 hipError_t launch_chaos_points(const double *z, const double *C, double r, int per, int nc, int d, double *U,
                                hipStream_t st);
-hipError_t launch_chaos_centres(const double *U, const double *e, int per, int nc, int d, double *C, double *Ce,
-                                hipStream_t st);
+hipError_t launch_chaos_centres(const double *U, const double *e, int per, int nc, int d, const double *C_src,
+                                const double *Ce_src, double *C, double *Ce, hipStream_t st);
 hipError_t launch_chaos_step(double *z, int count, hipStream_t st);
 // Pools and greedy choice of the acquisition search (kernels_gp.hip)
 constexpr int kPoolMax = 8192;     // values per round a pool is taken from
 constexpr int kGreedyMax = 32768;  // pool entries of one greedy choice
 hipError_t launch_pool_top(const double *pts, const double *vals, int rounds, int M, int d, int keep, double *pool_pts,
                            double *pool_vals, hipStream_t st);
-hipError_t launch_greedy(const double *pts, const double *vals, int N, int d, const double *taken, int T, int q,
+hipError_t launch_screen(const double *pts, int N, int d, const double *taken, int T, double ex2,
+                         unsigned char *alive, hipStream_t st);
+hipError_t launch_greedy(const double *pts, const double *vals, int N, int d, const unsigned char *alive, int q,
                          double ex2, int *idx, int *count, double *vmax, hipStream_t st);
 hipError_t launch_take_rows(const double *src, const double *vsrc, const int *idx, const int *count, int rows, int d,
                             double *dst, double *vdst, hipStream_t st);
-hipError_t launch_copy_f64(const double *src, double *dst, int n, hipStream_t st);
 hipError_t launch_ybar_final(const float *meas, const float *yK, float *ybar, int C, int nrays, size_t sino_cs,
                              hipStream_t st);
 

@@ -1615,7 +1615,16 @@ static boac_status gp_ei_args(const boac_gp_info *info, const double *d_u, const
     return BOAC_OK;
 }
 
-static boac_status gp_ei_scratch(boac_ctx *ctx, GpEiArgs *a) {
+// Scratch of an EI launch, and X in operand order for the fused kernel (once for every launch that uses
+// the same fit; up to kGpFuseMax observations).
+static boac_status gp_ei_scratch(boac_ctx *ctx, GpEiArgs *a, hipStream_t st) {
+    if (a->n <= kGpFuseMax) {
+        double *xp = nullptr;
+        BOAC_TRY(ensure_t(ctx, "gp_xp", (size_t)a->npad * a->npad, &xp));
+        HIP_TRY(launch_gp_pack(*a, xp, st));
+        a->xp = xp;
+        return BOAC_OK;
+    }
     BOAC_TRY(ensure_t(ctx, "gp_ks", (size_t)a->M * a->npad, &a->ks));
     return ensure_t(ctx, "gp_part", (size_t)a->M * a->nti, &a->part);
 }
@@ -1630,12 +1639,12 @@ boac_status boac_gp_ei(boac_ctx *ctx, const boac_gp_info *info, const double *d_
     BOAC_TRY(check_ptr(d_mu, "d_mu", true));
     BOAC_TRY(check_ptr(d_sigma, "d_sigma", true));
     CTX_CHECK();
-    BOAC_TRY(gp_ei_scratch(ctx, &a));
+    const hipStream_t st = (hipStream_t)stream;
+    BOAC_TRY(gp_ei_scratch(ctx, &a, st));
     a.q = d_q;
     a.mu = d_mu;
     a.sd = d_sigma;
     a.ei = d_ei;
-    const hipStream_t st = (hipStream_t)stream;
     return timed(ctx, BOAC_K_GP, 0.0, st, [&] { return launch_gp_ei(a, st); });
 }
 
@@ -1645,16 +1654,51 @@ static boac_status chaos_local_rounds(boac_ctx *ctx, GpEiArgs a, double *d_z, in
                                       double *d_centre_ei, int nc, double radius0, double shrink, int n_local,
                                       double *d_pts, double *d_vals, hipStream_t st) {
     const int per = P / nc, M = per * nc, d = a.d;
+    a.mu = a.sd = nullptr;
     double r = radius0;
+    if (a.xp) {
+        // one launch per round: it moves the centres by the round before (into the other of two buffers, as
+        // every workgroup of a centre forms the move for itself), so the last round's move is left
+        double *cb = nullptr, *ceb = nullptr;
+        BOAC_TRY(ensure_t(ctx, "gs_cbuf", (size_t)2 * nc * d, &cb));
+        BOAC_TRY(ensure_t(ctx, "gs_cebuf", (size_t)2 * nc, &ceb));
+        const double *C = d_centres, *Ce = d_centre_ei;
+        for (int t = 0; t < n_local; ++t) {
+            GpLocalArgs l{};
+            l.z = d_z;
+            l.P = P;
+            l.per = per;
+            l.r = r;
+            l.C_src = C;
+            l.Ce_src = Ce;
+            l.U = d_pts + (size_t)t * M * d;
+            if (t > 0) {
+                l.U_prev = d_pts + (size_t)(t - 1) * M * d;
+                l.e_prev = d_vals + (size_t)(t - 1) * M;
+                l.C_dst = cb + (size_t)(t & 1) * nc * d;
+                l.Ce_dst = ceb + (size_t)(t & 1) * nc;
+            }
+            a.ei = d_vals + (size_t)t * M;
+            BOAC_TRY(timed(ctx, BOAC_K_GP, 0.0, st, [&] { return launch_gp_local(a, l, st); }));
+            if (t > 0) {
+                C = l.C_dst;
+                Ce = l.Ce_dst;
+            }
+            r *= shrink;
+        }
+        if (n_local > 0)
+            HIP_TRY(launch_chaos_centres(d_pts + (size_t)(n_local - 1) * M * d, d_vals + (size_t)(n_local - 1) * M, per,
+                                         nc, d, C, Ce, d_centres, d_centre_ei, st));
+        return BOAC_OK;
+    }
     for (int t = 0; t < n_local; ++t) {
         double *U = d_pts + (size_t)t * M * d;
         double *e = d_vals + (size_t)t * M;
         HIP_TRY(launch_chaos_points(d_z, d_centres, r, per, nc, d, U, st));
         a.q = U;
         a.ei = e;
-        a.mu = a.sd = nullptr;
         BOAC_TRY(timed(ctx, BOAC_K_GP, 0.0, st, [&] { return launch_gp_ei(a, st); }));
-        HIP_TRY(launch_chaos_centres(U, e, per, nc, d, d_centres, d_centre_ei, st));
+        HIP_TRY(launch_chaos_centres(U, e, per, nc, d, d_centres, d_centre_ei, d_centres, d_centre_ei, st));
         HIP_TRY(launch_chaos_step(d_z, P * d, st));
         r *= shrink;
     }
@@ -1683,7 +1727,7 @@ boac_status boac_gp_chaos_local(boac_ctx *ctx, const boac_gp_info *info, const d
     if ((long long)P * d >= (1LL << 31) || (long long)n_local * M * d >= (1LL << 40))
         return fail(BOAC_EINVAL, "P x d or n_local x M x d too large");
     CTX_CHECK();
-    BOAC_TRY(gp_ei_scratch(ctx, &a));
+    BOAC_TRY(gp_ei_scratch(ctx, &a, (hipStream_t)stream));
     return chaos_local_rounds(ctx, a, d_z, P, d_centres, d_centre_ei, n_centres, radius0, shrink, n_local, d_pts,
                               d_vals, (hipStream_t)stream);
 }
@@ -1720,6 +1764,8 @@ boac_status boac_gp_chaos_search(boac_ctx *ctx, const boac_gp_info *info, const 
     double *z = nullptr, *gpts = nullptr, *gvals = nullptr, *lpts = nullptr, *lvals = nullptr, *pool = nullptr,
            *poolv = nullptr, *C = nullptr, *Ce = nullptr, *vmax = nullptr;
     int *idx = nullptr, *cnt = nullptr;
+    unsigned char *alive = nullptr;
+    BOAC_TRY(ensure_t(ctx, "gs_alive", (size_t)npool, &alive));
     BOAC_TRY(ensure_t(ctx, "gs_z", (size_t)P * d, &z));
     BOAC_TRY(ensure_t(ctx, "gs_gpts", (size_t)n_global * P * d, &gpts));
     BOAC_TRY(ensure_t(ctx, "gs_gvals", (size_t)n_global * P, &gvals));
@@ -1732,13 +1778,9 @@ boac_status boac_gp_chaos_search(boac_ctx *ctx, const boac_gp_info *info, const 
     BOAC_TRY(ensure_t(ctx, "gs_idx", (size_t)std::max(q, nc_max), &idx));
     BOAC_TRY(ensure_t(ctx, "gs_cnt", 2, &cnt));
     BOAC_TRY(ensure_t(ctx, "gs_max", 2, &vmax));
-    BOAC_TRY(gp_ei_scratch(ctx, &ag));
+    BOAC_TRY(gp_ei_scratch(ctx, &ag, st));
     // global stage: the chains' points of n_global rounds, their EI in one launch, each round's pool
-    HIP_TRY(launch_copy_f64(d_z0, z, P * d, st));
-    for (int t = 0; t < n_global; ++t) {
-        HIP_TRY(launch_copy_f64(z, gpts + (size_t)t * P * d, P * d, st));
-        HIP_TRY(launch_chaos_step(z, P * d, st));
-    }
+    HIP_TRY(launch_chaos_rounds(d_z0, P * d, n_global, gpts, z, st));
     ag.q = gpts;
     ag.ei = gvals;
     ag.mu = ag.sd = nullptr;
@@ -1746,7 +1788,7 @@ boac_status boac_gp_chaos_search(boac_ctx *ctx, const boac_gp_info *info, const 
     HIP_TRY(launch_pool_top(gpts, gvals, n_global, P, d, per_step, pool, poolv, st));
     // centres: the greedy choice over the global pool; their count fixes the local stage's split
     const int ng = (int)(kept * n_global);
-    HIP_TRY(launch_greedy(pool, poolv, ng, d, nullptr, 0, nc_max, exclusion * exclusion, idx, cnt, vmax, st));
+    HIP_TRY(launch_greedy(pool, poolv, ng, d, nullptr, nc_max, exclusion * exclusion, idx, cnt, vmax, st));
     int nc = 0;
     HIP_TRY(hipMemcpyAsync(&nc, cnt, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -1757,17 +1799,17 @@ boac_status boac_gp_chaos_search(boac_ctx *ctx, const boac_gp_info *info, const 
     long long nq = (long long)n_global * P;
     int nl_pool = 0;
     if (n_local > 0) {
-        GpEiArgs al{};
-        BOAC_TRY(gp_ei_args(info, d_u, d_linv, d_alpha, M, best, xi, &al));
-        BOAC_TRY(gp_ei_scratch(ctx, &al));
+        GpEiArgs al = ag;  // the same fit and scratch (M <= n_global P)
+        al.M = M;
         BOAC_TRY(chaos_local_rounds(ctx, al, z, P, C, Ce, nc, radius0, shrink, n_local, lpts, lvals, st));
         HIP_TRY(launch_pool_top(lpts, lvals, n_local, M, d, per_step, pool + (size_t)ng * d, poolv + ng, st));
         nl_pool = std::min(M, per_step) * n_local;
         nq += (long long)n_local * M;
     }
     // proposals: the greedy choice over every pool, away from the points taken
-    HIP_TRY(launch_greedy(pool, poolv, ng + nl_pool, d, d_taken, T, q, exclusion * exclusion, idx, cnt + 1, vmax + 1,
-                          st));
+    if (T > 0) HIP_TRY(launch_screen(pool, ng + nl_pool, d, d_taken, T, exclusion * exclusion, alive, st));
+    HIP_TRY(launch_greedy(pool, poolv, ng + nl_pool, d, T > 0 ? alive : nullptr, q, exclusion * exclusion, idx, cnt + 1,
+                          vmax + 1, st));
     HIP_TRY(launch_take_rows(pool, nullptr, idx, cnt + 1, q, d, d_props, nullptr, st));
     int count = 0;
     double mx = 0.0;
