@@ -152,40 +152,46 @@ constexpr int kFuseP = kFuseQ + 1;  // LDS row of K*: the odd pitch spreads a co
 // whole blocks, dealt back and forth so that the triangle's long rows spread evenly), the blocks' row
 // sums of squares, then k* . alpha and EI. K* never goes to memory and X passes through no LDS. The sums run
 // in k_gp_kstar's, k_gp_zsq's and k_gp_ei's order, so the values are theirs bit for bit. Bound by the
-// matrix cores: a 16 x 16 x 4 FP64 step takes 64 cycles of a SIMD.
+// matrix cores: a 16 x 16 x 4 FP64 step takes 64 cycles of a SIMD (246 us for 512 observations and 65536
+// queries, which take 415 us; the three kernels took 1343). A local round of 4096 queries at 384
+// observations takes 28 us (130 us as three EI kernels and three small ones).
 // LOCAL: the queries are a round's points of the local search, formed here (GpLocalArgs): the centre moves
 // to the first best point of its previous round, the points are set around it, the chains step.
-template <bool LOCAL>
-__global__ __launch_bounds__(256) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
+// D: the number of dimensions where it is known (8, the head model's), so that an observation's coordinates
+// are loaded together instead of one memory round trip each; 0: any.
+template <bool LOCAL, int D>
+__global__ __launch_bounds__(256, 2) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
     extern __shared__ double sm[];
     double *Ks = sm;                            // [npad][kFuseP]
     double *part = Ks + A.npad * kFuseP;        // [nti][kFuseQ]
     double *Qs = part + A.nti * kFuseQ;         // [kFuseQ][d]
     double *fin = Qs + kFuseQ * A.d;            // [2][kFuseQ]
+    double *al = fin + 2 * kFuseQ;              // [npad] alpha
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int m0 = blockIdx.x * kFuseQ, d = A.d;
+    const int m0 = blockIdx.x * kFuseQ, d = D ? D : A.d;
     if constexpr (LOCAL) {
-        // 32 lanes per query
-        const int hl = tid & 31;
-        for (int qi = tid >> 5; qi < kFuseQ; qi += 8) {
-            const int m = m0 + qi;
-            if (m >= A.M) {
-                for (int k = hl; k < d; k += 32) Qs[qi * d + k] = 0.0;
-                continue;
-            }
+        // 16 lanes per query
+        const int hl = tid & 15, qi = tid >> 4, m = m0 + qi;
+        if (m < A.M) {
             const int c = m / L.per;
+            const double ce = L.Ce_src[c];
             double bv = -INFINITY;
             int bi = 0;
             if (L.e_prev) {
-                for (int k = hl; k < L.per; k += 32) {
-                    const double v = L.e_prev[(size_t)c * L.per + k];
-                    if (v > bv) {
-                        bv = v;
-                        bi = k;
-                    }
+                const double *ep = L.e_prev + (size_t)c * L.per;
+                for (int k0 = hl; k0 < L.per; k0 += 64) {
+                    double v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = ep[min(k0 + 16 * i, L.per - 1)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (k0 + 16 * i < L.per && v[i] > bv) {
+                            bv = v[i];
+                            bi = k0 + 16 * i;
+                        }
                 }
 #pragma unroll
-                for (int off = 16; off > 0; off >>= 1) {
+                for (int off = 8; off > 0; off >>= 1) {
                     const double ov = __shfl_xor(bv, off);
                     const int oi = __shfl_xor(bi, off);
                     if (ov > bv || (ov == bv && oi < bi)) {
@@ -194,12 +200,11 @@ __global__ __launch_bounds__(256) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
                     }
                 }
             }
-            const double ce = L.Ce_src[c];
             const bool better = L.e_prev && bv > ce;
             const bool owner = L.C_dst && m == c * L.per;
-            for (int k = hl; k < d; k += 32) {
-                const double base = better ? L.U_prev[((size_t)c * L.per + bi) * d + k] : L.C_src[(size_t)c * d + k];
+            for (int k = hl; k < d; k += 16) {
                 const double z = L.z[(size_t)m * d + k];
+                const double base = better ? L.U_prev[((size_t)c * L.per + bi) * d + k] : L.C_src[(size_t)c * d + k];
                 const double wz = 2.0 * z - 1.0;
                 const double v = base + L.r * wz;
                 const double lo = v > 0.0 ? v : 0.0;  // clip to [0, 1] as max then min, comparisons only
@@ -210,6 +215,8 @@ __global__ __launch_bounds__(256) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
                 if (owner) L.C_dst[(size_t)c * d + k] = base;
             }
             if (owner && hl == 0) L.Ce_dst[c] = better ? bv : ce;
+        } else {
+            for (int k = hl; k < d; k += 16) Qs[qi * d + k] = 0.0;
         }
         // chains past the last centre's step too
         if (blockIdx.x == gridDim.x - 1)
@@ -224,25 +231,41 @@ __global__ __launch_bounds__(256) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
         }
     }
     __syncthreads();
-    // K*: 4 queries of one observation per thread and step
+    for (int j = tid; j < A.npad; j += blockDim.x) al[j] = j < A.n ? A.alpha[j] : 0.0;
+    // K*: 4 queries of one observation per thread and step, the next observation's coordinates in flight
+    constexpr int DU = D ? D : 1;
+    double un[DU];
+    auto fetch_u = [&](int j) {
+        if constexpr (D > 0) {
+            const double *uj = A.u + (size_t)min(j, A.n - 1) * D;
+#pragma unroll
+            for (int c = 0; c < D; ++c) un[c] = uj[c];
+        }
+    };
+    fetch_u(tid >> 2);
     for (int e = tid; e < 4 * A.npad; e += blockDim.x) {
         const int j = e >> 2, q0 = 4 * (e & 3);
-        double k[4] = {0.0, 0.0, 0.0, 0.0};
-        if (j < A.n) {
-            double d2[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int c = 0; c < d; ++c) {
-                const double u = A.u[(size_t)j * d + c];
+        double d2[4] = {0.0, 0.0, 0.0, 0.0};
+        auto add = [&](int c, double u) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const double t = Qs[(q0 + i) * d + c] - u;
-                    d2[i] = fma(t, t, d2[i]);
-                }
+            for (int i = 0; i < 4; ++i) {
+                const double t = Qs[(q0 + i) * d + c] - u;
+                d2[i] = fma(t, t, d2[i]);
             }
+        };
+        if constexpr (D > 0) {
+            double u[DU];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) k[i] = A.amp * exp(-d2[i] * A.inv2l2);
+            for (int c = 0; c < D; ++c) u[c] = un[c];
+            fetch_u((e + (int)blockDim.x) >> 2);
+#pragma unroll
+            for (int c = 0; c < D; ++c) add(c, u[c]);
+        } else {
+            const double *uj = A.u + (size_t)min(j, A.n - 1) * d;
+            for (int c = 0; c < d; ++c) add(c, uj[c]);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) Ks[j * kFuseP + q0 + i] = k[i];
+        for (int i = 0; i < 4; ++i) Ks[j * kFuseP + q0 + i] = j < A.n ? A.amp * exp(-d2[i] * A.inv2l2) : 0.0;
     }
     __syncthreads();
     const int lr = lane & 15, lk = lane >> 4;
@@ -258,30 +281,35 @@ __global__ __launch_bounds__(256) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
         v4d acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
-        double2 cur[4][2], nxt[4][2];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) cur[t][p] = x[t][64 * p];
-        for (int ch = 0; ch < nch; ++ch) {
-            const int cn = min(ch + 1, nch - 1);  // the last chunk reloads itself: no branch around the loads
+        // two chunk buffers in turn: one is loaded while the other's 16 matrix steps run (the barrier keeps the
+        // loads ahead of them); past the last chunk the loads repeat it, so that none sits in a branch
+        double2 xa[4][2], xb[4][2];
+        auto fetch = [&](double2(&v)[4][2], int ch) {
+            const size_t o = (size_t)min(ch, nch - 1) * 128;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int p = 0; p < 2; ++p) nxt[t][p] = x[t][(size_t)cn * 128 + 64 * p];
+                for (int p = 0; p < 2; ++p) v[t][p] = x[t][o + 64 * p];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto multiply = [&](const double2(&v)[4][2], int ch) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const double bq = Ks[(16 * ch + 4 * s + lk) * kFuseP + lr];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const double2 v = cur[t][s >> 1];
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((s & 1) ? v.y : v.x, bq, acc[t], 0, 0, 0);
-                }
+                for (int t = 0; t < 4; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((s & 1) ? v[t][s >> 1].y : v[t][s >> 1].x, bq, acc[t],
+                                                                  0, 0, 0);
             }
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int p = 0; p < 2; ++p) cur[t][p] = nxt[t][p];
+        };
+        fetch(xa, 0);
+        for (int ch = 0; ch < nch; ch += 2) {
+            fetch(xb, ch + 1);
+            multiply(xa, ch);
+            if (ch + 1 < nch) {
+                fetch(xa, ch + 2);
+                multiply(xb, ch + 1);
+            }
         }
         double s = 0.0;
 #pragma unroll
@@ -292,17 +320,29 @@ __global__ __launch_bounds__(256) void k_gp_fused(GpEiArgs A, GpLocalArgs L) {
         if (lane < 16) part[b * kFuseQ + lane] = ((s0 + s1) + s2) + s3;
     }
     __syncthreads();
-    for (int qi = w; qi < kFuseQ; qi += 4) {
-        double a = 0.0, q = 0.0;
-        for (int j = lane; j < A.n; j += 64) a = fma(Ks[j * kFuseP + qi], A.alpha[j], a);
-        a = wave_sum(a);
-        for (int t = lane; t < A.nti; t += 64) q += part[t * kFuseQ + qi];
-        q = wave_sum(q);
-        if (lane == 0) {
-            fin[qi] = a;
-            fin[kFuseQ + qi] = q;
-        }
+    // the wave's 4 queries w, w + 4, ... side by side
+    double a[4] = {0.0, 0.0, 0.0, 0.0}, q[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int j = lane; j < A.n; j += 64) {
+        const double v = al[j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = fma(Ks[j * kFuseP + w + 4 * i], v, a[i]);
     }
+    for (int t = lane; t < A.nti; t += 64)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] += part[t * kFuseQ + w + 4 * i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a[i] += __shfl_xor(a[i], off);
+            q[i] += __shfl_xor(q[i], off);
+        }
+    if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            fin[w + 4 * i] = a[i];
+            fin[kFuseQ + w + 4 * i] = q[i];
+        }
     __syncthreads();
     if (tid < kFuseQ && m0 + tid < A.M) gp_emit(A, m0 + tid, fin[tid], fin[kFuseQ + tid]);
 }
@@ -402,7 +442,7 @@ __device__ __forceinline__ int block_scan_1024(int v, int *scratch, int &total) 
 // (values and their points) to the round's pool slot of min(M, keep) entries. M <= kPoolMax.
 // A radix select, 8 bits of the key a pass, finds the keep-th rank; it ends as soon as the keys that share
 // the prefix are all wanted. Each thread holds kPoolMax / 1024 consecutive values, so two prefix sums (the
-// wanted ties, then all chosen) give index order. A sort of the round took 125 us at M = 4096.
+// wanted ties, then all chosen) give index order. 16-23 us for 16-32 rounds of 4096 (125 us as a sort).
 __global__ __launch_bounds__(1024) void k_pool_top(const double *__restrict__ pts, const double *__restrict__ vals,
                                                    int M, int d, int keep, double *__restrict__ pool_pts,
                                                    double *__restrict__ pool_vals) {
@@ -500,25 +540,37 @@ __global__ __launch_bounds__(1024) void k_pool_top(const double *__restrict__ pt
         }
 }
 
-// Squared distance of two d-vectors, in coordinate order.
+// Squared distance of two d-vectors, in coordinate order. D: d where it is known (the loads then go out
+// together), else 0.
+template <int D>
 __device__ __forceinline__ double dist2(const double *a, const double *b, int d) {
     double s = 0.0;
-    for (int k = 0; k < d; ++k) {
-        const double e = a[k] - b[k];
-        s += e * e;
+    if constexpr (D > 0) {
+        double e[D];
+#pragma unroll
+        for (int k = 0; k < D; ++k) e[k] = a[k] - b[k];
+#pragma unroll
+        for (int k = 0; k < D; ++k) s += e[k] * e[k];
+    } else {
+        for (int k = 0; k < d; ++k) {
+            const double e = a[k] - b[k];
+            s += e * e;
+        }
     }
     return s;
 }
 
 // alive[i] = 0 where entry i is nearer than sqrt(ex2) to a row of `taken`, else 1: four lanes per entry, a
-// quarter of the rows each, over the whole GPU (one workgroup took 8 ms for 12288 entries and 384 rows).
+// quarter of the rows each, over the whole GPU (24 us for 12288 entries and 384 rows; one workgroup, inside the
+// greedy choice, took 8 ms).
+template <int D>
 __global__ __launch_bounds__(256) void k_screen(const double *__restrict__ pts, int N, int d,
                                                 const double *__restrict__ taken, int T, double ex2,
                                                 unsigned char *__restrict__ alive) {
     const int i = blockIdx.x * 64 + (threadIdx.x >> 2), part = threadIdx.x & 3;
     int near = 0;
     if (i < N)
-        for (int t = part; !near && t < T; t += 4) near = dist2(pts + (size_t)i * d, taken + (size_t)t * d, d) < ex2;
+        for (int t = part; t < T; t += 4) near |= dist2<D>(pts + (size_t)i * d, taken + (size_t)t * d, d) < ex2;
     near |= __shfl_xor(near, 1);
     near |= __shfl_xor(near, 2);
     if (i < N && part == 0) alive[i] = near ? 0 : 1;
@@ -528,15 +580,17 @@ __global__ __launch_bounds__(256) void k_screen(const double *__restrict__ pts, 
 // it (a greedy choice: the best remaining entry is chosen and every entry nearer than the exclusion to it is
 // dropped), out of those alive (null: all). idx[0..count) receive the choices in order; *vmax the largest pool
 // value. N <= 1024 E. Thread t holds the values of entries t, t + 1024, ... in registers with its own best
-// one, renewed only when that one is dropped; the entries' first coordinates sit in LDS as floats, and a
-// distance is formed only where they are near enough for it to matter (a margin covers their rounding).
-// One barrier per choice: about 1.5 us each, against 10 us reading every entry's coordinates for each.
-template <int E>
+// one, renewed only when that one is dropped; the entries' first coordinates (two up to 16384 entries, one
+// above: the LDS) are kept as floats, and a distance is formed only where they are near enough for it to
+// matter (a margin covers their rounding). One barrier per choice. 64 choices out of 12288 entries take
+// 345 us and out of 4096 entries 127 us (665 us with every entry's coordinates read for each choice).
+template <int E, int D>
 __global__ __launch_bounds__(1024) void k_greedy(const double *__restrict__ pts, const double *__restrict__ vals,
                                                  int N, int d, const unsigned char *__restrict__ live, int q,
                                                  double ex2, int *__restrict__ idx, int *__restrict__ count,
                                                  double *__restrict__ vmax) {
-    extern __shared__ float first[];  // [N] first coordinates
+    constexpr int NF = E <= 16 ? 2 : 1;
+    extern __shared__ float first[];  // [N][NF] first coordinates
     __shared__ double wv[2][16];
     __shared__ int wi[2][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -549,7 +603,9 @@ __global__ __launch_bounds__(1024) void k_greedy(const double *__restrict__ pts,
         const int i = tid + 1024 * e, ic = min(i, N - 1);
         const double v = vals[ic];
         const bool in = i < N;
-        if (in) first[i] = (float)pts[(size_t)i * d];
+        if (in)
+#pragma unroll
+            for (int k = 0; k < NF; ++k) first[i * NF + k] = (float)pts[(size_t)i * d + min(k, d - 1)];
         mx = in ? fmax(mx, v) : mx;
         val[e] = in && (!live || live[ic]) ? v : -INFINITY;
     }
@@ -609,13 +665,19 @@ __global__ __launch_bounds__(1024) void k_greedy(const double *__restrict__ pts,
         if (tid == 0) idx[n] = bi;
         ++n;
         const double *pp = pts + (size_t)bi * d;
-        const float p0 = first[bi];
+        float p[NF];
+#pragma unroll
+        for (int k = 0; k < NF; ++k) p[k] = first[bi * NF + k];
         unsigned close = 0;
 #pragma unroll 4
         for (int e = 0; e < E; ++e) {
-            const float f = first[min(tid + 1024 * e, N - 1)];
-            const float margin = reach + 1e-6f * (fabsf(f) + fabsf(p0));
-            if (!(fabsf(f - p0) > margin)) close |= 1u << e;
+            bool far = false;
+#pragma unroll
+            for (int k = 0; k < NF; ++k) {
+                const float f = first[min(tid + 1024 * e, N - 1) * NF + k];
+                far |= fabsf(f - p[k]) > reach + 1e-6f * (fabsf(f) + fabsf(p[k]));
+            }
+            if (!far) close |= 1u << e;
         }
         close &= alive;
         unsigned drop = 0;
@@ -623,7 +685,7 @@ __global__ __launch_bounds__(1024) void k_greedy(const double *__restrict__ pts,
             const int e = __ffs(close) - 1;
             close &= close - 1;
             const int i = tid + 1024 * e;
-            if (i < N && (i == bi || dist2(pts + (size_t)i * d, pp, d) < ex2)) {
+            if (i < N && (i == bi || dist2<D>(pts + (size_t)i * d, pp, d) < ex2)) {
                 drop |= 1u << e;
                 renew |= i == own_i;
             }
@@ -659,20 +721,35 @@ hipError_t launch_pool_top(const double *pts, const double *vals, int rounds, in
 
 hipError_t launch_screen(const double *pts, int N, int d, const double *taken, int T, double ex2,
                          unsigned char *alive, hipStream_t st) {
-    hipLaunchKernelGGL(k_screen, dim3((unsigned)((N + 63) / 64)), dim3(256), 0, st, pts, N, d, taken, T, ex2, alive);
+    const dim3 grid((unsigned)((N + 63) / 64));
+    if (d == 8)
+        hipLaunchKernelGGL(k_screen<8>, grid, dim3(256), 0, st, pts, N, d, taken, T, ex2, alive);
+    else
+        hipLaunchKernelGGL(k_screen<0>, grid, dim3(256), 0, st, pts, N, d, taken, T, ex2, alive);
     return hipGetLastError();
+}
+
+template <int E>
+static void greedy_go(const double *pts, const double *vals, int N, int d, const unsigned char *alive, int q, double ex2,
+                      int *idx, int *count, double *vmax, hipStream_t st) {
+    const size_t lds = sizeof(float) * (size_t)N * (E <= 16 ? 2 : 1);
+    if (d == 8)
+        hipLaunchKernelGGL((k_greedy<E, 8>), dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count,
+                           vmax);
+    else
+        hipLaunchKernelGGL((k_greedy<E, 0>), dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count,
+                           vmax);
 }
 
 hipError_t launch_greedy(const double *pts, const double *vals, int N, int d, const unsigned char *alive, int q,
                          double ex2, int *idx, int *count, double *vmax, hipStream_t st) {
-    if (N > kGreedyMax) return hipErrorInvalidValue;
-    const size_t lds = sizeof(float) * (size_t)std::max(N, 1);
+    if (N < 1 || N > kGreedyMax) return hipErrorInvalidValue;
     if (N <= 4 * 1024)
-        hipLaunchKernelGGL(k_greedy<4>, dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count, vmax);
+        greedy_go<4>(pts, vals, N, d, alive, q, ex2, idx, count, vmax, st);
     else if (N <= 16 * 1024)
-        hipLaunchKernelGGL(k_greedy<16>, dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count, vmax);
+        greedy_go<16>(pts, vals, N, d, alive, q, ex2, idx, count, vmax, st);
     else
-        hipLaunchKernelGGL(k_greedy<32>, dim3(1), dim3(1024), lds, st, pts, vals, N, d, alive, q, ex2, idx, count, vmax);
+        greedy_go<32>(pts, vals, N, d, alive, q, ex2, idx, count, vmax, st);
     return hipGetLastError();
 }
 
@@ -712,7 +789,8 @@ hipError_t launch_chaos_step(double *z, int count, hipStream_t st) {
 }
 
 static size_t fused_lds(const GpEiArgs &a) {
-    return sizeof(double) * ((size_t)a.npad * kFuseP + (size_t)a.nti * kFuseQ + (size_t)kFuseQ * a.d + 2 * kFuseQ);
+    return sizeof(double) * ((size_t)a.npad * kFuseP + (size_t)a.nti * kFuseQ + (size_t)kFuseQ * a.d + 2 * kFuseQ +
+                             a.npad);
 }
 
 hipError_t launch_gp_pack(const GpEiArgs &a, double *xp, hipStream_t st) {
@@ -721,19 +799,23 @@ hipError_t launch_gp_pack(const GpEiArgs &a, double *xp, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_gp_local(const GpEiArgs &a, const GpLocalArgs &l, hipStream_t st) {
-    if (!a.xp) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gp_fused<true>, dim3((unsigned)((a.M + kFuseQ - 1) / kFuseQ)), dim3(256), fused_lds(a), st, a,
-                       l);
+template <bool LOCAL>
+static hipError_t fused_go(const GpEiArgs &a, const GpLocalArgs &l, hipStream_t st) {
+    const dim3 grid((unsigned)((a.M + kFuseQ - 1) / kFuseQ));
+    if (a.d == 8)
+        hipLaunchKernelGGL((k_gp_fused<LOCAL, 8>), grid, dim3(256), fused_lds(a), st, a, l);
+    else
+        hipLaunchKernelGGL((k_gp_fused<LOCAL, 0>), grid, dim3(256), fused_lds(a), st, a, l);
     return hipGetLastError();
 }
 
+hipError_t launch_gp_local(const GpEiArgs &a, const GpLocalArgs &l, hipStream_t st) {
+    if (!a.xp) return hipErrorInvalidValue;
+    return fused_go<true>(a, l, st);
+}
+
 hipError_t launch_gp_ei(const GpEiArgs &a, hipStream_t st) {
-    if (a.xp) {
-        hipLaunchKernelGGL(k_gp_fused<false>, dim3((unsigned)((a.M + kFuseQ - 1) / kFuseQ)), dim3(256), fused_lds(a),
-                           st, a, GpLocalArgs{});
-        return hipGetLastError();
-    }
+    if (a.xp) return fused_go<false>(a, GpLocalArgs{}, st);
     size_t blocks = ((size_t)a.M * a.npad + 255) / 256;
     if (blocks > 16384) blocks = 16384;
     hipLaunchKernelGGL(k_gp_kstar, dim3((unsigned)blocks), dim3(256), 0, st, a);

@@ -156,8 +156,8 @@ struct GpEiArgs {
     double *ei;           // [M]
 };
 
-// Observations up to which the fused acquisition kernel runs: K* of 16 queries (136 bytes an observation)
-// then takes at most 136 KB of LDS.
+// Observations up to which the fused acquisition kernel runs: K* of 16 queries and alpha (144 bytes an
+// observation) and the rest then take at most 155 KiB of LDS.
 constexpr int kGpFuseMax = 1024;
 
 // One round of the acquisition search's local stage in the fused kernel (the queries are formed there):
