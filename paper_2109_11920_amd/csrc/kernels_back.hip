@@ -606,15 +606,19 @@ __device__ __forceinline__ void back_epilogue(const DevGeom &g, const BackArgs &
     }
 }
 
-// Column-group variant of the slid-block gather (n_samples a multiple of 4). The host aligns the
-// block's first sample row to a multiple of 4, so the 4 samples k..k+3 (k = first row + 4 j) of a bin
+// Column-group variant of the slid-block gather. The host aligns the block's first sample row to a
+// multiple of 4, so the 4 samples k..k+3 (k = first row + 4 j) of a bin
 // are one aligned 16-byte load in the attenuation layout (sample fastest inside a 4 x 8 block): thread
 // t stages bin t % 32 of rows 4 (t / 32) .. + 3 with one 16-byte load per candidate, a quarter of the
 // vector-memory instructions of the slot variant (which is bound by its vector-memory pipeline), and
 // 8 lanes on consecutive bins read one whole 128-byte line. All 4 samples share the bin's ray weight,
 // folded in while staging as in the slot variant. A group is loaded unless all of it lies outside the
 // union of the tile pixels' supports (tested at its centre with half widths grown by 1.5 samples); a
-// skipped group keeps finite values, gathered only with weight 0.
+// skipped group keeps finite values, gathered only with weight 0. Where n_samples is no multiple of 4, a
+// block at the rays' end also stages the layout's padding rows; they hold no sample, so their slots are
+// set to 0 (TAIL; a variant of its own, as even the untaken branch costs the gather 6%). Such sizes once took
+// the slot variant without opposed-ray pairing, twice the bytes and angles: 110 us per launch for 109 x 109
+// images, 90 angles and 37 candidates, against 60 us, and 94 us against 36 us in the projection.
 // PAIRED (opposed-ray pairing, g.nah = na/2): the slab of angle a < na/2 also stands for angle
 // a + na/2, whose sample (nb-1-b, nt-1-k) sits at sample (b, k) of angle a with attenuation
 // exp(-T_ab) / att and the same bilinear weights; each staged slot holds both contributions,
@@ -627,7 +631,7 @@ __device__ __forceinline__ void back_epilogue(const DevGeom &g, const BackArgs &
 // on the LDS region lds. live = false: a stand-in workgroup beyond the grid (the persistent executor
 // runs workgroups four to a 1024-thread group) that takes part in every barrier and loads and writes
 // nothing.
-template <int CG, bool WEIGHTED, bool PAIRED, bool SPLIT>
+template <int CG, bool WEIGHTED, bool PAIRED, bool SPLIT, bool TAIL>
 __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, bool live, DevGeom g, BackCfg T,
                                                  BackArgs A, int mode) {
     constexpr int P = kSlidBlock;
@@ -790,6 +794,13 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
                     v[q] = WEIGHTED ? x * zv[q] : x;
                 }
             }
+            if constexpr (TAIL) {
+                if (cur.y + P > g.nt) {  // uniform: the block reaches past the last sample
+                    const bool real = cur.y + 4 * kb + t < g.nt;
+#pragma unroll
+                    for (int q = 0; q < CG; ++q) v[q] = real ? v[q] : 0.f;
+                }
+            }
             float *d = lds + ((4 * kb + t) * PL + bb) * V;
             if constexpr (CG == 8) {
                 reinterpret_cast<float4 *>(d)[0] = make_float4(v[0], v[1], v[2], v[3]);
@@ -878,10 +889,10 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
 }
 
 #ifndef BOAC_BODIES_ONLY
-template <int CG, bool WEIGHTED, bool PAIRED, bool SPLIT>
+template <int CG, bool WEIGHTED, bool PAIRED, bool SPLIT, bool TAIL>
 __global__ __launch_bounds__(256) void k_back_col4(DevGeom g, BackCfg T, BackArgs A, int mode) {
     extern __shared__ float lds[];
-    k_back_col4_body<CG, WEIGHTED, PAIRED, SPLIT>(blockIdx.x, threadIdx.x, lds, true, g, T, A, mode);
+    k_back_col4_body<CG, WEIGHTED, PAIRED, SPLIT, TAIL>(blockIdx.x, threadIdx.x, lds, true, g, T, A, mode);
 }
 #endif
 
@@ -901,21 +912,30 @@ __global__ __launch_bounds__(256) void k_back_combine(DevGeom g, BackArgs A, int
 #endif
 
 #ifndef BOAC_BODIES_ONLY
-template <int CG, bool SPLIT>
+template <int CG, bool SPLIT, bool TAIL>
 static void back_col4_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     const int ngroups = (a.C + CG - 1) / CG;
     const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * ngroups * (SPLIT ? bc.asplit : 1)));
     const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
     if (a.E) {
         if (weighted)
-            hipLaunchKernelGGL((k_back_col4<CG, true, true, SPLIT>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+            hipLaunchKernelGGL((k_back_col4<CG, true, true, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
         else
-            hipLaunchKernelGGL((k_back_col4<CG, false, true, SPLIT>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+            hipLaunchKernelGGL((k_back_col4<CG, false, true, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a,
+                               mode);
     } else if (weighted) {
-        hipLaunchKernelGGL((k_back_col4<CG, true, false, SPLIT>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_col4<CG, true, false, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     } else {
-        hipLaunchKernelGGL((k_back_col4<CG, false, false, SPLIT>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_col4<CG, false, false, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     }
+}
+
+template <int CG, bool SPLIT>
+static void back_col4_tail(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
+    if (g.nt & 3)
+        back_col4_go<CG, SPLIT, true>(g, bc, a, mode, st);
+    else
+        back_col4_go<CG, SPLIT, false>(g, bc, a, mode, st);
 }
 
 template <int CG>
@@ -923,12 +943,12 @@ static hipError_t back_col4(const DevGeom &g, const BackCfg &bc, const BackArgs 
     if (bc.asplit < 1 || (bc.asplit > 1 && !a.blk_out)) return hipErrorInvalidValue;
     if (a.E && g.nah * 2 != g.na) return hipErrorInvalidValue;
     if (bc.asplit > 1) {
-        back_col4_go<CG, true>(g, bc, a, mode, st);
+        back_col4_tail<CG, true>(g, bc, a, mode, st);
         const size_t n = (size_t)a.C * g.n * g.n;
         hipLaunchKernelGGL(k_back_combine, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, a,
                            (g.nah + 7) / 8, mode);
     } else {
-        back_col4_go<CG, false>(g, bc, a, mode, st);
+        back_col4_tail<CG, false>(g, bc, a, mode, st);
     }
     return hipGetLastError();
 }
@@ -963,9 +983,9 @@ static hipError_t back_tile(const DevGeom &g, const BackCfg &bc, const BackArgs 
 hipError_t launch_back(int mode, const DevGeom &g, const BackCfg &bc, const BackArgs &a, hipStream_t st) {
     if (TaskRecorder *r = task_recorder()) {
         if (bc.slid != 2 || bc.asplit != 1 || !(bc.cg == 1 || bc.cg == 2 || bc.cg == 4) || bc.tw != 16 ||
-            bc.th != 16 || bc.hb != 1)
+            bc.th != 16 || bc.hb != 1 || (g.nt & 3))
             return record_unsupported(r, "backprojection outside the column-group gather (one to four candidates per "
-                                         "workgroup, no angle split)");
+                                         "workgroup, no angle split, a sample count that is a multiple of 4)");
         if (a.E && g.nah * 2 != g.na) return hipErrorInvalidValue;
         const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
         TaskRec t{};

@@ -366,11 +366,12 @@ static boac_status rect_table(boac_ctx *ctx, const boac_geom &g, BackCfg *bc, in
                 if (wb > kSlidBlock || wk > kSlidBlock)
                     return fail(BOAC_EDEVICE, "internal: footprint %dx%d exceeds the %d-block", wb, wk, kSlidBlock);
                 const int b0 = std::min(std::max(b_lo, 0), g.n_bins - kSlidBlock);
-                int k0 = std::min(std::max(k_lo, 0), g.n_samples - kSlidBlock);
+                // column-group variant: the first sample row a multiple of 4; the block ends inside the
+                // layout's rows (n_samples rounded up to 4), and must still reach the clipped footprint's
+                // last row
+                const int rows = bc->slid == 2 ? (g.n_samples + 3) / 4 * 4 : g.n_samples;
+                int k0 = std::min(std::max(k_lo, 0), rows - kSlidBlock);
                 if (bc->slid == 2) {
-                    // column-group variant: the first sample row a multiple of 4 (n_samples is one, so
-                    // the block still ends inside the sinogram); it must still reach the clipped
-                    // footprint's last row
                     k0 &= ~3;
                     if (std::min(k_hi, g.n_samples - 1) >= k0 + kSlidBlock)
                         return fail(BOAC_EDEVICE, "internal: aligned footprint exceeds the %d-block", kSlidBlock);
@@ -603,7 +604,6 @@ static bool back_cfg_ok(const BackCfg &b) {
 // largest offset is below 2 cg bytes-per-candidate).
 static bool slid_ok(const boac_geom &g, const BackCfg &b) {
     if (!(b.slid == 1 || b.slid == 2) || b.tw != 16 || b.th != 16 || b.hb != 1) return false;
-    if (b.slid == 2 && g.n_samples % 4 != 0) return false;
     if (!(b.cg == 1 || b.cg == 2 || b.cg == 4 || b.cg == 8) || b.lds > kLdsBudget) return false;
     if (b.wbmax > kSlidBlock || b.wkmax > kSlidBlock) return false;
     if (g.n_bins < kSlidBlock || g.n_samples < kSlidBlock) return false;
