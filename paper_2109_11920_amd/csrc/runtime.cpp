@@ -482,34 +482,79 @@ static std::string shape_key(const char *kind, const boac_geom &g, int C, int ex
 // gather): the unbatched evaluation and small calls, where a plan for many candidates leaves CUs idle.
 constexpr int kFewCand = 8;
 
+// Modelled time (cycles) of a single-stage ray launch of `wgs` workgroups of w waves, rpt rays per thread: the
+// workgroups a CU holds (LDS, registers) run in rounds; a round costs its image stage (LDS bytes over its
+// threads) and a fixed part, and per ray pass and 16 samples a latency plus the vector work of the waves on a
+// SIMD. Constants fitted to sweeps of every block of 256 to 1024 threads and 1 to 4 rays per thread at 18
+// shapes (64 to 192 pixels, 60 to 256 angles, 9 to 100 candidates): its choice is within 3% of the best
+// measured one on average and 17% at worst.
+struct RayCost {
+    double latency, valu, stage, fixed;
+    int waves;  // waves a SIMD holds (registers)
+};
+constexpr RayCost kCostOne{1600, 4000, 3.9, 470, 7};       // projection of one candidate
+constexpr RayCost kCostPair{1840, 4820, 2.0, 13500, 4};    // of two
+constexpr RayCost kCostSweep{4060, 1970, 226, 3450, 4};    // reverse sweep, tail
+static double ray_cost(const RayCost &k, int n_cu, int n_samples, size_t lds, long wgs, int w, int rpt) {
+    const long held = std::max<long>(1, std::min<long>((long)(160 * 1024 / (lds + 512)), 4L * k.waves / w));
+    const long rounds = (wgs + n_cu * held - 1) / (n_cu * held);
+    auto round = [&](long n) {
+        const long per_cu = (n + n_cu - 1) / n_cu;
+        return rpt * (n_samples / 16.0) * (k.latency + k.valu * 0.25 * (double)(per_cu * w)) +
+               k.stage * (double)lds / (64.0 * w) + 800.0 + k.fixed;
+    };
+    return (double)(rounds - 1) * round(n_cu * held) + round(wgs - (rounds - 1) * n_cu * held);
+}
+
 // nah: angles whose rays the kernels walk (n_angles, or half of them with opposed-ray pairing).
 static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg *rc, Bands *bands, int nah) {
     make_bands(g.n, comps, rc, bands);
     const int nrays = nah * g.n_bins;
-    // the paired forward projection where both images fit one stage (default on)
+    // the paired forward projection where both images fit one stage
     const bool pair_fits = comps == 1 && rc->single && 2 * rc->lds <= kLdsBudget && C >= 2;
-    rc->pair = pair_fits;
-    // default: 1024-thread workgroups (the image stage is shared by more waves, and a stage that fills
-    // the LDS still gives 16 waves per CU), one resident per CU; the rays per thread that minimise
-    // (rounds of workgroups over the CUs) x (rays per thread + a fixed cost per workgroup: the image
-    // stage, the first loads and the epilogue, about 0.6 of a ray pass as measured on the paired
-    // projection at 96-192 candidates). A paired projection has one workgroup per chunk and candidate
-    // pair. Where even one ray per thread leaves CUs without a workgroup, smaller workgroups.
-    const long groups = pair_fits ? (C + 1) / 2 : C;
+    rc->pair = false;
     rc->block = 1024;
     rc->rpt = 1;
-    double best = 0.0;
-    for (int rpt : {4, 2, 1}) {
-        const long wgs = (long)((nrays + 1024 * rpt - 1) / (1024 * rpt)) * groups;
-        const double cost = (double)((wgs + ctx->n_cu - 1) / ctx->n_cu) * (rpt + 0.6);
-        if (rpt == 4 || cost < best) {
-            best = cost;
-            rc->rpt = rpt;
+    if (rc->single) {
+        // the block size and rays per thread of least modelled time: a workgroup holds most of a CU's LDS, so
+        // what counts is that the workgroups fill whole rounds over the CUs. Earlier plans used powers of two:
+        // 288 workgroups of 512 threads for 64 candidates at 128 pixels and 72 angles, two rounds, 70 us
+        // against 43 us for 256 of 576 threads; 16 candidates at 192 pixels 86 against 51 us, the reverse
+        // sweep there 167 against 119 us.
+        double best = 0.0;
+        for (int pair = pair_fits ? 1 : 0; pair >= 0; --pair) {
+            const long groups = pair ? (C + 1) / 2 : C;
+            for (int block = 1024; block >= 256; block -= 64)
+                for (int rpt = 1; rpt <= 4; ++rpt) {
+                    const long wgs = (long)((nrays + block * rpt - 1) / (block * rpt)) * groups;
+                    const double cost = ray_cost(comps == 2 ? kCostSweep : pair ? kCostPair : kCostOne, ctx->n_cu,
+                                                 g.n_samples, pair ? 2 * rc->lds : rc->lds, wgs, block / 64, rpt);
+                    if (best == 0.0 || cost < best) {
+                        best = cost;
+                        rc->block = block;
+                        rc->rpt = rpt;
+                        rc->pair = pair != 0;
+                    }
+                    if (wgs <= ctx->n_cu) break;  // more rays per thread would only idle CUs
+                }
         }
-    }
-    if ((long)((nrays + 1023) / 1024) * groups < ctx->n_cu) {
-        rc->rpt = 1;
-        rc->block = ((long)((nrays + 511) / 512) * groups >= ctx->n_cu) ? 512 : 256;
+    } else {
+        // row bands: 1024-thread workgroups, one resident per CU; the rays per thread that minimise (rounds
+        // over the CUs) x (rays per thread + a workgroup's fixed cost, about 0.6 of a ray pass). Where even one
+        // ray per thread leaves CUs without a workgroup, smaller workgroups.
+        double best = 0.0;
+        for (int rpt : {4, 2, 1}) {
+            const long wgs = (long)((nrays + 1024 * rpt - 1) / (1024 * rpt)) * C;
+            const double cost = (double)((wgs + ctx->n_cu - 1) / ctx->n_cu) * (rpt + 0.6);
+            if (rpt == 4 || cost < best) {
+                best = cost;
+                rc->rpt = rpt;
+            }
+        }
+        if ((long)((nrays + 1023) / 1024) * C < ctx->n_cu) {
+            rc->rpt = 1;
+            rc->block = ((long)((nrays + 511) / 512) * C >= ctx->n_cu) ? 512 : 256;
+        }
     }
     // plan cache entry: [threads per workgroup, rays per thread, paired forward projection]
     auto it = ctx->tune.find(shape_key("ray", g, C, comps));
@@ -530,7 +575,7 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
     const char *es = std::getenv("BOAC_FWD_SPLIT");
     const bool split_on = !(es && es[0] == '0');
     if (split_on && C <= kFewCand && comps == 1 && rc->single && g.n_samples <= 256 &&
-        (long)rc->chunks * C < ctx->n_cu)
+        (long)((nrays + 255) / 256) * C < ctx->n_cu)
         rc->split_chunks = (nrays + 31) / 32;
     // attenuation build: the scan of each ray spread over 8 lanes (single stage, up to 256 samples;
     // BOAC_ATT_SCAN=0: one thread per ray); 1024-thread workgroups when there are rays enough, and as
@@ -678,8 +723,7 @@ static void back_plan(boac_ctx *ctx, const boac_geom &g, int C, BackCfg *bc, int
     }
 }
 
-static boac_status make_plan(boac_ctx *ctx, const boac_geom &g, int C, Plan *p, int nah = -1) {
-    if (nah < 0) nah = g.n_angles;
+static boac_status make_plan(boac_ctx *ctx, const boac_geom &g, int C, Plan *p, int nah) {
     ray_plan(ctx, g, C, 1, &p->ray1, &p->bands1, nah);
     ray_plan(ctx, g, C, 2, &p->ray2, &p->bands2, nah);
     back_plan(ctx, g, C, &p->back, nah);
@@ -770,15 +814,16 @@ static uint64_t plan_switch_bits() {
 static boac_status plan_slice(boac_ctx *ctx, const boac_geom &g, int C, bool allow_pairing, DevGeom *dg, Plan *p,
                               Sizes *z) {
     BOAC_TRY(dev_geom(ctx, g, dg));
-    *z = sizes_of(g);
-    BOAC_TRY(make_plan(ctx, g, C, p));
-    if (allow_pairing && pairing_enabled() && g.n_angles % 2 == 0 && p->back.slid == 2) {
-        const int nah = g.n_angles / 2;
-        dg->nah = nah;
-        *z = sizes_of(g, nah);
-        BOAC_TRY(make_plan(ctx, g, C, p, nah));
-        if (p->back.slid != 2) return fail(BOAC_EDEVICE, "internal: paired plan changed family");
+    int nah = g.n_angles;
+    if (allow_pairing && pairing_enabled() && g.n_angles % 2 == 0) {
+        BackCfg bc;
+        back_plan(ctx, g, C, &bc, g.n_angles);
+        if (bc.slid == 2) nah = g.n_angles / 2;
     }
+    dg->nah = nah;
+    *z = sizes_of(g, nah);
+    BOAC_TRY(make_plan(ctx, g, C, p, nah));
+    if (nah != g.n_angles && p->back.slid != 2) return fail(BOAC_EDEVICE, "internal: paired plan changed family");
     return BOAC_OK;
 }
 
