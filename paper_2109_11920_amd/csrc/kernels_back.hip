@@ -15,6 +15,8 @@
 // Angle sums run in blocks of 8 angles, each block added to a compensated total. Because the
 // workgroup sees all angles of its pixels, the MLEM update F <- F * b / s is its epilogue: no partial
 // images are written.
+#include <algorithm>
+
 #include "launch.h"
 
 namespace boac {
@@ -631,7 +633,7 @@ __device__ __forceinline__ void back_epilogue(const DevGeom &g, const BackArgs &
 // on the LDS region lds. live = false: a stand-in workgroup beyond the grid (the persistent executor
 // runs workgroups four to a 1024-thread group) that takes part in every barrier and loads and writes
 // nothing.
-template <int CG, bool WEIGHTED, bool PAIRED, bool SPLIT, bool TAIL>
+template <int CG, bool WEIGHTED, bool PAIRED, bool TAIL>
 __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, bool live, DevGeom g, BackCfg T,
                                                  BackArgs A, int mode) {
     constexpr int P = kSlidBlock;
@@ -642,17 +644,11 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
     // lds: [PLANES][P rows][PL slots][V], then the ray weights wz, we
     const int ntiles = T.tiles_x * T.tiles_y;
     const int ngroups = (A.C + CG - 1) / CG;
-    const int nsplit = SPLIT ? T.asplit : 1;
-    const int total = ntiles * ngroups * nsplit;
+    const int total = ntiles * ngroups;
     int id = bid;
     if (T.xcd_remap && (total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
-    const int grp = id / (ntiles * nsplit);
-    const int rem = id - grp * (ntiles * nsplit);
-    const int tile = rem / nsplit;
-    // angle split: this workgroup gathers the held angles [a_lo, a_hi), whole 8-angle blocks
-    const int split = rem - tile * nsplit;
-    const int bps = ((g.nah + 7) / 8 + nsplit - 1) / nsplit;
-    const int a_lo = min(split * bps * 8, g.nah), a_hi = min((split + 1) * bps * 8, g.nah);
+    const int grp = id / ntiles;
+    const int tile = id - grp * ntiles;
     const int ty = tile / T.tiles_x, tx = tile - ty * T.tiles_x;
     const int l0 = tx * 16, i0 = ty * 16;
     const int c0 = grp * CG;
@@ -754,19 +750,16 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
         }
     };
 
-    int4 cur = make_int4(0, 0, 0, 0);
-    if (a_lo < a_hi) {
-        cur = const_ld(rects, a_lo);
-        wload(a_lo, cur);
-        prefetch(a_lo, cur);
-    }
+    int4 cur = const_ld(rects, 0);
+    wload(0, cur);
+    prefetch(0, cur);
     const bool field = (mode == BACK_FIELD);
 
-    for (int a = a_lo; a < a_hi; ++a) {
+    for (int a = 0; a < g.nah; ++a) {
         // the gather's per-angle constants, loaded here so the staging hides their latency
         const float4 t0 = const_ld(T.angt, 2 * a), t1 = const_ld(T.angt, 2 * a + 1);
         const float4 f0 = const_ld(rectf, 2 * a), f1 = const_ld(rectf, 2 * a + 1);
-        if (a == a_lo) wstore();  // later angles' weights are stored after the previous gather
+        if (a == 0) wstore();  // later angles' weights are stored after the previous gather
         __syncthreads();  // previous gather done with the LDS
         // this thread's bin: z and (PAIRED) the opposed ray's factor exp(-T) z'
         float zv[CG], ez[CG];
@@ -814,7 +807,7 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
             }
         }
         __syncthreads();
-        if (a + 1 < a_hi) {
+        if (a + 1 < g.nah) {
             cur = const_ld(rects, a + 1);
             wload(a + 1, cur);
             prefetch(a + 1, cur);
@@ -857,30 +850,17 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
                 if (db < 1) __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (a + 1 < a_hi) wstore();  // the weights of angle a + 1, for its staging
+        if (a + 1 < g.nah) wstore();  // the weights of angle a + 1, for its staging
         if ((a & 7) == 7 || a == g.nah - 1) {
-            if constexpr (SPLIT) {
-                // angle split: the block's sum goes to the partial buffer [block][candidate][pixel];
-                // k_back_combine adds the blocks in order, as the loop below would
-                if (pv) {
-                    const size_t pix = (size_t)i * g.n + l;
 #pragma unroll
-                    for (int q = 0; q < CG; ++q)
-                        if (q < ncg) A.blk_out[((size_t)(a >> 3) * A.C + c0 + q) * A.img_cs + pix] = blk[q];
-                }
-#pragma unroll
-                for (int q = 0; q < CG; ++q) blk[q] = 0.f;
-            } else {
-#pragma unroll
-                for (int q = 0; q < CG; ++q) {
-                    comp_add(acc[q], blk[q]);
-                    blk[q] = 0.f;
-                }
+            for (int q = 0; q < CG; ++q) {
+                comp_add(acc[q], blk[q]);
+                blk[q] = 0.f;
             }
         }
     }
 
-    if (!pv || SPLIT) return;
+    if (!pv) return;
     const size_t pix = (size_t)i * g.n + l;
     // a guard rather than a break: the loop must unroll, or acc[] would live in scratch memory
 #pragma unroll
@@ -889,67 +869,204 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
 }
 
 #ifndef BOAC_BODIES_ONLY
-template <int CG, bool WEIGHTED, bool PAIRED, bool SPLIT, bool TAIL>
+template <int CG, bool WEIGHTED, bool PAIRED, bool TAIL>
 __global__ __launch_bounds__(256) void k_back_col4(DevGeom g, BackCfg T, BackArgs A, int mode) {
     extern __shared__ float lds[];
-    k_back_col4_body<CG, WEIGHTED, PAIRED, SPLIT, TAIL>(blockIdx.x, threadIdx.x, lds, true, g, T, A, mode);
+    k_back_col4_body<CG, WEIGHTED, PAIRED, TAIL>(blockIdx.x, threadIdx.x, lds, true, g, T, A, mode);
 }
 #endif
 
-// Second pass of the angle-split gather: per (candidate, pixel) the 8-angle block sums, added in angle
-// order to a compensated total exactly as the unsplit gather adds them, then the same epilogue.
+// ---------------------------------------------------------------------------------------------------
+// The column-group gather for few candidates, where 16 x 16 tiles give too few workgroups: one workgroup
+// per 8 x 8 tile and candidate, one wave per block of 8 angles (at most kWaveBlocks of them, in turn beyond
+// that). A wave's lanes are the tile's pixels; it stages the tile's footprint of each of its angles, a block
+// of kWavePB bins x kWavePK samples with an origin as k_back_col4's, in LDS of its own: 4 samples of a bin
+// per lane and load, all 8 angles' loads in flight before the first is used, and no barrier until the
+// blocks' sums meet in LDS, where the first wave adds them in order. The window, its weights, the staged
+// values and the order of every sum are k_back_col4's, so the results are too, bit for bit.
+// Bound by latency: one memory round trip, 8 short gathers and one barrier (one candidate, 128 x 128, 128
+// angles: 8.8 us a launch; the split over workgroups it replaces, with its second pass over the block sums, 14.3).
+constexpr int kWavePL = kWavePB + 1;  // LDS pitch of a staged row
+
 #ifndef BOAC_BODIES_ONLY
-__global__ __launch_bounds__(256) void k_back_combine(DevGeom g, BackArgs A, int nblk, int mode) {
-    const size_t npix = (size_t)g.n * g.n;
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (size_t)A.C * npix) return;
-    const size_t c = t / npix, pix = t - c * npix;
-    const size_t o = c * A.img_cs + pix;
+template <bool WEIGHTED, bool PAIRED, bool TAIL>
+__global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackCfg T, BackArgs A, int mode) {
+    __shared__ float stage[kWaveBlocks][kWavePK * kWavePL];
+    extern __shared__ float sums[];  // [8-angle blocks][64 pixels]
+    const int ntiles = T.tiles_x * T.tiles_y;
+    const int total = ntiles * A.C;
+    int id = blockIdx.x;
+    if (T.xcd_remap && (total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+    const int cand = id / ntiles, tile = id - cand * ntiles;
+    const int ty = tile / T.tiles_x, tx = tile - ty * T.tiles_x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nwaves = (int)blockDim.x >> 6;
+    const int l = 8 * tx + (lane & 7), i = 8 * ty + (lane >> 3);
+    const bool pv = (l < g.n) && (i < g.n);
+    const float xc = (float)l - g.cN, yc = (float)i - g.cN;
+    const float cB5 = g.cB + 0.5f, cT5 = g.cT + 0.5f;
+    const size_t o = (size_t)cand * A.img_cs + (size_t)i * g.n + l;
+    const bool field = (mode == BACK_FIELD);
+
+    // staging: 16 bins x 5 groups of 4 samples; lane t takes bin t % 16 of groups t / 16 and (lanes < 16) 4
+    const int bb = lane & 15, kb = lane >> 4;
+    const unsigned line_bytes = 4u * ((unsigned)g.nb8 << 5);
+    const unsigned off0 = (unsigned)kb * line_bytes + 16u * (unsigned)bb;
+    const unsigned off1 = 4u * line_bytes + 16u * (unsigned)bb;
+    const unsigned cand_src = 4u * (unsigned)A.att_cs, cand_z = 4u * (unsigned)A.sino_cs, cand_e = 4u * (unsigned)A.e_cs;
+    const float *src = field ? A.z : A.att;
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(src + (size_t)cand * A.att_cs, cand_src);
+    const __amdgpu_buffer_rsrc_t rz =
+        buffer_rsrc(WEIGHTED ? A.z + (size_t)cand * A.sino_cs : src, WEIGHTED ? cand_z : 0u);
+    const __amdgpu_buffer_rsrc_t re = buffer_rsrc(PAIRED ? A.E + (size_t)cand * A.e_cs : src, PAIRED ? cand_e : 0u);
+    const int2 *orgs = reinterpret_cast<const int2 *>(T.rects) + (size_t)tile * g.nah;  // block origins (b0, k0)
+    float *st = stage[wave];
+
+    const int nblk = (g.nah + 7) / 8;
+    for (int b = wave; b < nblk; b += nwaves) {
+        float4 v0[8], v1[8];
+        float lz[8], le[8], lo[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int a = min(8 * b + j, g.nah - 1);  // past the last angle: loaded, not gathered
+            const int2 r = const_ld(orgs, a);
+            const unsigned org =
+                4u * (unsigned)a * (unsigned)g.slab + (unsigned)(r.y >> 2) * line_bytes + 16u * (unsigned)r.x;
+            v0[j] = buffer_ld4(rs, off0, org);
+            v1[j] = v0[j];
+            if (lane < 16) v1[j] = buffer_ld4(rs, off1, org);
+            lz[j] = 1.f;
+            le[j] = lo[j] = 0.f;
+            if constexpr (WEIGHTED) lz[j] = buffer_ld(rz, 4u * (unsigned)bb, 4u * (unsigned)(a * g.nb + r.x));
+            if constexpr (PAIRED) {
+                // exp(-T) of ray (a, bin); the opposed ray (a + na/2, nb-1-bin) takes its weight
+                le[j] = buffer_ld(re, 4u * (unsigned)bb, 4u * (unsigned)(a * g.nb + r.x));
+                if constexpr (WEIGHTED)
+                    lo[j] = buffer_ld(rz, 4u * (unsigned)((a + g.nah) * g.nb + (g.nb - 1 - r.x) - bb), 0u);
+            }
+        }
+        float blk = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int a = 8 * b + j;
+            if (a >= g.nah) break;  // uniform
+            const float4 t0 = const_ld(T.angt, 2 * a), t1 = const_ld(T.angt, 2 * a + 1);
+            const int2 r = const_ld(orgs, a);
+            const float fb1 = (float)(r.x + 1), fk1 = (float)(r.y + 1);
+            const float ez = WEIGHTED ? le[j] * lo[j] : le[j];
+            auto put = [&](const float4 &x4, int kg) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float x = f4at(x4, t);
+                    float v;
+                    if constexpr (PAIRED) {
+                        const float ri = __builtin_amdgcn_rcpf(x);
+                        if constexpr (WEIGHTED)
+                            v = fmaf(ri, ez, x * lz[j]);
+                        else
+                            v = field ? x + ez : fmaf(ri, ez, x);
+                    } else {
+                        v = WEIGHTED ? x * lz[j] : x;
+                    }
+                    if constexpr (TAIL) v = (r.y + 4 * kg + t < g.nt) ? v : 0.f;  // the layout's padding rows
+                    st[(4 * kg + t) * kWavePL + bb] = v;
+                }
+            };
+            put(v0[j], kb);
+            if (lane < 16) put(v1[j], 4);
+            // the wave's own LDS: its operations run in order; the fences keep the compiler's order too
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const float c = t0.x, s = t0.y;
+            const float ub = t0.z, vb = t0.w;
+            const float Sj5 = fmaf(xc, t1.x, fmaf(yc, t1.y, cB5));
+            const float Tj5 = fmaf(yc, c, fmaf(xc, -s, cT5));
+            const float bcf = __builtin_amdgcn_fmed3f(floorf(Sj5), fb1, fb1 + (float)(kWavePB - 3));
+            const float kcf = __builtin_amdgcn_fmed3f(floorf(Tj5), fk1, fk1 + (float)(kWavePK - 3));
+            const float sig = (bcf - g.cB) * g.bscale, tau = kcf - g.cT;
+            const float du0 = fmaf(sig, c, fmaf(tau, -s, -xc));
+            const float dv0 = fmaf(sig, s, fmaf(tau, c, -yc));
+            const float *base = st + (int)fmaf(kcf - fk1, (float)kWavePL, bcf - fb1);  // window tap (-1, -1)
+#pragma unroll
+            for (int db = -1; db <= 1; ++db) {
+                const float dub = (db == 0) ? du0 : (db < 0 ? du0 - ub : du0 + ub);
+                const float dvb = (db == 0) ? dv0 : (db < 0 ? dv0 - vb : dv0 + vb);
+#pragma unroll
+                for (int dk = -1; dk <= 1; ++dk) {
+                    const float du = (dk == 0) ? dub : (dk < 0 ? dub + s : dub - s);
+                    const float dv = (dk == 0) ? dvb : (dk < 0 ? dvb - c : dvb + c);
+                    blk = fmaf(hat2(du, dv), base[(dk + 1) * kWavePL + (db + 1)], blk);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+        sums[64 * b + lane] = blk;
+    }
+    __syncthreads();
+    if (wave > 0 || !pv) return;
     Comp acc{0.f, 0.f};
-    for (int b = 0; b < nblk; ++b) comp_add(acc, A.blk_out[((size_t)b * A.C + c) * A.img_cs + pix]);
+    for (int b = 0; b < nblk; ++b) comp_add(acc, sums[64 * b + lane]);
     back_epilogue(g, A, mode, o, comp_value(acc));
 }
 #endif
 
 #ifndef BOAC_BODIES_ONLY
-template <int CG, bool SPLIT, bool TAIL>
+template <int CG, bool TAIL>
 static void back_col4_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     const int ngroups = (a.C + CG - 1) / CG;
-    const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * ngroups * (SPLIT ? bc.asplit : 1)));
+    const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * ngroups));
     const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
     if (a.E) {
         if (weighted)
-            hipLaunchKernelGGL((k_back_col4<CG, true, true, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+            hipLaunchKernelGGL((k_back_col4<CG, true, true, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
         else
-            hipLaunchKernelGGL((k_back_col4<CG, false, true, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a,
+            hipLaunchKernelGGL((k_back_col4<CG, false, true, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a,
                                mode);
     } else if (weighted) {
-        hipLaunchKernelGGL((k_back_col4<CG, true, false, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_col4<CG, true, false, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     } else {
-        hipLaunchKernelGGL((k_back_col4<CG, false, false, SPLIT, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_col4<CG, false, false, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     }
-}
-
-template <int CG, bool SPLIT>
-static void back_col4_tail(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    if (g.nt & 3)
-        back_col4_go<CG, SPLIT, true>(g, bc, a, mode, st);
-    else
-        back_col4_go<CG, SPLIT, false>(g, bc, a, mode, st);
 }
 
 template <int CG>
 static hipError_t back_col4(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    if (bc.asplit < 1 || (bc.asplit > 1 && !a.blk_out)) return hipErrorInvalidValue;
     if (a.E && g.nah * 2 != g.na) return hipErrorInvalidValue;
-    if (bc.asplit > 1) {
-        back_col4_tail<CG, true>(g, bc, a, mode, st);
-        const size_t n = (size_t)a.C * g.n * g.n;
-        hipLaunchKernelGGL(k_back_combine, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, a,
-                           (g.nah + 7) / 8, mode);
+    if (g.nt & 3)
+        back_col4_go<CG, true>(g, bc, a, mode, st);
+    else
+        back_col4_go<CG, false>(g, bc, a, mode, st);
+    return hipGetLastError();
+}
+
+template <bool TAIL>
+static void back_wave_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
+    const int nblk = (g.nah + 7) / 8;
+    const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * a.C)), block((unsigned)(64 * std::min(nblk, kWaveBlocks)));
+    const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
+    if (a.E) {
+        if (weighted)
+            hipLaunchKernelGGL((k_back_wave<true, true, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
+        else
+            hipLaunchKernelGGL((k_back_wave<false, true, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
+    } else if (weighted) {
+        hipLaunchKernelGGL((k_back_wave<true, false, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
     } else {
-        back_col4_tail<CG, false>(g, bc, a, mode, st);
+        hipLaunchKernelGGL((k_back_wave<false, false, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
     }
+}
+
+static hipError_t back_wave(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
+    if (bc.tw != 8 || bc.th != 8 || bc.hb != 1 || bc.cg != 1 || (a.E && g.nah * 2 != g.na) ||
+        bc.lds < (size_t)256 * ((g.nah + 7) / 8))
+        return hipErrorInvalidValue;
+    if (g.nt & 3)
+        back_wave_go<true>(g, bc, a, mode, st);
+    else
+        back_wave_go<false>(g, bc, a, mode, st);
     return hipGetLastError();
 }
 
@@ -982,10 +1099,10 @@ static hipError_t back_tile(const DevGeom &g, const BackCfg &bc, const BackArgs 
 
 hipError_t launch_back(int mode, const DevGeom &g, const BackCfg &bc, const BackArgs &a, hipStream_t st) {
     if (TaskRecorder *r = task_recorder()) {
-        if (bc.slid != 2 || bc.asplit != 1 || !(bc.cg == 1 || bc.cg == 2 || bc.cg == 4) || bc.tw != 16 ||
+        if (bc.slid != 2 || !(bc.cg == 1 || bc.cg == 2 || bc.cg == 4) || bc.tw != 16 ||
             bc.th != 16 || bc.hb != 1 || (g.nt & 3))
             return record_unsupported(r, "backprojection outside the column-group gather (one to four candidates per "
-                                         "workgroup, no angle split, a sample count that is a multiple of 4)");
+                                         "workgroup, a sample count that is a multiple of 4)");
         if (a.E && g.nah * 2 != g.na) return hipErrorInvalidValue;
         const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
         TaskRec t{};
@@ -999,7 +1116,8 @@ hipError_t launch_back(int mode, const DevGeom &g, const BackCfg &bc, const Back
         return record_task(r, t);
     }
     // opposed-ray pairing exists in the column-group gather only
-    if ((a.E || g.nah != g.na) && bc.slid != 2) return hipErrorInvalidValue;
+    if ((a.E || g.nah != g.na) && bc.slid < 2) return hipErrorInvalidValue;
+    if (bc.slid == 3) return back_wave(g, bc, a, mode, st);
     if (bc.slid == 2) {
         if (bc.tw != 16 || bc.th != 16 || bc.hb != 1) return hipErrorInvalidValue;
         switch (bc.cg) {

@@ -266,20 +266,22 @@ __global__ __launch_bounds__(1024) void k_att_scan(DevGeom g, Band band, int pas
 
 // ------------------------------------------------------------------ forward projection
 // The epilogue of one ray: y, or the MLEM ratio, or (returned) the NLL term; zero_proj is set where
-// S > 0 meets y <= 0.
+// S > 0 meets y <= 0. S: the ray's measured count (unused in a plain projection).
 template <int MODE>
-__device__ __forceinline__ float fwd_emit(const FwdArgs &A, size_t cand, int ray, float y, bool &zero_proj) {
+__device__ __forceinline__ float fwd_meas(const FwdArgs &A, int ray) {
+    return MODE == FWD_PROJ ? 0.f : A.meas[ray];
+}
+template <int MODE>
+__device__ __forceinline__ float fwd_emit(const FwdArgs &A, size_t cand, int ray, float S, float y, bool &zero_proj) {
     const size_t si = cand * A.sino_cs + ray;
     if constexpr (MODE == FWD_PROJ) {
         A.y_out[si] = y;
         return 0.f;
     } else if constexpr (MODE == FWD_RATIO) {
-        const float S = A.meas[ray];
         A.r_out[si] = (y > 0.f) ? S / y : 0.f;
         if (A.y_out) A.y_out[si] = y;
         return 0.f;
     } else {  // FWD_NLL
-        const float S = A.meas[ray];
         if (A.y_out) A.y_out[si] = y;
         float term;
         if (S > 0.f) {
@@ -436,12 +438,12 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
         if (j >= rpt) break;
         const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
         if (ray >= nrays) continue;
-        const float t0 = fwd_emit<MODE>(A, cand, ray, g.dx * comp_value(acc[j]), zero_proj);
+        const float t0 = fwd_emit<MODE>(A, cand, ray, fwd_meas<MODE>(A, ray), g.dx * comp_value(acc[j]), zero_proj);
         if constexpr (MODE == FWD_NLL) comp_add(nll, t0);
         if constexpr (PAIRED) {
             const int a = ray / g.nb, b = ray - a * g.nb;
-            const float t1 =
-                fwd_emit<MODE>(A, cand, (a + g.nah) * g.nb + (g.nb - 1 - b), g.dx * comp_value(acc2[j]), zero_proj);
+            const int opp = (a + g.nah) * g.nb + (g.nb - 1 - b);
+            const float t1 = fwd_emit<MODE>(A, cand, opp, fwd_meas<MODE>(A, opp), g.dx * comp_value(acc2[j]), zero_proj);
             if constexpr (MODE == FWD_NLL) comp_add(nll, t1);
         }
     }
@@ -566,11 +568,13 @@ __device__ __forceinline__ void k_fwd_pair_body(int bid, float *lds, float *red,
             if (j >= rpt) break;
             const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
             if (ray >= nrays || !live) continue;
-            const float t0 = fwd_emit<MODE>(A, cand, ray, g.dx * comp_value(h ? acc1[j] : acc0[j]), zero_proj);
+            const float t0 = fwd_emit<MODE>(A, cand, ray, fwd_meas<MODE>(A, ray), g.dx * comp_value(h ? acc1[j] : acc0[j]),
+                                            zero_proj);
             if constexpr (MODE == FWD_NLL) comp_add(nll, t0);
             if constexpr (PAIRED) {
                 const int a = ray / g.nb, b = ray - a * g.nb;
-                const float t1 = fwd_emit<MODE>(A, cand, (a + g.nah) * g.nb + (g.nb - 1 - b),
+                const int opp = (a + g.nah) * g.nb + (g.nb - 1 - b);
+                const float t1 = fwd_emit<MODE>(A, cand, opp, fwd_meas<MODE>(A, opp),
                                                 g.dx * comp_value(h ? opp1[j] : opp0[j]), zero_proj);
                 if constexpr (MODE == FWD_NLL) comp_add(nll, t1);
             }
@@ -1066,19 +1070,29 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
     const int lane = threadIdx.x & (kSplitLanes - 1);
     const int ray = chunk * (blockDim.x / kSplitLanes) + threadIdx.x / kSplitLanes;
     const bool live = ray < nrays;
-    stage_whole(A.img + cand * A.img_cs, g.n, band, lds);
-    __syncthreads();
-
     constexpr int KC = 16, KG = KC / 4;
     const int a = live ? ray / g.nb : 0, b = live ? ray - a * g.nb : 0;
+    const int opp = (a + g.nah) * g.nb + (g.nb - 1 - b);
     const float2 cs = g.trig[a];
     float Ub, Vb;
     ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(A.att + cand * A.att_cs, (unsigned)(4 * A.att_cs));
     const unsigned roff = 4u * (unsigned)att_base(g, a, b);
     const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float e_ray = (PAIRED && live) ? A.E[cand * A.e_cs + ray] : 0.f;
     const int nck = (g.nt + KC - 1) / KC;
+    // the kernel is one chain of memory round trips: the first chunk of att, exp(-T) and the counts are on
+    // their way while the image is staged
+    float4 v0[KG];
+    const bool has0 = live && lane < nck;
+#pragma unroll
+    for (int q = 0; q < KG; ++q)
+        v0[q] = (has0 && lane * KC + 4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, lane * KC + 4 * q)) : z4;
+    const float e_ray = (PAIRED && live) ? A.E[cand * A.e_cs + ray] : 0.f;
+    const float S = live ? fwd_meas<MODE>(A, ray) : 0.f;
+    const float S2 = (PAIRED && live) ? fwd_meas<MODE>(A, opp) : 0.f;
+    stage_whole<16>(A.img + cand * A.img_cs, g.n, band, lds);
+    __syncthreads();
+
     float part[kSplitCpl], part2[kSplitCpl];
 #pragma unroll
     for (int h = 0; h < kSplitCpl; ++h) {
@@ -1088,7 +1102,9 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
         const int k0 = ck * KC;
         float4 v[KG];
 #pragma unroll
-        for (int q = 0; q < KG; ++q) v[q] = (k0 + 4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, k0 + 4 * q)) : z4;
+        for (int q = 0; q < KG; ++q)
+            v[q] = h == 0 ? v0[q]
+                          : (k0 + 4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, k0 + 4 * q)) : z4;
         float tau = (float)k0 - g.cT;
         float p = 0.f, p2 = 0.f;
 #pragma unroll
@@ -1120,8 +1136,8 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
     }
     if (!live || lane != 0) return;
     bool zero_proj = false;
-    fwd_emit<MODE>(A, cand, ray, g.dx * comp_value(c), zero_proj);
-    if constexpr (PAIRED) fwd_emit<MODE>(A, cand, (a + g.nah) * g.nb + (g.nb - 1 - b), g.dx * comp_value(c2), zero_proj);
+    fwd_emit<MODE>(A, cand, ray, S, g.dx * comp_value(c), zero_proj);
+    if constexpr (PAIRED) fwd_emit<MODE>(A, cand, opp, S2, g.dx * comp_value(c2), zero_proj);
 }
 #endif
 

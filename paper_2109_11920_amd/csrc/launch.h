@@ -104,13 +104,14 @@ struct BackCfg {
     int xcd_remap;        // keep a candidate group's tiles on one XCD
     int slid;             // 16 x 16 tiles, one-bin half window: fixed 32 x 32 staging block slid inside
                           // the sinogram; rects then hold (b0, k0, u0 bits, v0 bits). 1: staging by
-                          // 4-byte slots; 2: by aligned 4-sample column groups (k0 a multiple of 4)
-    int asplit;           // column-group gather: workgroups per (tile, candidate group) splitting the held
-                          // angles in whole 8-angle blocks (1 = none; > 1 needs BackArgs::blk_out)
+                          // 4-byte slots; 2: by aligned 4-sample column groups (k0 a multiple of 4). 3: few
+                          // candidates, the column-group gather on 8 x 8 tiles with a wave per 8 angles
 };
 
 constexpr int kSlidBlock = 32;  // staged bins and samples of the slid-block backprojection
 constexpr int kSlidPitch = 34;  // its LDS row pitch, in slots
+constexpr int kWavePB = 16, kWavePK = 20;  // staged bins and samples of the few-candidate gather
+constexpr int kWaveBlocks = 8;             // its waves per workgroup, at most (one per 8 held angles)
 
 struct BackArgs {
     const float *att;     // [C] attenuation tensors (4 x 8-block slabs)
@@ -121,7 +122,6 @@ struct BackArgs {
     const float *aux;     // ADJ: direct part of F_bar
     float *out;           // [C][n][n]
     float *q_out;         // MLEM: update factor b/s (nullable)
-    float *blk_out;       // angle split: [ceil(nah / 8)][C][img_cs] per-8-angle-block sums (else null)
     size_t att_cs, sino_cs, img_cs;
     size_t e_cs;          // E stride per candidate
     int C;

@@ -308,11 +308,13 @@ static boac_status host_trig(int na, std::vector<float2> &h) {
 static boac_status rect_table(boac_ctx *ctx, const boac_geom &g, BackCfg *bc, int nah) {
     std::vector<int> key{g.n, g.n_angles, g.n_bins, g.n_samples, bc->tw, bc->th, bc->hb, bc->slid, nah};
     const size_t nent = (size_t)bc->tiles_x * bc->tiles_y * nah;
-    // one allocation: the int4 rectangles, then (slid blocks) their float forms and the angle table
+    // one allocation: the int4 rectangles, then (slid blocks) their float forms and the angle table; the
+    // 8 x 8 tiles' blocks as int2 origins, two to an int4 (four times the tiles in no more memory)
+    const size_t nrect = bc->slid == 3 ? (nent + 1) / 2 : nent;
     auto point = [&](int4 *d) {
         bc->rects = d;
-        bc->rectf = bc->slid ? reinterpret_cast<const float4 *>(d + nent) : nullptr;
-        bc->angt = bc->slid ? bc->rectf + 2 * nent : nullptr;
+        bc->rectf = bc->slid ? reinterpret_cast<const float4 *>(d + nrect) : nullptr;
+        bc->angt = bc->slid == 3 ? bc->rectf : bc->slid ? bc->rectf + 2 * nent : nullptr;
     };
     auto it = ctx->rects.find(key);
     if (!ctx->arena && it != ctx->rects.end()) {
@@ -338,6 +340,7 @@ static boac_status rect_table(boac_ctx *ctx, const boac_geom &g, BackCfg *bc, in
     const int ntiles = bc->tiles_x * bc->tiles_y;
     const int wb_cap = std::min(bc->wbmax, 64);
     const int wk_cap = bc->wkmax;
+    const int PB = bc->slid == 3 ? kWavePB : kSlidBlock, PK = bc->slid == 3 ? kWavePK : kSlidBlock;  // staged block
     std::vector<int4> h((size_t)ntiles * nah);
     for (int t = 0; t < ntiles; ++t) {
         const int ty = t / bc->tiles_x, tx = t % bc->tiles_x;
@@ -363,18 +366,18 @@ static boac_status rect_table(boac_ctx *ctx, const boac_geom &g, BackCfg *bc, in
             const int wb = b_hi - b_lo + 1, wk = k_hi - k_lo + 1;
             if (bc->slid) {
                 // slide the fixed block inside the sinogram; it still holds the clipped rectangle
-                if (wb > kSlidBlock || wk > kSlidBlock)
-                    return fail(BOAC_EDEVICE, "internal: footprint %dx%d exceeds the %d-block", wb, wk, kSlidBlock);
-                const int b0 = std::min(std::max(b_lo, 0), g.n_bins - kSlidBlock);
+                if (wb > PB || wk > PK)
+                    return fail(BOAC_EDEVICE, "internal: footprint %dx%d exceeds the %dx%d block", wb, wk, PB, PK);
+                const int b0 = std::min(std::max(b_lo, 0), g.n_bins - PB);
                 // column-group variant: the first sample row a multiple of 4; the block ends inside the
                 // layout's rows (n_samples rounded up to 4), and must still reach the clipped footprint's
                 // last row
-                const int rows = bc->slid == 2 ? (g.n_samples + 3) / 4 * 4 : g.n_samples;
-                int k0 = std::min(std::max(k_lo, 0), rows - kSlidBlock);
-                if (bc->slid == 2) {
+                const int rows = bc->slid >= 2 ? (g.n_samples + 3) / 4 * 4 : g.n_samples;
+                int k0 = std::min(std::max(k_lo, 0), rows - PK);
+                if (bc->slid >= 2) {
                     k0 &= ~3;
-                    if (std::min(k_hi, g.n_samples - 1) >= k0 + kSlidBlock)
-                        return fail(BOAC_EDEVICE, "internal: aligned footprint exceeds the %d-block", kSlidBlock);
+                    if (std::min(k_hi, g.n_samples - 1) >= k0 + PK)
+                        return fail(BOAC_EDEVICE, "internal: aligned footprint exceeds the %dx%d block", PB, PK);
                 }
                 // image position of sample (b0, k0), relative to the centre of the tile's support box
                 const double sig = ((double)b0 - cB) * ((double)g.n / (double)g.n_bins), tau = (double)k0 - cT;
@@ -399,7 +402,14 @@ static boac_status rect_table(boac_ctx *ctx, const boac_geom &g, BackCfg *bc, in
         // value the FP32 operation the kernel would otherwise repeat per angle (same rounding)
         const float bscale = (float)g.n / (float)g.n_bins;
         const float inv_bscale = 1.f / bscale;
-        for (size_t e = 0; e < nent; ++e) {
+        if (bc->slid == 3) {
+            for (size_t e = 0; e < nrect; ++e) {
+                const int4 p0 = h[2 * e], p1 = h[std::min(2 * e + 1, nent - 1)];
+                h[e] = make_int4(p0.x, p0.y, p1.x, p1.y);
+            }
+            h.resize(nrect);
+        }
+        for (size_t e = 0; bc->slid != 3 && e < nent; ++e) {
             const float fb1 = (float)(h[e].x + 1), fk1 = (float)(h[e].y + 1);
             const float f[8] = {fb1, fk1, fb1 + (float)(kSlidBlock - 3), fk1 + (float)(kSlidBlock - 3),
                                 fk1 * (float)kSlidPitch + fb1, 0.f, 0.f, 0.f};
@@ -706,20 +716,20 @@ static void back_plan(boac_ctx *ctx, const boac_geom &g, int C, BackCfg *bc, int
         back_fill(g, &t);
         if (plan_ok(g, t)) *bc = t;
     }
-    // few candidates (at most kFewCand): the column-group gather splits the angles in whole 8-angle
-    // blocks over more workgroups (a second pass adds the blocks in order) while the grid would not fill
-    // the GPU twice over (BOAC_GATHER_SPLIT=0 turns it off)
-    bc->asplit = 1;
     if (ctx->persist_plans && bc->slid == 2 && bc->cg > 4) {
         bc->cg = 4;  // the persistent executor runs one to four candidates per gather workgroup
         back_fill(g, bc);
     }
+    // few candidates (at most kFewCand): the column-group gather on 8 x 8 tiles with a wave per 8 angles
+    // while the grid of 16 x 16 tiles would not fill the GPU twice over (BOAC_GATHER_SPLIT=0 turns it off)
     const char *eg = std::getenv("BOAC_GATHER_SPLIT");
-    if (bc->slid == 2 && C <= kFewCand && !ctx->persist_plans && !(eg && eg[0] == '0')) {
-        const long wgs = (long)bc->tiles_x * bc->tiles_y * ((C + bc->cg - 1) / bc->cg);
-        const int nblk = (nah + 7) / 8;
-        if (wgs < 2L * ctx->n_cu)
-            bc->asplit = (int)std::min<long>(nblk, (2L * ctx->n_cu + wgs - 1) / wgs);
+    if (bc->slid == 2 && C <= kFewCand && !ctx->persist_plans && !(eg && eg[0] == '0') &&
+        (long)bc->tiles_x * bc->tiles_y * ((C + bc->cg - 1) / bc->cg) < 2L * ctx->n_cu) {
+        bc->tw = bc->th = 8;
+        bc->cg = 1;
+        bc->slid = 3;
+        back_fill(g, bc);
+        bc->lds = (size_t)256 * ((nah + 7) / 8);  // the 8-angle blocks' sums of 64 pixels
     }
 }
 
@@ -818,12 +828,12 @@ static boac_status plan_slice(boac_ctx *ctx, const boac_geom &g, int C, bool all
     if (allow_pairing && pairing_enabled() && g.n_angles % 2 == 0) {
         BackCfg bc;
         back_plan(ctx, g, C, &bc, g.n_angles);
-        if (bc.slid == 2) nah = g.n_angles / 2;
+        if (bc.slid >= 2) nah = g.n_angles / 2;
     }
     dg->nah = nah;
     *z = sizes_of(g, nah);
     BOAC_TRY(make_plan(ctx, g, C, p, nah));
-    if (nah != g.n_angles && p->back.slid != 2) return fail(BOAC_EDEVICE, "internal: paired plan changed family");
+    if (nah != g.n_angles && p->back.slid < 2) return fail(BOAC_EDEVICE, "internal: paired plan changed family");
     return BOAC_OK;
 }
 
@@ -854,15 +864,8 @@ static boac_status run_fwd(boac_ctx *ctx, int mode, const DevGeom &dg, const Pla
 
 static boac_status run_back(boac_ctx *ctx, int mode, const DevGeom &dg, const Plan &p, const Sizes &z,
                             const BackArgs &a, hipStream_t st) {
-    BackArgs b = a;
-    double bytes = bytes_back(z, a.C, mode);
-    if (p.back.asplit > 1) {
-        // angle split: one partial image per 8-angle block, written by the gather, read by the combine pass
-        const size_t nblk = (size_t)(dg.nah + 7) / 8;
-        BOAC_TRY(ensure_t(ctx, "blk", nblk * a.C * z.I, &b.blk_out));
-        bytes += 8.0 * nblk * a.C * z.I;
-    }
-    return timed(ctx, BOAC_K_BACK, bytes, st, [&] { return launch_back(mode, dg, p.back, b, st); });
+    const double bytes = bytes_back(z, a.C, mode);
+    return timed(ctx, BOAC_K_BACK, bytes, st, [&] { return launch_back(mode, dg, p.back, a, st); });
 }
 
 static FwdArgs fwd_args(const Sizes &z, const float *att, const float *img, const float *meas,

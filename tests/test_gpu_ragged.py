@@ -49,3 +49,23 @@ def test_ragged_samples(ctx, n, na, nb, nt, C):
         report(f"J cand {c}", [J[c].item(), J2[c].item()], [Jr, Jr], TOL)
         report(f"image cand {c}", img[c].cpu().numpy(), Fr, TOL)
         report(f"gradient cand {c}", grad[c].cpu().numpy(), gr, TOL_GRAD)
+
+
+@pytest.mark.parametrize("n,na,nb,nt,C", [(32, 2, 32, 32, 1), (33, 14, 34, 33, 8), (40, 131, 40, 41, 2), (64, 258, 64, 64, 5),
+                                          (121, 18, 128, 124, 1)])
+def test_few_candidate_gather_equals_tile_gather(ctx, monkeypatch, n, na, nb, nt, C):
+    # 8 x 8 tiles with a wave per 8 angles against 16 x 16 tiles: one to 17 blocks (more than the waves of a
+    # workgroup), a last block of one angle, ragged image edges; same arithmetic, so the same bits
+    g, og = geom_pair(n, na, nb, nt)
+    rng = np.random.default_rng(na)
+    S = _dev(rng.poisson(20.0, (na, nb)))
+    th = _dev(cands(na, C))
+    z = _dev(rng.uniform(0.2, 2.0, (C, na, nb)))
+    out = {}
+    for flag in ("1", "0"):
+        monkeypatch.setenv("BOAC_GATHER_SPLIT", flag)
+        mu = ctx.rasterize_mu(g, th, 0.8)
+        out[flag] = [ctx.backproject(g, mu, z), *ctx.objective_grad_ex(g, S, th, 0.8, 3, 2)]
+        out[flag] = [x.cpu().numpy().copy() for x in out[flag]]
+    for a, b in zip(out["1"], out["0"]):
+        np.testing.assert_array_equal(a, b)
