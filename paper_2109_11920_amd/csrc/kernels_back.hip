@@ -608,7 +608,10 @@ __device__ __forceinline__ void back_epilogue(const DevGeom &g, const BackArgs &
     }
 }
 
-// Column-group variant of the slid-block gather. The host aligns the block's first sample row to a
+// Column-group variant of the slid-block gather, for bin half windows HB of 1 to 3 (detectors up to twice as
+// fine as the pixels): blocks of col4_bins(HB) bins, two per staging thread where they are more than 32 (the
+// general kernel took those, one candidate per workgroup and without opposed-ray pairing: 47 iterations of 7
+// candidates at 223 pixels, 262 bins and 168 angles 34.3 ms against 16.6 ms). The host aligns the block's first sample row to a
 // multiple of 4, so the 4 samples k..k+3 (k = first row + 4 j) of a bin
 // are one aligned 16-byte load in the attenuation layout (sample fastest inside a 4 x 8 block): thread
 // t stages bin t % 32 of rows 4 (t / 32) .. + 3 with one 16-byte load per candidate, a quarter of the
@@ -633,14 +636,16 @@ __device__ __forceinline__ void back_epilogue(const DevGeom &g, const BackArgs &
 // on the LDS region lds. live = false: a stand-in workgroup beyond the grid (the persistent executor
 // runs workgroups four to a 1024-thread group) that takes part in every barrier and loads and writes
 // nothing.
-template <int CG, bool WEIGHTED, bool PAIRED, bool TAIL>
+template <int CG, bool WEIGHTED, bool PAIRED, bool TAIL, int HB>
 __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, bool live, DevGeom g, BackCfg T,
                                                  BackArgs A, int mode) {
-    constexpr int P = kSlidBlock;
-    constexpr int PL = kSlidPitch;
+    constexpr int P = kSlidBlock;            // staged sample rows
+    constexpr int PB = col4_bins(HB);        // staged bins
+    constexpr int PL = PB + 2;               // LDS row pitch, in slots
+    constexpr int MB = (PB + 31) / 32;       // bins a staging thread takes: bb, bb + 32
     constexpr int V = SlidLayout<CG>::V;
     constexpr int PLANES = SlidLayout<CG>::PLANES;
-    constexpr int PLANE = SlidLayout<CG>::PLANE;
+    constexpr int PLANE = P * PL * V;
     // lds: [PLANES][P rows][PL slots][V], then the ray weights wz, we
     const int ntiles = T.tiles_x * T.tiles_y;
     const int ngroups = (A.C + CG - 1) / CG;
@@ -668,7 +673,7 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
     const float hv = 0.5f * (float)(i1 - i0) + 1.f + 1e-3f;
 
     // staging group: bin bb, rows 4 kb .. 4 kb + 3
-    const int bb = tid & (P - 1), kb = tid >> 5;
+    const int bb = tid & 31, kb = tid >> 5;
     const float fbb = (float)bb, fkc = (float)(4 * kb) + 1.5f;  // group centre, in samples
     const unsigned a_stride = 4u * (unsigned)g.slab;
     // byte offset of the group's first sample in the attenuation layout, less the block origin's part:
@@ -703,21 +708,23 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
 
     // PAIRED: the initial staging values are 1 (a reciprocal is taken of them; never gathered with a
     // nonzero weight, as in the unpaired case where they are 0)
-    float4 pre[CG];
+    float4 pre[MB][CG];
 #pragma unroll
-    for (int q = 0; q < CG; ++q)
-        pre[q] = PAIRED ? make_float4(1.f, 1.f, 1.f, 1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int q = 0; q < CG; ++q)
+            pre[m][q] = PAIRED ? make_float4(1.f, 1.f, 1.f, 1.f) : make_float4(0.f, 0.f, 0.f, 0.f);
 
     // Ray weights of the staged angle, [bin][candidate], shared through LDS: wz = z of the ray, we = its
-    // opposed ray's factor exp(-T) z' (PAIRED; exp(-T) alone when unweighted). Thread t < 32 CG loads
-    // those of bin t % 32 and candidate t / 32 for the next angle while the current one is gathered,
+    // opposed ray's factor exp(-T) z' (PAIRED; exp(-T) alone when unweighted). Thread t < PB CG loads
+    // those of bin t % PB and candidate t / PB for the next angle while the current one is gathered,
     // and writes them after the gather (the staging, their only reader, is then done); every thread of
     // a bin reads them back. One load per (bin, candidate) instead of one per staging thread, and no
     // registers held across the gather.
     float *wz = lds + PLANES * PLANE;
-    float *we = wz + P * CG;
-    const bool wl = (WEIGHTED || PAIRED) && tid < P * CG;
-    const int wj = tid & (P - 1), wq = min(tid >> 5, CG - 1);
+    float *we = wz + PB * CG;
+    const bool wl = (WEIGHTED || PAIRED) && tid < PB * CG;
+    const int wj = tid % PB, wq = min(tid / PB, CG - 1);
     const unsigned wcz = (unsigned)min(wq, ncg - 1) * cand_z, wce = (unsigned)min(wq, ncg - 1) * cand_e;
     float lz = 1.f, le = 0.f, lo = 1.f;
     auto wload = [&](int a, int4 r) {
@@ -728,25 +735,31 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
             le = buffer_ld(re, 4u * (unsigned)wj + wce, 4u * (unsigned)(a * g.nb + r.x));
             if constexpr (WEIGHTED)
                 // bin nb-1-(r.x+wj) of angle a + na/2: the per-lane offset stays non-negative since the
-                // block's last bin r.x + 31 is inside the sinogram
+                // block's last bin r.x + PB - 1 is inside the sinogram
                 lo = buffer_ld(rz, wcz + 4u * (unsigned)((a + g.nah) * g.nb + (g.nb - 1 - r.x) - wj), 0u);
         }
     };
     auto wstore = [&]() {
         if (!wl) return;
         if constexpr (WEIGHTED) lds[PLANES * PLANE + wj * CG + wq] = lz;
-        if constexpr (PAIRED) lds[PLANES * PLANE + P * CG + wj * CG + wq] = WEIGHTED ? le * lo : le;
+        if constexpr (PAIRED) lds[PLANES * PLANE + PB * CG + wj * CG + wq] = WEIGHTED ? le * lo : le;
     };
     auto prefetch = [&](int a, int4 r) {
         const float4 t = const_ld(T.angt, 2 * a);  // c, s, c bscale, s bscale
-        const float U = fmaf(fkc, -t.y, fmaf(fbb, t.z, __int_as_float(r.z)));
-        const float V = fmaf(fkc, t.x, fmaf(fbb, t.w, __int_as_float(r.w)));
-        // a group sample is within 1.5 samples of the group centre; one sample step moves (U, V) by (-s, c)
-        if (fabsf(U) < fmaf(1.5f, fabsf(t.y), hu) && fabsf(V) < fmaf(1.5f, fabsf(t.x), hv)) {
-            // the block origin's part of the offset is uniform: (r.y / 4) lines and 16 r.x bytes
-            const unsigned org = (unsigned)a * a_stride + (unsigned)(r.y >> 2) * line_bytes + 16u * (unsigned)r.x;
 #pragma unroll
-            for (int q = 0; q < CG; ++q) pre[q] = buffer_ld4(rs, grp_off, org + qs[q]);
+        for (int m = 0; m < MB; ++m) {
+            const float fb = m ? fbb + (float)(32 * m) : fbb;
+            const float U = fmaf(fkc, -t.y, fmaf(fb, t.z, __int_as_float(r.z)));
+            const float V = fmaf(fkc, t.x, fmaf(fb, t.w, __int_as_float(r.w)));
+            // a group sample is within 1.5 samples of the group centre; one sample step moves (U, V) by (-s, c)
+            if ((32 * m + 32 <= PB || bb < PB - 32 * m) && fabsf(U) < fmaf(1.5f, fabsf(t.y), hu) &&
+                fabsf(V) < fmaf(1.5f, fabsf(t.x), hv)) {
+                // the block origin's part of the offset is uniform: (r.y / 4) lines and 16 r.x bytes
+                const unsigned org = (unsigned)a * a_stride + (unsigned)(r.y >> 2) * line_bytes +
+                                     16u * (unsigned)r.x + 512u * (unsigned)m;
+#pragma unroll
+                for (int q = 0; q < CG; ++q) pre[m][q] = buffer_ld4(rs, grp_off, org + qs[q]);
+            }
         }
     };
 
@@ -761,49 +774,54 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
         const float4 f0 = const_ld(rectf, 2 * a), f1 = const_ld(rectf, 2 * a + 1);
         if (a == 0) wstore();  // later angles' weights are stored after the previous gather
         __syncthreads();  // previous gather done with the LDS
-        // this thread's bin: z and (PAIRED) the opposed ray's factor exp(-T) z'
-        float zv[CG], ez[CG];
-        if constexpr (WEIGHTED) load_cands<CG>(wz + bb * CG, zv);
-        if constexpr (PAIRED) load_cands<CG>(we + bb * CG, ez);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            float v[CG];
+        for (int m = 0; m < MB; ++m) {
+            const int bm = bb + 32 * m;
+            if (32 * m + 32 > PB && bm >= PB) break;
+            // this thread's bin: z and (PAIRED) the opposed ray's factor exp(-T) z'
+            float zv[CG], ez[CG];
+            if constexpr (WEIGHTED) load_cands<CG>(wz + bm * CG, zv);
+            if constexpr (PAIRED) load_cands<CG>(we + bm * CG, ez);
 #pragma unroll
-            for (int q = 0; q < CG; ++q) {
-                const float x = t == 0 ? pre[q].x : t == 1 ? pre[q].y : t == 2 ? pre[q].z : pre[q].w;
-                if constexpr (PAIRED) {
-                    // att z + (exp(-T) / att) z'. The attenuation build stores att no smaller than the
-                    // smallest normal float (exact for path lengths below ~87 optical depths) and every
-                    // staged group lies inside the sinogram, so the reciprocal needs no clamp here. The
-                    // field mode (unweighted) stages m_bar plus the ray's dx Tbar instead, picked by a
-                    // select rather than a branch per value (its reciprocal is discarded).
-                    const float ri = __builtin_amdgcn_rcpf(x);
-                    if constexpr (WEIGHTED) {
-                        v[q] = fmaf(ri, ez[q], x * zv[q]);
+            for (int t = 0; t < 4; ++t) {
+                float v[CG];
+#pragma unroll
+                for (int q = 0; q < CG; ++q) {
+                    const float x = f4at(pre[m][q], t);
+                    if constexpr (PAIRED) {
+                        // att z + (exp(-T) / att) z'. The attenuation build stores att no smaller than the
+                        // smallest normal float (exact for path lengths below ~87 optical depths) and every
+                        // staged group lies inside the sinogram, so the reciprocal needs no clamp here. The
+                        // field mode (unweighted) stages m_bar plus the ray's dx Tbar instead, picked by a
+                        // select rather than a branch per value (its reciprocal is discarded).
+                        const float ri = __builtin_amdgcn_rcpf(x);
+                        if constexpr (WEIGHTED) {
+                            v[q] = fmaf(ri, ez[q], x * zv[q]);
+                        } else {
+                            v[q] = field ? x + ez[q] : fmaf(ri, ez[q], x);
+                        }
                     } else {
-                        v[q] = field ? x + ez[q] : fmaf(ri, ez[q], x);
+                        v[q] = WEIGHTED ? x * zv[q] : x;
                     }
-                } else {
-                    v[q] = WEIGHTED ? x * zv[q] : x;
                 }
-            }
-            if constexpr (TAIL) {
-                if (cur.y + P > g.nt) {  // uniform: the block reaches past the last sample
-                    const bool real = cur.y + 4 * kb + t < g.nt;
+                if constexpr (TAIL) {
+                    if (cur.y + P > g.nt) {  // uniform: the block reaches past the last sample
+                        const bool real = cur.y + 4 * kb + t < g.nt;
 #pragma unroll
-                    for (int q = 0; q < CG; ++q) v[q] = real ? v[q] : 0.f;
+                        for (int q = 0; q < CG; ++q) v[q] = real ? v[q] : 0.f;
+                    }
                 }
-            }
-            float *d = lds + ((4 * kb + t) * PL + bb) * V;
-            if constexpr (CG == 8) {
-                reinterpret_cast<float4 *>(d)[0] = make_float4(v[0], v[1], v[2], v[3]);
-                reinterpret_cast<float4 *>(d + PLANE)[0] = make_float4(v[4], v[5], v[6], v[7]);
-            } else if constexpr (CG == 4) {
-                reinterpret_cast<float4 *>(d)[0] = make_float4(v[0], v[1], v[2], v[3]);
-            } else if constexpr (CG == 2) {
-                reinterpret_cast<float2 *>(d)[0] = make_float2(v[0], v[1]);
-            } else {
-                d[0] = v[0];
+                float *d = lds + ((4 * kb + t) * PL + bm) * V;
+                if constexpr (CG == 8) {
+                    reinterpret_cast<float4 *>(d)[0] = make_float4(v[0], v[1], v[2], v[3]);
+                    reinterpret_cast<float4 *>(d + PLANE)[0] = make_float4(v[4], v[5], v[6], v[7]);
+                } else if constexpr (CG == 4) {
+                    reinterpret_cast<float4 *>(d)[0] = make_float4(v[0], v[1], v[2], v[3]);
+                } else if constexpr (CG == 2) {
+                    reinterpret_cast<float2 *>(d)[0] = make_float2(v[0], v[1]);
+                } else {
+                    d[0] = v[0];
+                }
             }
         }
         __syncthreads();
@@ -814,7 +832,7 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
         }
 
         // ---- gather (as in the slot variant); t0 = (c, s, c bscale, s bscale), t1 = (c / bscale,
-        // s / bscale, ..), f0 = (b0 + 1, k0 + 1, b0 + P - 2, k0 + P - 2), f1.x = (k0 + 1) PL + b0 + 1
+        // s / bscale, ..), f0 = (b0 + HB, k0 + 1, b0 + PB - 1 - HB, k0 + P - 2), f1.x = (k0 + 1) PL + b0 + HB
         const float c = t0.x, s = t0.y;
         const float ub = t0.z, vb = t0.w;
         if (pv) {
@@ -825,13 +843,13 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
             const float sig = (bcf - g.cB) * g.bscale, tau = kcf - g.cT;
             const float du0 = fmaf(sig, c, fmaf(tau, -s, -xc));
             const float dv0 = fmaf(sig, s, fmaf(tau, c, -yc));
-            // window tap (-1, -1): (kcf - k0 - 1) PL + bcf - b0 - 1, exact in FP32
+            // window tap (-HB, -1): (kcf - k0 - 1) PL + bcf - b0 - HB, exact in FP32
             const int corner = (int)(fmaf(kcf, (float)PL, bcf) - f1.x);
             const float *base = lds + corner * V;
 #pragma unroll
-            for (int db = -1; db <= 1; ++db) {
-                const float dub = (db == 0) ? du0 : (db < 0 ? du0 - ub : du0 + ub);
-                const float dvb = (db == 0) ? dv0 : (db < 0 ? dv0 - vb : dv0 + vb);
+            for (int db = -HB; db <= HB; ++db) {
+                const float dub = (db == 0) ? du0 : db == -1 ? du0 - ub : db == 1 ? du0 + ub : fmaf((float)db, ub, du0);
+                const float dvb = (db == 0) ? dv0 : db == -1 ? dv0 - vb : db == 1 ? dv0 + vb : fmaf((float)db, vb, dv0);
 #pragma unroll
                 for (int dk = -1; dk <= 1; ++dk) {
                     const float du = (dk == 0) ? dub : (dk < 0 ? dub + s : dub - s);
@@ -840,14 +858,14 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
 #pragma unroll
                     for (int h = 0; h < PLANES; ++h) {
                         Vec<V> gv;
-                        gv.load(base + h * PLANE + ((dk + 1) * PL + (db + 1)) * V);
+                        gv.load(base + h * PLANE + ((dk + 1) * PL + (db + HB)) * V);
 #pragma unroll
                         for (int q = 0; q < V; ++q) blk[h * V + q] = fmaf(w, gv.v[q], blk[h * V + q]);
                     }
                 }
                 // keep the next window row's LDS reads after this row's FMAs: 12 registers of taps in
                 // flight instead of 36 (71 VGPRs, one more wave per SIMD)
-                if (db < 1) __builtin_amdgcn_sched_barrier(0);
+                if (db < HB) __builtin_amdgcn_sched_barrier(0);
             }
         }
         if (a + 1 < g.nah) wstore();  // the weights of angle a + 1, for its staging
@@ -869,10 +887,10 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
 }
 
 #ifndef BOAC_BODIES_ONLY
-template <int CG, bool WEIGHTED, bool PAIRED, bool TAIL>
+template <int CG, bool WEIGHTED, bool PAIRED, bool TAIL, int HB>
 __global__ __launch_bounds__(256) void k_back_col4(DevGeom g, BackCfg T, BackArgs A, int mode) {
     extern __shared__ float lds[];
-    k_back_col4_body<CG, WEIGHTED, PAIRED, TAIL>(blockIdx.x, threadIdx.x, lds, true, g, T, A, mode);
+    k_back_col4_body<CG, WEIGHTED, PAIRED, TAIL, HB>(blockIdx.x, threadIdx.x, lds, true, g, T, A, mode);
 }
 #endif
 
@@ -880,18 +898,19 @@ __global__ __launch_bounds__(256) void k_back_col4(DevGeom g, BackCfg T, BackArg
 // The column-group gather for few candidates, where 16 x 16 tiles give too few workgroups: one workgroup
 // per 8 x 8 tile and candidate, one wave per block of 8 angles (at most kWaveBlocks of them, in turn beyond
 // that). A wave's lanes are the tile's pixels; it stages the tile's footprint of each of its angles, a block
-// of kWavePB bins x kWavePK samples with an origin as k_back_col4's, in LDS of its own: 4 samples of a bin
+// of wave_bins(HB) bins x kWavePK samples with an origin as k_back_col4's, in LDS of its own: 4 samples of a bin
 // per lane and load, all 8 angles' loads in flight before the first is used, and no barrier until the
 // blocks' sums meet in LDS, where the first wave adds them in order. The window, its weights, the staged
 // values and the order of every sum are k_back_col4's, so the results are too, bit for bit.
 // Bound by latency: one memory round trip, 8 short gathers and one barrier (one candidate, 128 x 128, 128
 // angles: 8.8 us a launch; the split over workgroups it replaces, with its second pass over the block sums, 14.3).
-constexpr int kWavePL = kWavePB + 1;  // LDS pitch of a staged row
-
 #ifndef BOAC_BODIES_ONLY
-template <bool WEIGHTED, bool PAIRED, bool TAIL>
+template <bool WEIGHTED, bool PAIRED, bool TAIL, int HB>
 __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackCfg T, BackArgs A, int mode) {
-    __shared__ float stage[kWaveBlocks][kWavePK * kWavePL];
+    constexpr int PB = wave_bins(HB), PL = PB + 1;   // staged bins, LDS pitch of a staged row
+    constexpr int RPL = 64 / PB;                     // 4-sample groups a load covers
+    constexpr int NG = kWavePK / 4, NL = (NG + RPL - 1) / RPL;
+    __shared__ float stage[kWaveBlocks][kWavePK * PL];
     extern __shared__ float sums[];  // [8-angle blocks][64 pixels]
     const int ntiles = T.tiles_x * T.tiles_y;
     const int total = ntiles * A.C;
@@ -908,11 +927,10 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
     const size_t o = (size_t)cand * A.img_cs + (size_t)i * g.n + l;
     const bool field = (mode == BACK_FIELD);
 
-    // staging: 16 bins x 5 groups of 4 samples; lane t takes bin t % 16 of groups t / 16 and (lanes < 16) 4
-    const int bb = lane & 15, kb = lane >> 4;
+    // staging: PB bins x 5 groups of 4 samples; lane t takes bin t % PB of groups t / PB + RPL m
+    const int bb = lane & (PB - 1), kb = lane / PB;
     const unsigned line_bytes = 4u * ((unsigned)g.nb8 << 5);
     const unsigned off0 = (unsigned)kb * line_bytes + 16u * (unsigned)bb;
-    const unsigned off1 = 4u * line_bytes + 16u * (unsigned)bb;
     const unsigned cand_src = 4u * (unsigned)A.att_cs, cand_z = 4u * (unsigned)A.sino_cs, cand_e = 4u * (unsigned)A.e_cs;
     const float *src = field ? A.z : A.att;
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(src + (size_t)cand * A.att_cs, cand_src);
@@ -924,7 +942,7 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
 
     const int nblk = (g.nah + 7) / 8;
     for (int b = wave; b < nblk; b += nwaves) {
-        float4 v0[8], v1[8];
+        float4 v[8][NL];
         float lz[8], le[8], lo[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -932,9 +950,11 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
             const int2 r = const_ld(orgs, a);
             const unsigned org =
                 4u * (unsigned)a * (unsigned)g.slab + (unsigned)(r.y >> 2) * line_bytes + 16u * (unsigned)r.x;
-            v0[j] = buffer_ld4(rs, off0, org);
-            v1[j] = v0[j];
-            if (lane < 16) v1[j] = buffer_ld4(rs, off1, org);
+#pragma unroll
+            for (int m = 0; m < NL; ++m) {
+                v[j][m] = make_float4(1.f, 1.f, 1.f, 1.f);
+                if (kb + RPL * m < NG) v[j][m] = buffer_ld4(rs, off0, org + (unsigned)(RPL * m) * line_bytes);
+            }
             lz[j] = 1.f;
             le[j] = lo[j] = 0.f;
             if constexpr (WEIGHTED) lz[j] = buffer_ld(rz, 4u * (unsigned)bb, 4u * (unsigned)(a * g.nb + r.x));
@@ -952,28 +972,29 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
             if (a >= g.nah) break;  // uniform
             const float4 t0 = const_ld(T.angt, 2 * a), t1 = const_ld(T.angt, 2 * a + 1);
             const int2 r = const_ld(orgs, a);
-            const float fb1 = (float)(r.x + 1), fk1 = (float)(r.y + 1);
+            const float fb1 = (float)(r.x + HB), fk1 = (float)(r.y + 1);
             const float ez = WEIGHTED ? le[j] * lo[j] : le[j];
             auto put = [&](const float4 &x4, int kg) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const float x = f4at(x4, t);
-                    float v;
+                    float y;
                     if constexpr (PAIRED) {
                         const float ri = __builtin_amdgcn_rcpf(x);
                         if constexpr (WEIGHTED)
-                            v = fmaf(ri, ez, x * lz[j]);
+                            y = fmaf(ri, ez, x * lz[j]);
                         else
-                            v = field ? x + ez : fmaf(ri, ez, x);
+                            y = field ? x + ez : fmaf(ri, ez, x);
                     } else {
-                        v = WEIGHTED ? x * lz[j] : x;
+                        y = WEIGHTED ? x * lz[j] : x;
                     }
-                    if constexpr (TAIL) v = (r.y + 4 * kg + t < g.nt) ? v : 0.f;  // the layout's padding rows
-                    st[(4 * kg + t) * kWavePL + bb] = v;
+                    if constexpr (TAIL) y = (r.y + 4 * kg + t < g.nt) ? y : 0.f;  // the layout's padding rows
+                    st[(4 * kg + t) * PL + bb] = y;
                 }
             };
-            put(v0[j], kb);
-            if (lane < 16) put(v1[j], 4);
+#pragma unroll
+            for (int m = 0; m < NL; ++m)
+                if (kb + RPL * m < NG) put(v[j][m], kb + RPL * m);
             // the wave's own LDS: its operations run in order; the fences keep the compiler's order too
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -982,21 +1003,21 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
             const float ub = t0.z, vb = t0.w;
             const float Sj5 = fmaf(xc, t1.x, fmaf(yc, t1.y, cB5));
             const float Tj5 = fmaf(yc, c, fmaf(xc, -s, cT5));
-            const float bcf = __builtin_amdgcn_fmed3f(floorf(Sj5), fb1, fb1 + (float)(kWavePB - 3));
+            const float bcf = __builtin_amdgcn_fmed3f(floorf(Sj5), fb1, fb1 + (float)(PB - 1 - 2 * HB));
             const float kcf = __builtin_amdgcn_fmed3f(floorf(Tj5), fk1, fk1 + (float)(kWavePK - 3));
             const float sig = (bcf - g.cB) * g.bscale, tau = kcf - g.cT;
             const float du0 = fmaf(sig, c, fmaf(tau, -s, -xc));
             const float dv0 = fmaf(sig, s, fmaf(tau, c, -yc));
-            const float *base = st + (int)fmaf(kcf - fk1, (float)kWavePL, bcf - fb1);  // window tap (-1, -1)
+            const float *base = st + (int)fmaf(kcf - fk1, (float)PL, bcf - fb1);  // window tap (-HB, -1)
 #pragma unroll
-            for (int db = -1; db <= 1; ++db) {
-                const float dub = (db == 0) ? du0 : (db < 0 ? du0 - ub : du0 + ub);
-                const float dvb = (db == 0) ? dv0 : (db < 0 ? dv0 - vb : dv0 + vb);
+            for (int db = -HB; db <= HB; ++db) {
+                const float dub = (db == 0) ? du0 : db == -1 ? du0 - ub : db == 1 ? du0 + ub : fmaf((float)db, ub, du0);
+                const float dvb = (db == 0) ? dv0 : db == -1 ? dv0 - vb : db == 1 ? dv0 + vb : fmaf((float)db, vb, dv0);
 #pragma unroll
                 for (int dk = -1; dk <= 1; ++dk) {
                     const float du = (dk == 0) ? dub : (dk < 0 ? dub + s : dub - s);
                     const float dv = (dk == 0) ? dvb : (dk < 0 ? dvb - c : dvb + c);
-                    blk = fmaf(hat2(du, dv), base[(dk + 1) * kWavePL + (db + 1)], blk);
+                    blk = fmaf(hat2(du, dv), base[(dk + 1) * PL + (db + HB)], blk);
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1014,59 +1035,79 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
 #endif
 
 #ifndef BOAC_BODIES_ONLY
-template <int CG, bool TAIL>
+template <int CG, bool TAIL, int HB>
 static void back_col4_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     const int ngroups = (a.C + CG - 1) / CG;
     const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * ngroups));
     const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
     if (a.E) {
         if (weighted)
-            hipLaunchKernelGGL((k_back_col4<CG, true, true, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+            hipLaunchKernelGGL((k_back_col4<CG, true, true, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
         else
-            hipLaunchKernelGGL((k_back_col4<CG, false, true, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a,
-                               mode);
+            hipLaunchKernelGGL((k_back_col4<CG, false, true, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     } else if (weighted) {
-        hipLaunchKernelGGL((k_back_col4<CG, true, false, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_col4<CG, true, false, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     } else {
-        hipLaunchKernelGGL((k_back_col4<CG, false, false, TAIL>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_col4<CG, false, false, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     }
+}
+
+template <int CG, int HB>
+static void back_col4_tail(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
+    // wider windows take the variant with the padding rows' test at every sample count
+    if (HB > 1 || (g.nt & 3))
+        back_col4_go<CG, true, HB>(g, bc, a, mode, st);
+    else
+        back_col4_go<CG, HB != 1, HB>(g, bc, a, mode, st);
 }
 
 template <int CG>
 static hipError_t back_col4(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    if (a.E && g.nah * 2 != g.na) return hipErrorInvalidValue;
-    if (g.nt & 3)
-        back_col4_go<CG, true>(g, bc, a, mode, st);
+    if ((a.E && g.nah * 2 != g.na) || bc.tw != 16 || bc.th != 16) return hipErrorInvalidValue;
+    if (bc.hb == 1)
+        back_col4_tail<CG, 1>(g, bc, a, mode, st);
+    else if constexpr (CG > 4)
+        return hipErrorInvalidValue;
+    else if (bc.hb == 2)
+        back_col4_tail<CG, 2>(g, bc, a, mode, st);
+    else if (bc.hb == 3)
+        back_col4_tail<CG, 3>(g, bc, a, mode, st);
     else
-        back_col4_go<CG, false>(g, bc, a, mode, st);
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-template <bool TAIL>
+template <bool TAIL, int HB>
 static void back_wave_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     const int nblk = (g.nah + 7) / 8;
     const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * a.C)), block((unsigned)(64 * std::min(nblk, kWaveBlocks)));
     const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
     if (a.E) {
         if (weighted)
-            hipLaunchKernelGGL((k_back_wave<true, true, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
+            hipLaunchKernelGGL((k_back_wave<true, true, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
         else
-            hipLaunchKernelGGL((k_back_wave<false, true, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
+            hipLaunchKernelGGL((k_back_wave<false, true, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
     } else if (weighted) {
-        hipLaunchKernelGGL((k_back_wave<true, false, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_wave<true, false, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
     } else {
-        hipLaunchKernelGGL((k_back_wave<false, false, TAIL>), grid, block, bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_wave<false, false, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
     }
 }
 
 static hipError_t back_wave(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    if (bc.tw != 8 || bc.th != 8 || bc.hb != 1 || bc.cg != 1 || (a.E && g.nah * 2 != g.na) ||
+    if (bc.tw != 8 || bc.th != 8 || bc.cg != 1 || (a.E && g.nah * 2 != g.na) ||
         bc.lds < (size_t)256 * ((g.nah + 7) / 8))
         return hipErrorInvalidValue;
-    if (g.nt & 3)
-        back_wave_go<true>(g, bc, a, mode, st);
+    if (bc.hb == 1 && !(g.nt & 3))
+        back_wave_go<false, 1>(g, bc, a, mode, st);
+    else if (bc.hb == 1)
+        back_wave_go<true, 1>(g, bc, a, mode, st);
+    else if (bc.hb == 2)
+        back_wave_go<true, 2>(g, bc, a, mode, st);
+    else if (bc.hb == 3)
+        back_wave_go<true, 3>(g, bc, a, mode, st);
     else
-        back_wave_go<false>(g, bc, a, mode, st);
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -1119,7 +1160,6 @@ hipError_t launch_back(int mode, const DevGeom &g, const BackCfg &bc, const Back
     if ((a.E || g.nah != g.na) && bc.slid < 2) return hipErrorInvalidValue;
     if (bc.slid == 3) return back_wave(g, bc, a, mode, st);
     if (bc.slid == 2) {
-        if (bc.tw != 16 || bc.th != 16 || bc.hb != 1) return hipErrorInvalidValue;
         switch (bc.cg) {
             case 1: return back_col4<1>(g, bc, a, mode, st);
             case 2: return back_col4<2>(g, bc, a, mode, st);

@@ -64,7 +64,7 @@ template <int CG, bool W, bool P>
 __device__ __forceinline__ void run_col4(const TaskRec &T, int item, float *lds) {
     const int vb = quarter_block(item, T.grid);
     float *l = lds + (threadIdx.x >> 8) * (T.sub_lds / 4);
-    k_back_col4_body<CG, W, P, false>(vb >= 0 ? vb : T.grid - 1, threadIdx.x & 255, l, vb >= 0, T.u.back.g,
+    k_back_col4_body<CG, W, P, false, 1>(vb >= 0 ? vb : T.grid - 1, threadIdx.x & 255, l, vb >= 0, T.u.back.g,
                                       T.u.back.T, T.u.back.A, T.u.back.mode);
 }
 

@@ -97,21 +97,28 @@ struct BackCfg {
     int tiles_x, tiles_y; // tiles per image
     size_t lds;
     const int4 *rects;    // [tiles][n_angles] footprint rectangles (b_lo, k_lo, wb, wk)
-    const float4 *rectf;  // slid blocks: [tiles][n_angles][2] block origin as floats, (b0 + 1, k0 + 1,
-                          // b0 + P - 2, k0 + P - 2) and ((k0 + 1) kSlidPitch + b0 + 1, 0, 0, 0)
+    const float4 *rectf;  // slid blocks: [tiles][n_angles][2] block origin as floats, (b0 + hb, k0 + 1,
+                          // b0 + bins - 1 - hb, k0 + P - 2) and ((k0 + 1) pitch + b0 + hb, 0, 0, 0)
     const float4 *angt;   // slid blocks: [n_angles][2] (c, s, c bscale, s bscale), (c / bscale, s / bscale,
                           // 0, 0), each the FP32 product the kernels would form
     int xcd_remap;        // keep a candidate group's tiles on one XCD
-    int slid;             // 16 x 16 tiles, one-bin half window: fixed 32 x 32 staging block slid inside
-                          // the sinogram; rects then hold (b0, k0, u0 bits, v0 bits). 1: staging by
-                          // 4-byte slots; 2: by aligned 4-sample column groups (k0 a multiple of 4). 3: few
-                          // candidates, the column-group gather on 8 x 8 tiles with a wave per 8 angles
+    int slid;             // 16 x 16 tiles: fixed staging block (32 x 32; more bins for half windows above 1)
+                          // slid inside the sinogram; rects then hold (b0, k0, u0 bits, v0 bits). 1: staging
+                          // by 4-byte slots (half window 1); 2: by aligned 4-sample column groups (k0 a
+                          // multiple of 4). 3: few candidates, the column-group gather on 8 x 8 tiles with a
+                          // wave per 8 angles
 };
 
 constexpr int kSlidBlock = 32;  // staged bins and samples of the slid-block backprojection
 constexpr int kSlidPitch = 34;  // its LDS row pitch, in slots
-constexpr int kWavePB = 16, kWavePK = 20;  // staged bins and samples of the few-candidate gather
-constexpr int kWaveBlocks = 8;             // its waves per workgroup, at most (one per 8 held angles)
+// Staged bins of the column-group gather by its bin half window: a 16 x 16 tile's footprint is at most
+// ceil(15 sqrt(2) n_bins / n) + 2 hb + 4 bins wide, n_bins / n at most 1.06, 1.76 and 2.
+constexpr int col4_bins(int hb) { return hb == 1 ? kSlidBlock : hb == 2 ? 48 : 64; }
+// Few candidates (8 x 8 tiles): staged samples, staged bins (ceil(7 sqrt(2) n_bins / n) + 2 hb + 3 at most), and
+// waves per workgroup at most (one per 8 held angles).
+constexpr int kWavePK = 20;
+constexpr int wave_bins(int hb) { return hb == 1 ? 16 : 32; }
+constexpr int kWaveBlocks = 8;
 
 struct BackArgs {
     const float *att;     // [C] attenuation tensors (4 x 8-block slabs)

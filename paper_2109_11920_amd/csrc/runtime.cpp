@@ -340,7 +340,8 @@ static boac_status rect_table(boac_ctx *ctx, const boac_geom &g, BackCfg *bc, in
     const int ntiles = bc->tiles_x * bc->tiles_y;
     const int wb_cap = std::min(bc->wbmax, 64);
     const int wk_cap = bc->wkmax;
-    const int PB = bc->slid == 3 ? kWavePB : kSlidBlock, PK = bc->slid == 3 ? kWavePK : kSlidBlock;  // staged block
+    // staged block
+    const int PB = bc->slid == 3 ? wave_bins(bc->hb) : col4_bins(bc->hb), PK = bc->slid == 3 ? kWavePK : kSlidBlock;
     std::vector<int4> h((size_t)ntiles * nah);
     for (int t = 0; t < ntiles; ++t) {
         const int ty = t / bc->tiles_x, tx = t % bc->tiles_x;
@@ -410,9 +411,9 @@ static boac_status rect_table(boac_ctx *ctx, const boac_geom &g, BackCfg *bc, in
             h.resize(nrect);
         }
         for (size_t e = 0; bc->slid != 3 && e < nent; ++e) {
-            const float fb1 = (float)(h[e].x + 1), fk1 = (float)(h[e].y + 1);
-            const float f[8] = {fb1, fk1, fb1 + (float)(kSlidBlock - 3), fk1 + (float)(kSlidBlock - 3),
-                                fk1 * (float)kSlidPitch + fb1, 0.f, 0.f, 0.f};
+            const float fb1 = (float)(h[e].x + bc->hb), fk1 = (float)(h[e].y + 1);
+            const float f[8] = {fb1, fk1, fb1 + (float)(PB - 1 - 2 * bc->hb), fk1 + (float)(PK - 3),
+                                fk1 * (float)(PB + 2) + fb1, 0.f, 0.f, 0.f};
             int4 w[2];
             std::memcpy(w, f, sizeof(f));
             h.push_back(w[0]);
@@ -630,7 +631,8 @@ static void back_fill(const boac_geom &g, BackCfg *bc) {
     bc->tiles_x = (g.n + bc->tw - 1) / bc->tw;
     bc->tiles_y = (g.n + bc->th - 1) / bc->th;
     // slid blocks: the staged block, then two [bin][candidate] ray-weight tables
-    bc->lds = bc->slid ? (size_t)bc->cg * (kSlidBlock * kSlidPitch + 2 * kSlidBlock) * sizeof(float)
+    const int bins = col4_bins(bc->hb);
+    bc->lds = bc->slid ? (size_t)bc->cg * (kSlidBlock * (bins + 2) + 2 * bins) * sizeof(float)
                        : (size_t)bc->cg * (bc->wbmax * bc->wkmax + bc->wbmax) * sizeof(float);
 }
 
@@ -654,14 +656,16 @@ static bool back_cfg_ok(const BackCfg &b) {
     return b.hb == 1;
 }
 
-// The slid-block kernel: 16 x 16 tiles, one-bin half window, a footprint within the 32 x 32 block, a
-// sinogram at least one block wide and tall, and 32-bit buffer offsets that cannot wrap (the kernel's
-// largest offset is below 2 cg bytes-per-candidate).
+// The slid-block kernels: 16 x 16 tiles, a footprint within the staged block (slot staging: a one-bin half
+// window), a sinogram at least one block wide and tall, and 32-bit buffer offsets that cannot wrap (the
+// kernel's largest offset is below 2 cg bytes-per-candidate).
 static bool slid_ok(const boac_geom &g, const BackCfg &b) {
-    if (!(b.slid == 1 || b.slid == 2) || b.tw != 16 || b.th != 16 || b.hb != 1) return false;
+    if (!(b.slid == 1 || b.slid == 2) || b.tw != 16 || b.th != 16 || b.hb > 3) return false;
+    if (b.hb > 1 && (b.slid == 1 || b.cg > 4)) return false;
+    const int bins = col4_bins(b.hb);
     if (!(b.cg == 1 || b.cg == 2 || b.cg == 4 || b.cg == 8) || b.lds > kLdsBudget) return false;
-    if (b.wbmax > kSlidBlock || b.wkmax > kSlidBlock) return false;
-    if (g.n_bins < kSlidBlock || g.n_samples < kSlidBlock) return false;
+    if (b.wbmax > bins || b.wkmax > kSlidBlock) return false;
+    if (g.n_bins < bins || g.n_samples < kSlidBlock) return false;
     const double att_bytes = 4.0 * g.n_angles * (double)att_slab(g);
     return 2.0 * b.cg * att_bytes < 4294967296.0;
 }
@@ -694,7 +698,7 @@ static void back_plan(boac_ctx *ctx, const boac_geom &g, int C, BackCfg *bc, int
         slid_seen = t.slid;
         if (C >= t.cg && (long)t.tiles_x * t.tiles_y * ((C + t.cg - 1) / t.cg) >= target) break;
     }
-    if (!set || bin_half_window(g) > 1) {
+    if (!set) {
         BackCfg t{};
         t.tw = 16;
         t.th = 16;

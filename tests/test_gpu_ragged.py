@@ -1,5 +1,6 @@
-"""Sample counts that are no multiple of 4 in the column-group gather: the blocks at the rays' end stage the
-layout's padding rows as zeros. Each remainder, with and without opposed-ray pairing (even and odd angle
+"""The column-group gather off its first sizes. Sample counts that are no multiple of 4: the blocks at the
+rays' end stage the layout's padding rows as zeros. Detectors finer than the pixels: bin windows of two and
+three. Each remainder, with and without opposed-ray pairing (even and odd angle
 counts), every candidates-per-workgroup variant the counts select, and the angle split of few candidates,
 against the FP64 oracle (relative L2 and largest error within the repository's gates)."""
 import numpy as np
@@ -25,7 +26,11 @@ def _dev(a):
 
 
 @pytest.mark.parametrize("n,na,nb,nt,C", [(32, 6, 32, 33, 1), (33, 7, 33, 33, 12), (34, 8, 32, 34, 10), (35, 5, 36, 35, 3),
-                                          (47, 16, 47, 47, 33), (64, 10, 64, 66, 40), (109, 6, 109, 109, 17)])
+                                          (47, 16, 47, 47, 33), (64, 10, 64, 66, 40), (109, 6, 109, 109, 17),
+                                          # wider bin windows: the smallest and largest detector of each, one
+                                          # to 4 candidates per workgroup, paired and not
+                                          (46, 8, 49, 46, 17), (45, 9, 48, 44, 40), (49, 6, 86, 50, 33), (33, 7, 58, 33, 2),
+                                          (48, 8, 85, 48, 40), (40, 10, 80, 40, 33), (36, 5, 72, 35, 3), (16, 6, 32, 32, 5)])
 def test_ragged_samples(ctx, n, na, nb, nt, C):
     from oracle.adjoint import objective_and_grad
     g, og = geom_pair(n, na, nb, nt)
@@ -52,7 +57,8 @@ def test_ragged_samples(ctx, n, na, nb, nt, C):
 
 
 @pytest.mark.parametrize("n,na,nb,nt,C", [(32, 2, 32, 32, 1), (33, 14, 34, 33, 8), (40, 131, 40, 41, 2), (64, 258, 64, 64, 5),
-                                          (121, 18, 128, 124, 1)])
+                                          (121, 18, 128, 124, 1), (40, 70, 48, 40, 3), (33, 9, 58, 37, 8),
+                                          (36, 20, 64, 36, 1), (50, 131, 100, 49, 2)])
 def test_few_candidate_gather_equals_tile_gather(ctx, monkeypatch, n, na, nb, nt, C):
     # 8 x 8 tiles with a wave per 8 angles against 16 x 16 tiles: one to 17 blocks (more than the waves of a
     # workgroup), a last block of one angle, ragged image edges; same arithmetic, so the same bits
