@@ -40,10 +40,12 @@ __device__ __forceinline__ float coverage_slope(float d, float inv_h) {
     return 6.f * x * (1.f - x) * inv_h;
 }
 
-// mu of pixel pix of candidate cidx.
+// mu of pixel pix of candidate cidx; ones (or null): the MLEM start, 1 on every pixel.
 __device__ __forceinline__ void raster_at(const DevGeom &g, const float *__restrict__ cand, float delta_r,
-                                          float *__restrict__ mu, size_t img_cs, uint32_t *status, int cidx, int pix) {
+                                          float *__restrict__ mu, size_t img_cs, uint32_t *status,
+                                          float *__restrict__ ones, int cidx, int pix) {
     if (pix >= g.n * g.n) return;
+    if (ones) ones[(size_t)cidx * img_cs + pix] = 1.f;
     const int i = pix / g.n, l = pix - i * g.n;
     const float *th = cand + (size_t)cidx * 8;
     const float inv_h = 4.f / g.dx;
@@ -76,8 +78,9 @@ __device__ __forceinline__ void raster_at(const DevGeom &g, const float *__restr
 
 #ifndef BOAC_BODIES_ONLY
 __global__ __launch_bounds__(256) void k_raster(DevGeom g, const float *__restrict__ cand, int C, float delta_r,
-                                                float *__restrict__ mu, size_t img_cs, uint32_t *status) {
-    raster_at(g, cand, delta_r, mu, img_cs, status, blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x);
+                                                float *__restrict__ mu, size_t img_cs, uint32_t *status,
+                                                float *__restrict__ ones) {
+    raster_at(g, cand, delta_r, mu, img_cs, status, ones, blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x);
 }
 #endif
 
@@ -147,9 +150,15 @@ __global__ void k_fill(float *p, size_t count, float v) {
 }
 #endif
 #ifndef BOAC_BODIES_ONLY
-__global__ void k_fill_u32(uint32_t *p, size_t count, uint32_t v) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = v;
+// two ranges in one launch
+__global__ void k_fill_u32(uint32_t *p, size_t count, uint32_t *p2, size_t count2, uint32_t v) {
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count + count2;
+         i += (size_t)gridDim.x * blockDim.x) {
+        if (i < count)
+            p[i] = v;
+        else
+            p2[i - count] = v;
+    }
 }
 #endif
 #ifndef BOAC_BODIES_ONLY
@@ -226,37 +235,19 @@ __device__ __forceinline__ void k_lgamma_sum_body(float *red, const float *meas,
 }
 
 #ifndef BOAC_BODIES_ONLY
-__global__ __launch_bounds__(512) void k_lgamma_sum(const float *meas, int count, float2 *out, uint32_t *flag) {
-    __shared__ __align__(8) float red[32];
-    k_lgamma_sum_body(red, meas, count, out, flag);
-}
-
 // The constant over gridDim.x workgroups: workgroup b sums the bins b * blockDim.x + tid + k * gridDim.x *
-// blockDim.x into part[b]; k_lgamma_final adds the parts in order.
+// blockDim.x into part[b]; k_nll_finish adds the parts.
 __global__ __launch_bounds__(512) void k_lgamma_part(const float *meas, int count, double *part, uint32_t *flag) {
     __shared__ double red[16];
     const double t = lgamma_block_sum(red, meas, count, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x,
                                       flag);
     if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
-
-__global__ void k_lgamma_final(const double *part, int nparts, float2 *out) {
-    if (threadIdx.x != 0) return;
-    double t = 0.0;
-    for (int p = 0; p < nparts; ++p) t += part[p];
-    put_double(out, t);
-}
 #endif
 
-// J[c] = sum of the per-workgroup NLL partials + the ln Gamma constant; status bits.
-__device__ __forceinline__ void nll_finish_at(const float2 *partial, int chunks, int C, const float2 *lg,
-                                              const uint32_t *meas_flag, float *obj, uint32_t *status, int c) {
-    if (c >= C) return;
-    Comp acc{lg->x, lg->y};
-    for (int j = 0; j < chunks; ++j) {
-        const float2 p = partial[(size_t)c * chunks + j];
-        comp_merge(acc, Comp{p.x, p.y});
-    }
+// J[c] from the sum acc of the per-workgroup NLL partials and the ln Gamma constant; status bits.
+__device__ __forceinline__ void nll_store(const Comp &acc, const uint32_t *meas_flag, float *obj, uint32_t *status,
+                                          int c) {
     const float J = comp_value(acc);
     obj[c] = J;
     if (status) {
@@ -265,11 +256,40 @@ __device__ __forceinline__ void nll_finish_at(const float2 *partial, int chunks,
         status[c] = st;
     }
 }
+__device__ __forceinline__ void nll_finish_at(const float2 *partial, int chunks, int C, const float2 *lg,
+                                              const uint32_t *meas_flag, float *obj, uint32_t *status, int c) {
+    if (c >= C) return;
+    Comp acc{lg->x, lg->y};
+    for (int j = 0; j < chunks; ++j) {
+        const float2 p = partial[(size_t)c * chunks + j];
+        comp_merge(acc, Comp{p.x, p.y});
+    }
+    nll_store(acc, meas_flag, obj, status, c);
+}
 
 #ifndef BOAC_BODIES_ONLY
-__global__ void k_nll_finish(const float2 *partial, int chunks, int C, const float2 *lg, const uint32_t *meas_flag,
-                             float *obj, uint32_t *status) {
-    nll_finish_at(partial, chunks, C, lg, meas_flag, obj, status, blockIdx.x * blockDim.x + threadIdx.x);
+// One wave per candidate: its lanes merge the partials j, j + 64, ... in turn, then each other in a fixed tree;
+// the constant's parts (doubles, at most 64) are added the same way. One thread per candidate took a memory
+// round trip per partial, and the constant a launch of its own.
+__global__ __launch_bounds__(256) void k_nll_finish(const float2 *partial, int chunks, int C, const double *part,
+                                                    int nparts, const uint32_t *meas_flag, float *obj,
+                                                    uint32_t *status) {
+    const int lane = threadIdx.x & (kWave - 1), c = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    if (c >= C) return;  // uniform per wave
+    double t = lane < nparts ? part[lane] : 0.0;
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, kWave);
+    Comp acc{0.f, 0.f};
+    for (int j = lane; j < chunks; j += kWave) {
+        const float2 p = partial[(size_t)c * chunks + j];
+        comp_merge(acc, Comp{p.x, p.y});
+    }
+    acc = wave_reduce(acc);
+    float2 lg;
+    put_double(&lg, t);
+    Comp all{lg.x, lg.y};
+    comp_merge(all, acc);
+    if (lane == 0) nll_store(all, meas_flag, obj, status, c);
 }
 #endif
 
@@ -337,11 +357,11 @@ static unsigned fill_blocks(size_t count) {
 }
 
 hipError_t launch_raster(const DevGeom &g, const float *cand, int C, float delta_r, float *mu, size_t img_cs,
-                         uint32_t *status, hipStream_t st) {
+                         uint32_t *status, float *ones, hipStream_t st) {
     if (TaskRecorder *r = task_recorder()) {
         TaskRec t{};
         t.kind = T_RASTER;
-        t.u.raster = {g, cand, delta_r, mu, img_cs, status, (g.n * g.n + 255) / 256};
+        t.u.raster = {g, cand, delta_r, mu, img_cs, status, ones, (g.n * g.n + 255) / 256};
         t.grid = t.u.raster.nbx * C;
         t.items = (t.grid + 3) / 4;
         return record_task(r, t);
@@ -350,7 +370,8 @@ hipError_t launch_raster(const DevGeom &g, const float *cand, int C, float delta
         const int n = C - c0 < 65535 ? C - c0 : 65535;
         const dim3 grid((unsigned)((g.n * g.n + 255) / 256), (unsigned)n);
         hipLaunchKernelGGL(k_raster, grid, dim3(256), 0, st, g, cand + (size_t)c0 * 8, n, delta_r,
-                           mu + (size_t)c0 * img_cs, img_cs, status ? status + c0 : nullptr);
+                           mu + (size_t)c0 * img_cs, img_cs, status ? status + c0 : nullptr,
+                           ones ? ones + (size_t)c0 * img_cs : nullptr);
     }
     return hipGetLastError();
 }
@@ -379,17 +400,21 @@ hipError_t launch_fill(float *p, size_t count, float v, hipStream_t st) {
     hipLaunchKernelGGL(k_fill, dim3(fill_blocks(count)), dim3(256), 0, st, p, count, v);
     return hipGetLastError();
 }
-hipError_t launch_fill_u32(uint32_t *p, size_t count, uint32_t v, hipStream_t st) {
+hipError_t launch_fill_u32(uint32_t *p, size_t count, uint32_t *p2, size_t count2, uint32_t v, hipStream_t st) {
     if (TaskRecorder *r = task_recorder()) {
-        TaskRec t{};
-        t.kind = T_FILL_U32;
-        t.u.elem.out = p;
-        t.u.elem.u = v;
-        t.u.elem.count = count;
-        t.grid = t.items = (int)((t.u.elem.count + kPersistElems - 1) / kPersistElems);
-        return record_task(r, t);
+        for (int k = 0; k < 2; ++k) {
+            TaskRec t{};
+            t.kind = T_FILL_U32;
+            t.u.elem.out = k ? p2 : p;
+            t.u.elem.u = v;
+            t.u.elem.count = k ? count2 : count;
+            t.grid = t.items = (int)((t.u.elem.count + kPersistElems - 1) / kPersistElems);
+            const hipError_t e = record_task(r, t);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
-    hipLaunchKernelGGL(k_fill_u32, dim3(fill_blocks(count)), dim3(256), 0, st, p, count, v);
+    hipLaunchKernelGGL(k_fill_u32, dim3(fill_blocks(count + count2)), dim3(256), 0, st, p, count, p2, count2, v);
     return hipGetLastError();
 }
 hipError_t launch_mul_copy(const float *a, const float *b, float *out, size_t count, hipStream_t st) {
@@ -441,16 +466,14 @@ hipError_t launch_lgamma_sum(const float *meas, int count, float2 *out, uint32_t
         return record_task(r, t);
     }
     // 512-thread workgroups (double-precision ln Gamma needs more than the 128 registers a 1024-thread
-    // workgroup leaves each lane), about 8 bins per thread, at most kLgammaParts of them; the parts in
-    // out[2..]
-    const int nparts = std::min(kLgammaParts, std::max(1, (count + 4095) / 4096));
-    double *part = reinterpret_cast<double *>(out + 2);
-    hipLaunchKernelGGL(k_lgamma_part, dim3((unsigned)nparts), dim3(512), 0, st, meas, count, part, flag);
-    hipLaunchKernelGGL(k_lgamma_final, dim3(1), dim3(64), 0, st, (const double *)part, nparts, out);
+    // workgroup leaves each lane), one bin per thread up to kLgammaParts of them: a bin's ln Gamma and logarithm
+    // are one long dependent chain (8 bins per thread took 15 us where one takes 6); the parts in out[2..]
+    hipLaunchKernelGGL(k_lgamma_part, dim3((unsigned)lgamma_parts(count)), dim3(512), 0, st, meas, count,
+                       reinterpret_cast<double *>(out + 2), flag);
     return hipGetLastError();
 }
-hipError_t launch_nll_finish(const float2 *partial, int chunks, int C, const float2 *lg, const uint32_t *meas_flag,
-                             float *obj, uint32_t *status, hipStream_t st) {
+hipError_t launch_nll_finish(const float2 *partial, int chunks, int C, const float2 *lg, int count,
+                             const uint32_t *meas_flag, float *obj, uint32_t *status, hipStream_t st) {
     if (TaskRecorder *r = task_recorder()) {
         TaskRec t{};
         t.kind = T_NLL_FINISH;
@@ -458,8 +481,8 @@ hipError_t launch_nll_finish(const float2 *partial, int chunks, int C, const flo
         t.grid = t.items = (C + kPersistThreads - 1) / kPersistThreads;
         return record_task(r, t);
     }
-    hipLaunchKernelGGL(k_nll_finish, dim3((unsigned)((C + 63) / 64)), dim3(64), 0, st, partial, chunks, C, lg,
-                       meas_flag, obj, status);
+    hipLaunchKernelGGL(k_nll_finish, dim3((unsigned)((C + 3) / 4)), dim3(256), 0, st, partial, chunks, C,
+                       reinterpret_cast<const double *>(lg + 2), lgamma_parts(count), meas_flag, obj, status);
     return hipGetLastError();
 }
 hipError_t launch_adj_elem(const AdjElemArgs &a, hipStream_t st) {

@@ -1052,16 +1052,16 @@ __global__ __launch_bounds__(1024) void k_tail(DevGeom g, Bands bands, int rpt, 
 // j + kSplitLanes, ... of the ray. A chunk is summed exactly as in k_fwd's single-stage path (same
 // positions, same bilinear reads, FMAs in sample order), and the chunk sums are then added to the
 // compensated total in chunk order after a shuffle, so every ray's result equals k_fwd's and
-// k_fwd_pair's bit for bit. Single-stage images, n_samples <= 16 kSplitLanes kSplitCpl; epilogues y and
-// the MLEM ratio (the likelihood keeps its per-workgroup partials in k_fwd).
+// k_fwd_pair's bit for bit. Single-stage images, n_samples <= 16 kSplitLanes kSplitCpl. In the likelihood
+// a ray's first lane forms its terms, and the workgroup's sum is its partial.
 constexpr int kSplitLanes = 8;
 constexpr int kSplitCpl = 2;  // chunks per lane
 
 #ifndef BOAC_BODIES_ONLY
 template <int MODE, bool PAIRED>
 __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chunks, int C, FwdArgs A) {
-    static_assert(MODE != FWD_NLL, "the likelihood epilogue runs in k_fwd");
     extern __shared__ float lds[];
+    __shared__ float red[32];
     int cand, chunk;
     ray_block(blockIdx.x, chunks, C, cand, chunk);
     const int nrays = g.nah * g.nb;
@@ -1134,10 +1134,21 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
             kahan_add(c2, __shfl(mine2, base + ck % kSplitLanes, kWave));
         }
     }
-    if (!live || lane != 0) return;
     bool zero_proj = false;
-    fwd_emit<MODE>(A, cand, ray, S, g.dx * comp_value(c), zero_proj);
-    if constexpr (PAIRED) fwd_emit<MODE>(A, cand, opp, S2, g.dx * comp_value(c2), zero_proj);
+    Comp nll{0.f, 0.f};
+    if (live && lane == 0) {
+        const float t0 = fwd_emit<MODE>(A, cand, ray, S, g.dx * comp_value(c), zero_proj);
+        if constexpr (MODE == FWD_NLL) comp_add(nll, t0);
+        if constexpr (PAIRED) {
+            const float t1 = fwd_emit<MODE>(A, cand, opp, S2, g.dx * comp_value(c2), zero_proj);
+            if constexpr (MODE == FWD_NLL) comp_add(nll, t1);
+        }
+    }
+    if constexpr (MODE == FWD_NLL) {
+        if (zero_proj && A.status) atomicOr(A.status + cand, 1u);
+        const Comp r = block_reduce(nll, red);
+        if (threadIdx.x == 0) A.partial[(size_t)cand * chunks + chunk] = make_float2(r.s, r.e);
+    }
 }
 #endif
 
@@ -1178,12 +1189,10 @@ hipError_t launch_att(const DevGeom &g, const RayCfg &rc, const Bands &bands, co
 template <int MODE, bool PAIRED>
 static void fwd_mode(const DevGeom &g, const RayCfg &rc, const Bands &bands, const FwdArgs &a, int C,
                      hipStream_t st) {
-    if constexpr (MODE != FWD_NLL) {
-        if (rc.split_chunks > 0 && rc.single && a.img_comps == 1 && g.nt <= 16 * kSplitLanes * kSplitCpl) {
-            hipLaunchKernelGGL((k_fwd_split<MODE, PAIRED>), dim3((unsigned)(rc.split_chunks * C)), dim3(256), rc.lds,
-                               st, g, bands.band(0, g.n), rc.split_chunks, C, a);
-            return;
-        }
+    if (rc.split_chunks > 0 && (MODE != FWD_NLL || rc.split_nll)) {
+        hipLaunchKernelGGL((k_fwd_split<MODE, PAIRED>), dim3((unsigned)(rc.split_chunks * C)), dim3(256), rc.lds, st, g,
+                           bands.band(0, g.n), rc.split_chunks, C, a);
+        return;
     }
     if (rc.pair && rc.single && a.img_comps == 1 && C >= 2)
         hipLaunchKernelGGL((k_fwd_pair<MODE, PAIRED>), dim3((unsigned)(rc.chunks * ((C + 1) / 2))), dim3(rc.block),
@@ -1212,6 +1221,8 @@ hipError_t launch_fwd(int mode, const DevGeom &g, const RayCfg &rc, const Bands 
     }
     const bool paired = a.E != nullptr;
     if (paired && g.nah * 2 != g.na) return hipErrorInvalidValue;
+    if (rc.split_chunks > 0 && (!rc.single || a.img_comps != 1 || g.nt > 16 * kSplitLanes * kSplitCpl))
+        return hipErrorInvalidValue;
     switch (mode) {
         case FWD_PROJ: paired ? fwd_mode<FWD_PROJ, true>(g, rc, bands, a, C, st)
                               : fwd_mode<FWD_PROJ, false>(g, rc, bands, a, C, st); break;

@@ -32,8 +32,10 @@ struct RayCfg {
     size_t lds;  // dynamic LDS bytes of one image stage
     bool single; // whole image staged at once
     bool pair;   // forward projection of two candidates per workgroup (single stage, 2 lds bytes)
-    int split_chunks;  // > 0: few candidates: the projection (not the likelihood) splits each ray over 8
-                       // lanes, 32 rays per 256-thread workgroup, split_chunks workgroups per candidate
+    int split_chunks;  // > 0: few candidates: the projection splits each ray over 8 lanes, 32 rays per
+                       // 256-thread workgroup, split_chunks workgroups per candidate
+    bool split_nll;    // the likelihood's projection too (its partials: split_chunks per candidate)
+    int nll_chunks() const { return split_nll ? split_chunks : chunks; }
     // attenuation build with the scan over 8 lanes per ray (single stage; scan_passes 0 = one thread per
     // ray): scan_block threads, scan_passes rays per lane group, scan_chunks workgroups per candidate
     int scan_block, scan_passes, scan_chunks;
@@ -213,7 +215,7 @@ struct TaskRec {
     unsigned lds;      // dynamic LDS bytes of one item (all of its recorded workgroups)
     unsigned sub_lds;  // 256-thread tasks: dynamic LDS bytes of one recorded workgroup
     union {
-        struct { DevGeom g; const float *cand; float delta_r; float *mu; size_t img_cs; uint32_t *status; int nbx; } raster;
+        struct { DevGeom g; const float *cand; float delta_r; float *mu; size_t img_cs; uint32_t *status; float *ones; int nbx; } raster;
         struct { DevGeom g; const float *cand; float delta_r; const float *mubar; size_t img_cs; float *grad; } raster_adj;
         struct { RayTask r; const float *mu; float *att; size_t img_cs, att_cs; float *E; size_t e_cs; int passes; } att;
         struct { RayTask r; FwdArgs A; } fwd;
@@ -252,8 +254,9 @@ struct PersistArgs {
 hipError_t launch_persist(const PersistArgs &a, int workgroups, unsigned lds, hipStream_t st);
 
 // ---- launchers (each returns the hipError_t of the launch) ----
+// ones: null, or images to set to 1 (the MLEM start)
 hipError_t launch_raster(const DevGeom &g, const float *cand, int C, float delta_r, float *mu, size_t img_cs,
-                         uint32_t *status, hipStream_t st);
+                         uint32_t *status, float *ones, hipStream_t st);
 // grad: [C][kGradComps] partial gradients
 hipError_t launch_raster_adj(const DevGeom &g, const float *cand, int C, float delta_r, const float *mubar,
                              size_t img_cs, float *grad, hipStream_t st);
@@ -270,14 +273,17 @@ hipError_t launch_tail(const DevGeom &g, const RayCfg &rc, const Bands &bands, c
                        hipStream_t st);
 hipError_t launch_back(int mode, const DevGeom &g, const BackCfg &bc, const BackArgs &a, hipStream_t st);
 hipError_t launch_fill(float *p, size_t count, float v, hipStream_t st);
-hipError_t launch_fill_u32(uint32_t *p, size_t count, uint32_t v, hipStream_t st);
-// The likelihood's measurement-only constant (FP64). out holds kLgammaOut float2: out[0] receives the
-// constant as (value, remainder), the rest the per-workgroup partial sums (doubles).
+hipError_t launch_fill_u32(uint32_t *p, size_t count, uint32_t *p2, size_t count2, uint32_t v, hipStream_t st);
+// The likelihood's measurement-only constant (FP64). out holds kLgammaOut float2: from out[2] on the
+// per-workgroup partial sums (doubles), which launch_nll_finish adds; out[0], in a recorded sequence, the
+// constant as (value, remainder).
 constexpr int kLgammaParts = 32;
+inline int lgamma_parts(int count) { return count < 512 * kLgammaParts ? (count + 511) / 512 : kLgammaParts; }
 constexpr int kLgammaOut = 2 + 2 * kLgammaParts;
 hipError_t launch_lgamma_sum(const float *meas, int count, float2 *out, uint32_t *flag, hipStream_t st);
-hipError_t launch_nll_finish(const float2 *partial, int chunks, int C, const float2 *lg, const uint32_t *meas_flag,
-                             float *obj, uint32_t *status, hipStream_t st);
+// count: the bins launch_lgamma_sum was given
+hipError_t launch_nll_finish(const float2 *partial, int chunks, int C, const float2 *lg, int count,
+                             const uint32_t *meas_flag, float *obj, uint32_t *status, hipStream_t st);
 hipError_t launch_adj_elem(const AdjElemArgs &a, hipStream_t st);
 hipError_t launch_grad_finish(const float *grad, int C, int ncomp, float *d_grad, uint32_t *status, hipStream_t st);
 hipError_t launch_mul_copy(const float *a, const float *b, float *out, size_t count, hipStream_t st);

@@ -588,6 +588,9 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
     if (split_on && C <= kFewCand && comps == 1 && rc->single && g.n_samples <= 256 &&
         (long)((nrays + 255) / 256) * C < ctx->n_cu)
         rc->split_chunks = (nrays + 31) / 32;
+    // its likelihood partials, one per 32 held rays, are within the no-allocation scratch's estimate (one per 64
+    // rays of every angle) only with half the angles held
+    rc->split_nll = rc->split_chunks > 0 && (!ctx->arena || nah < g.n_angles);
     // attenuation build: the scan of each ray spread over 8 lanes (single stage, up to 256 samples;
     // BOAC_ATT_SCAN=0: one thread per ray); 1024-thread workgroups when there are rays enough, and as
     // many rays per lane group as still give every CU two workgroups (at most 32)
@@ -612,6 +615,7 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
             }
         rc->chunks = (nrays + 1024 * rc->rpt - 1) / (1024 * rc->rpt);
         rc->split_chunks = 0;
+        rc->split_nll = false;
         if (rc->scan_passes > 0) {
             const long total = (nrays + 127) / 128;
             rc->scan_block = 1024;
@@ -950,7 +954,7 @@ static boac_status eval_forward(boac_ctx *ctx, const boac_geom &g, const float *
     BOAC_TRY(ensure_t(ctx, "F0", (size_t)Cc * z.I, &F0));
     BOAC_TRY(ensure_t(ctx, "F1", (size_t)Cc * z.I, &F1));
     BOAC_TRY(ensure_t(ctx, "r", (size_t)Cc * z.Y, &r));
-    BOAC_TRY(ensure_t(ctx, "partial", (size_t)Cc * p.ray1.chunks, &partial));
+    BOAC_TRY(ensure_t(ctx, "partial", (size_t)Cc * p.ray1.nll_chunks(), &partial));
     BOAC_TRY(ensure_t(ctx, "lg", kLgammaOut, &lg));
     BOAC_TRY(ensure_t(ctx, "flag", 4, &flag));
     BOAC_TRY(ensure_t(ctx, "status_int", (size_t)C, &st_int));
@@ -966,8 +970,7 @@ static boac_status eval_forward(boac_ctx *ctx, const boac_geom &g, const float *
     }
     uint32_t *stat = status ? status : st_int;
 
-    HIP_TRY(launch_fill_u32(flag, 4, 0u, st));
-    HIP_TRY(launch_fill_u32(stat, (size_t)C, 0u, st));
+    HIP_TRY(launch_fill_u32(flag, 4, stat, (size_t)C, 0u, st));
     BOAC_TRY(timed(ctx, BOAC_K_REDUCE, 4.0 * z.Y, st,
                    [&] { return launch_lgamma_sum(meas, (int)z.Y, lg, flag, st); }));
 
@@ -975,15 +978,15 @@ static boac_status eval_forward(boac_ctx *ctx, const boac_geom &g, const float *
         const int n = std::min(Cc, C - c0);
         const float *cd = cand + (size_t)c0 * 8;
         BOAC_TRY(timed(ctx, BOAC_K_RASTER, 4.0 * n * (8 + z.I), st,
-                       [&] { return launch_raster(dg, cd, n, delta_r, mu, z.I, stat + c0, st); }));
+                       [&] { return launch_raster(dg, cd, n, delta_r, mu, z.I, stat + c0, F0, st); }));
         BOAC_TRY(run_att(ctx, dg, p, z, mu, att, n, st, E));
         {
             BackArgs b = back_args(z, att, nullptr, s, n, E);
             BOAC_TRY(run_back(ctx, BACK_SENS, dg, p, z, b, st));
         }
-        HIP_TRY(launch_fill(F0, (size_t)n * z.I, 1.f, st));
         float *Fc = F0, *Fn = F1;
         for (int it = 0; it < K; ++it) {
+            if (it == K - 1 && img_out) Fn = img_out + (size_t)c0 * z.I;  // the last iterate, in place
             FwdArgs a = fwd_args(z, att, Fc, meas, E);
             a.r_out = r;
             BOAC_TRY(run_fwd(ctx, FWD_RATIO, dg, p, z, a, n, st));
@@ -998,10 +1001,10 @@ static boac_status eval_forward(boac_ctx *ctx, const boac_geom &g, const float *
         a.status = stat + c0;
         a.y_out = yK;
         BOAC_TRY(run_fwd(ctx, FWD_NLL, dg, p, z, a, n, st));
-        BOAC_TRY(timed(ctx, BOAC_K_REDUCE, 8.0 * n * p.ray1.chunks, st, [&] {
-            return launch_nll_finish(partial, p.ray1.chunks, n, lg, flag, obj + c0, stat + c0, st);
+        BOAC_TRY(timed(ctx, BOAC_K_REDUCE, 8.0 * n * p.ray1.nll_chunks(), st, [&] {
+            return launch_nll_finish(partial, p.ray1.nll_chunks(), n, lg, (int)z.Y, flag, obj + c0, stat + c0, st);
         }));
-        if (img_out) HIP_TRY(launch_copy(Fc, img_out + (size_t)c0 * z.I, (size_t)n * z.I, st));
+        if (img_out && K == 0) HIP_TRY(launch_copy(Fc, img_out + (size_t)c0 * z.I, (size_t)n * z.I, st));
         if (env_grad) {
             // y = A F^K with F^K constant: att_bar = dx ybar (W F^K), then the scan and exp transposes
             // (the tail with a zero first image and rho = ybar), mu_bar = W^T m_bar, raster adjoint
@@ -1074,7 +1077,7 @@ static boac_status eval_grad(boac_ctx *ctx, const boac_geom &g, const float *mea
     BOAC_TRY(ensure_t(ctx, "Ftmp", (size_t)Cc * I, &Ftmp));
     BOAC_TRY(ensure_t(ctx, "Fwork", (size_t)2 * Cc * I, &Fwork));
     BOAC_TRY(ensure_t(ctx, "pair", (size_t)Cc * I, &pair));
-    BOAC_TRY(ensure_t(ctx, "partial", (size_t)Cc * p.ray1.chunks, &partial));
+    BOAC_TRY(ensure_t(ctx, "partial", (size_t)Cc * p.ray1.nll_chunks(), &partial));
     BOAC_TRY(ensure_t(ctx, "lg", kLgammaOut, &lg));
     BOAC_TRY(ensure_t(ctx, "flag", 4, &flag));
     BOAC_TRY(ensure_t(ctx, "status_int", (size_t)C, &st_int));
@@ -1088,8 +1091,7 @@ static boac_status eval_grad(boac_ctx *ctx, const boac_geom &g, const float *mea
     BOAC_TRY(ensure_t(ctx, "segQ", (size_t)ck * Cc * I, &segQ));
     uint32_t *stat = status ? status : st_int;
 
-    HIP_TRY(launch_fill_u32(flag, 4, 0u, st));
-    HIP_TRY(launch_fill_u32(stat, (size_t)C, 0u, st));
+    HIP_TRY(launch_fill_u32(flag, 4, stat, (size_t)C, 0u, st));
     BOAC_TRY(timed(ctx, BOAC_K_REDUCE, 4.0 * Y, st, [&] { return launch_lgamma_sum(meas, (int)Y, lg, flag, st); }));
 
     for (int c0 = 0; c0 < C; c0 += Cc) {
@@ -1099,7 +1101,7 @@ static boac_status eval_grad(boac_ctx *ctx, const boac_geom &g, const float *mea
         auto rec = [&](float *base, int slot, size_t per) { return base + (size_t)slot * Cc * per; };
 
         BOAC_TRY(timed(ctx, BOAC_K_RASTER, 4.0 * n * (8 + I), st,
-                       [&] { return launch_raster(dg, cd, n, delta_r, mu, I, stat + c0, st); }));
+                       [&] { return launch_raster(dg, cd, n, delta_r, mu, I, stat + c0, recF, st); }));
         BOAC_TRY(run_att(ctx, dg, p, z, mu, att, n, st, E));
         {
             BackArgs b = back_args(z, att, nullptr, s, n, E);
@@ -1119,8 +1121,7 @@ static boac_status eval_grad(boac_ctx *ctx, const boac_geom &g, const float *mea
         };
 
         // ---- forward sweep, storing records at checkpoints
-        float *Fcur = rec(recF, 0, I);
-        HIP_TRY(launch_fill(Fcur, nI, 1.f, st));
+        float *Fcur = rec(recF, 0, I);  // F^0 = 1, set with the rasteriser
         float *work[2] = {Fwork, Fwork + (size_t)Cc * I};
         int wsel = 0;
         for (int it = 0; it < K; ++it) {
@@ -1145,8 +1146,8 @@ static boac_status eval_grad(boac_ctx *ctx, const boac_geom &g, const float *mea
             a.status = stat + c0;
             a.y_out = yK;
             BOAC_TRY(run_fwd(ctx, FWD_NLL, dg, p, z, a, n, st));
-            BOAC_TRY(timed(ctx, BOAC_K_REDUCE, 8.0 * n * p.ray1.chunks, st, [&] {
-                return launch_nll_finish(partial, p.ray1.chunks, n, lg, flag, obj + c0, stat + c0, st);
+            BOAC_TRY(timed(ctx, BOAC_K_REDUCE, 8.0 * n * p.ray1.nll_chunks(), st, [&] {
+                return launch_nll_finish(partial, p.ray1.nll_chunks(), n, lg, (int)z.Y, flag, obj + c0, stat + c0, st);
             }));
         }
         // ---- reverse sweep
@@ -1360,7 +1361,7 @@ boac_status boac_rasterize_mu(boac_ctx *ctx, const boac_geom *geom, const boac_c
     hipStream_t st = (hipStream_t)stream;
     const Sizes z = sizes_of(*geom);
     return timed(ctx, BOAC_K_RASTER, 4.0 * C * (8 + z.I), st, [&] {
-        return launch_raster(dg, (const float *)d_cand, C, delta_r_cm, d_mu, z.I, nullptr, st);
+        return launch_raster(dg, (const float *)d_cand, C, delta_r_cm, d_mu, z.I, nullptr, nullptr, st);
     });
 }
 
