@@ -33,6 +33,14 @@ constexpr int kMaxRpt = 4;
 constexpr int kBandChunk = 16;  // samples per load batch in the row-band paths
 
 // ------------------------------------------------------------------ attenuation
+// One thread per ray, from the detector end: T the compensated suffix sum of m = W mu, att = exp(-L) of
+// L_k = dx (m_k / 2 + T), the 4 samples of a group (k a multiple of 4) as one 16-byte store, padding rows 0.
+// Bound by the stores (268M samples, 256 candidates at 128 pixels and 128 angles: 263 us, 4.1 TB/s; over 8
+// lanes per ray, with its shuffles, 381 us).
+// Row bands (!SINGLE): V is monotone along a ray, so the ray meets the bands in the order of its direction
+// and each is staged once for the rays of that direction; a ray keeps its sum, its open group and its next
+// sample in registers from band to band. (Storing m band by band and scanning it in a second pass took 562 us
+// for 32 candidates at 256 pixels and 128 angles, against 356.)
 template <bool SINGLE>
 __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const Bands &bands, int rpt, int chunks, int C,
                                              const float *__restrict__ mu, float *__restrict__ att, size_t img_cs,
@@ -45,114 +53,116 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
     const float *img = mu + cand * img_cs;
     float *out = att + cand * att_cs;
 
-    for (int bi = 0; bi < bands.count; ++bi) {
-        const Band band = bands.band(bi, g.n);
+    if constexpr (SINGLE) {
+        __syncthreads();  // the persistent executor's previous item
+        stage_whole(img, g.n, bands.band(0, g.n), lds);
         __syncthreads();
-        stage_band<1>(img, g.n, band, lds);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kMaxRpt; ++j) {
-            if (j >= rpt) break;
+        for (int j = 0; j < rpt; ++j) {
             const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-            if (ray >= nrays) continue;
+            if (ray >= nrays) break;
             const int a = ray / g.nb, b = ray - a * g.nb;
             const float2 cs = g.trig[a];
             float Ub, Vb;
             ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
             float *col = out + att_base(g, a, b);
-            if constexpr (SINGLE) {
-                // single pass from the detector end: running suffix sum T = sum_{k'>k} m_k'; the 4
-                // samples of a group (k a multiple of 4) are one 16-byte store, padding rows get 0
-                Comp T{0.f, 0.f};
-                for (int kg = (g.nt - 1) >> 2; kg >= 0; --kg) {
-                    float e[4];
+            Comp T{0.f, 0.f};
+            for (int kg = (g.nt - 1) >> 2; kg >= 0; --kg) {
+                float e[4];
 #pragma unroll
-                    for (int q = 3; q >= 0; --q) {
-                        const int k = 4 * kg + q;
-                        e[q] = 0.f;
-                        if (k < g.nt) {
-                            float U, V;
-                            sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
-                            const Tap t = make_tap<true>(U, V, nf, pitch, band);
-                            const float m = lerp2(lds + t.off, pitch, t.fu, t.fv);
-                            const float L = g.dx * (fmaf(0.5f, m, T.s) + T.e);
-                            e[q] = fmaxf(expf(-L), kMinNormal);
-                            comp_add(T, m);
-                        }
+                for (int q = 3; q >= 0; --q) {
+                    const int k = 4 * kg + q;
+                    e[q] = 0.f;
+                    if (k < g.nt) {
+                        float U, V;
+                        sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
+                        const float m = bilinear_whole(lds, U, V, nf, pitch);
+                        const float L = g.dx * (fmaf(0.5f, m, T.s) + T.e);
+                        e[q] = fmaxf(expf(-L), kMinNormal);
+                        comp_add(T, m);
                     }
-                    *reinterpret_cast<float4 *>(col + att_row(g, 4 * kg)) = make_float4(e[0], e[1], e[2], e[3]);
                 }
-                // opposed-ray pairing: exp(-T) of the whole ray, T = dx sum_k m_k
-                if (E) E[cand * e_cs + ray] = expf(-g.dx * comp_value(T));
-            } else {
-                // pass 1 of 2: store m_k of the samples in this band, a 4-sample group (one 16-byte
-                // load and store) at a time from the 4-aligned group holding the first. The ray is this
-                // thread's alone and its bands run in order, so a group's samples owned by another band
-                // are written back as loaded (values of an earlier band, or not yet written).
-                int k0, k1;
-                band_k_range(g, band, Vb, cs.x, k0, k1);
-                const int kstart = (k0 <= k1) ? (k0 & ~3) : k1 + 1;
-                for (int kg = kstart; kg <= k1; kg += 4) {
-                    float4 *grp = reinterpret_cast<float4 *>(col + att_row(g, kg));
-                    const float4 old = *grp;
-                    float ov[4] = {old.x, old.y, old.z, old.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int k = kg + q;
-                        if (k <= k1) {
-                            float U, V;
-                            sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
-                            const Tap t = make_tap<false>(U, V, nf, pitch, band);
-                            if (t.mine) ov[q] = lerp2(lds + t.off, pitch, t.fu, t.fv);
-                        }
-                    }
-                    *grp = make_float4(ov[0], ov[1], ov[2], ov[3]);
-                }
+                *reinterpret_cast<float4 *>(col + att_row(g, 4 * kg)) = make_float4(e[0], e[1], e[2], e[3]);
             }
+            // opposed-ray pairing: exp(-T) of the whole ray, T = dx sum_k m_k
+            if (E) E[cand * e_cs + ray] = expf(-g.dx * comp_value(T));
         }
-    }
-    if constexpr (!SINGLE) {
-        // pass 2: scan the stored m_k (written by this same thread) from the detector end
+    } else {
+        // directions of the workgroup's rays: V grows with k (cos >= 0: the last band first), or falls
+        const int r0 = chunk * rpt * (int)blockDim.x, r1 = min(r0 + rpt * (int)blockDim.x, nrays) - 1;
+        bool up = false, down = false;
+        for (int a = r0 / g.nb; a <= r1 / g.nb; ++a) {
+            if (g.trig[a].x >= 0.f)
+                up = true;
+            else
+                down = true;
+        }
+        Comp T[kMaxRpt];
+        float4 open[kMaxRpt];  // the open group: its samples so far, the latest first
+        int next[kMaxRpt];
 #pragma unroll
         for (int j = 0; j < kMaxRpt; ++j) {
-            if (j >= rpt) break;
-            const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-            if (ray >= nrays) continue;
-            const int a = ray / g.nb, b = ray - a * g.nb;
-            // 16 samples (4 groups of 4, one 16-byte access each) at a time from the detector end:
-            // the chunk's loads precede its stores; padding rows get 0
-            constexpr int KG = kBandChunk / 4;
-            const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(out, (unsigned)(4 * att_cs));
-            const unsigned roff = 4u * (unsigned)att_base(g, a, b);
-            const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-            Comp T{0.f, 0.f};
-            for (int kg0 = (g.nt - 1) >> 2; kg0 >= 0; kg0 -= KG) {
-                float4 mv[KG];
+            T[j] = Comp{0.f, 0.f};
+            open[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            next[j] = g.nt - 1;
+        }
+        const int visits = up && down ? 2 * bands.count - 1 : bands.count;
+        for (int v = 0; v < visits; ++v) {
+            const int bi = !up ? v : v < bands.count ? bands.count - 1 - v : v - (bands.count - 1);
+            const Band band = bands.band(bi, g.n);
+            __syncthreads();
+            stage_band<1>(img, g.n, band, lds);
+            __syncthreads();
 #pragma unroll
-                for (int j = 0; j < KG; ++j) {
-                    const int kg = kg0 - j;
-                    mv[j] = (kg >= 0) ? buffer_ld4(rs, roff + 4u * att_row(g, 4 * kg), 0u) : z4;
-                }
-#pragma unroll
-                for (int j = 0; j < KG; ++j) {
-                    const int kg = kg0 - j;
-                    if (kg < 0) break;
-                    float e[4];
-#pragma unroll
-                    for (int q = 3; q >= 0; --q) {
-                        const int k = 4 * kg + q;
-                        e[q] = 0.f;
-                        if (k < g.nt) {
-                            const float m = f4at(mv[j], q);
-                            const float L = g.dx * (fmaf(0.5f, m, T.s) + T.e);
-                            e[q] = fmaxf(expf(-L), kMinNormal);
-                            comp_add(T, m);
+            for (int j = 0; j < kMaxRpt; ++j) {
+                if (j >= rpt) break;
+                const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
+                if (ray >= nrays) continue;
+                const int a = ray / g.nb, b = ray - a * g.nb;
+                const float2 cs = g.trig[a];
+                // rays of the other direction start on the last visit of these, with the same band
+                if (cs.x >= 0.f ? v >= bands.count : (up && v < bands.count - 1)) continue;
+                float Ub, Vb;
+                ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
+                float *col = out + att_base(g, a, b);
+                Comp t = T[j];
+                float4 o = open[j];
+                int k = next[j];
+                auto step = [&](const Tap &tap) {
+                    const float m = lerp2(lds + tap.off, pitch, tap.fu, tap.fv);
+                    const float L = g.dx * (fmaf(0.5f, m, t.s) + t.e);
+                    o = make_float4(fmaxf(expf(-L), kMinNormal), o.x, o.y, o.z);
+                    comp_add(t, m);
+                };
+                auto tap_at = [&](int kk) {
+                    float U, V;
+                    sample_uv(Ub, Vb, tau_of(g, kk), cs.x, cs.y, U, V);
+                    return make_tap<false>(U, V, nf, pitch, band);
+                };
+                while (k >= 0) {
+                    const Tap t0 = tap_at(k);
+                    if (!t0.mine) break;
+                    if ((k & 3) == 3) {
+                        // a whole group: in the band if its first and last samples are
+                        const Tap t3 = tap_at(k - 3);
+                        if (t3.mine) {
+                            step(t0);
+                            step(tap_at(k - 1));
+                            step(tap_at(k - 2));
+                            step(t3);
+                            *reinterpret_cast<float4 *>(col + att_row(g, k - 3)) = o;
+                            k -= 4;
+                            continue;
                         }
                     }
-                    buffer_st4(rs, roff + 4u * att_row(g, 4 * kg), 0u, make_float4(e[0], e[1], e[2], e[3]));
+                    step(t0);
+                    if ((k & 3) == 0) *reinterpret_cast<float4 *>(col + att_row(g, k)) = o;
+                    --k;
                 }
+                T[j] = t;
+                open[j] = o;
+                next[j] = k;
+                if (E && k < 0) E[cand * e_cs + ray] = expf(-g.dx * comp_value(t));
             }
-            if (E) E[cand * e_cs + ray] = expf(-g.dx * comp_value(T));  // opposed-ray pairing
         }
     }
 }
@@ -167,28 +177,25 @@ __global__ __launch_bounds__(1024) void k_att(DevGeom g, Bands bands, int rpt, i
 }
 #endif
 
-// Attenuation build with each ray's scan spread over kScanLanes lanes of one wave (single-stage images).
-// The ray is walked from the detector end in rounds of kScanLanes 4-sample groups, lane j taking the
-// j-th group of the round counted from the detector: each lane samples its 4 values m_k = (W mu)_k from
-// the staged image and sums them (compensated); a Kogge-Stone scan over the 8 lanes (3 shuffle steps of
-// compensated merges) gives each lane the sum of the groups nearer the detector in this round, to which
-// the carry of the earlier rounds is merged; the lane then scans its own 4 samples toward the source,
-// L_k = dx (m_k / 2 + sum_{k'>k} m_k'), and stores att = exp(-L) (no smaller than the smallest normal
-// float) as one 16-byte store, and the round's total joins the carry. The 8 lanes of a ray and the 8
-// rays of a wave (consecutive bins) write whole 128-byte lines of the 4 x 8-block layout. The carry
-// ends as the ray total: exp(-T) for opposed-ray pairing. passes: rays per lane group handled in turn,
-// so that one image stage serves many rays.
+// The same for few candidates: a ray's samples over kScanLanes lanes of one wave (single-stage images). The
+// ray is walked from the detector end in rounds of kScanLanes 4-sample groups, lane j sampling the j-th group
+// of the round; every lane then runs the round's compensated sum sample by sample (the other lanes' values by
+// shuffles), noting it where its own group begins, so every att has k_att's bits. The exponentials and stores
+// are spread again; the 8 lanes of a ray and the 8 rays of a wave (consecutive bins) write whole 128-byte
+// lines. passes: rays per lane group handled in turn, so that one image stage serves many rays.
 constexpr int kScanLanes = 8;
 
-__device__ __forceinline__ void k_att_scan_body(int bid, float *lds, DevGeom g, Band band, int passes, int chunks, int C,
+#ifndef BOAC_BODIES_ONLY
+__global__ __launch_bounds__(256) void k_att_scan(DevGeom g, Band band, int passes, int chunks, int C,
                                                   const float *__restrict__ mu, float *__restrict__ att,
                                                   size_t img_cs, size_t att_cs, float *__restrict__ E,
                                                   size_t e_cs) {
+    extern __shared__ float lds[];
     int cand, chunk;
-    ray_block(bid, chunks, C, cand, chunk);
+    ray_block(blockIdx.x, chunks, C, cand, chunk);
     const int pitch = g.n + 3;
     const float nf = (float)g.n;
-    stage_whole(mu + cand * img_cs, g.n, band, lds);
+    stage_whole<16>(mu + cand * img_cs, g.n, band, lds);
     __syncthreads();
     const int nrays = g.nah * g.nb;
     const int rpp = blockDim.x / kScanLanes;
@@ -205,35 +212,27 @@ __device__ __forceinline__ void k_att_scan_body(int bid, float *lds, DevGeom g, 
         float Ub, Vb;
         ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
         const unsigned roff = 4u * (unsigned)att_base(g, a, b);
-        Comp carry{0.f, 0.f};
+        Comp T{0.f, 0.f};
         for (int r = 0; r < rounds; ++r) {
             const int grp = ng - 1 - (r * kScanLanes + lane);
             float m[4];
-            Comp own{0.f, 0.f};
 #pragma unroll
             for (int q = 3; q >= 0; --q) {
                 const int k = 4 * grp + q;
-                m[q] = 0.f;
+                m[q] = 0.f;  // no sample: adds nothing
                 if (live && grp >= 0 && k < g.nt) {
                     float U, V;
                     sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
                     m[q] = bilinear_whole(lds, U, V, nf, pitch);
-                    comp_add(own, m[q]);
                 }
             }
-            // inclusive scan over the lanes of the ray (lane 0 nearest the detector)
-            Comp inc = own;
+            Comp own{0.f, 0.f};
 #pragma unroll
-            for (int off = 1; off < kScanLanes; off <<= 1) {
-                const Comp o{__shfl(inc.s, base + ((lane - off) & (kScanLanes - 1)), kWave),
-                             __shfl(inc.e, base + ((lane - off) & (kScanLanes - 1)), kWave)};
-                if (lane >= off) comp_merge(inc, o);
+            for (int j = 0; j < kScanLanes; ++j) {
+                if (lane == j) own = T;
+#pragma unroll
+                for (int q = 3; q >= 0; --q) comp_add(T, __shfl(m[q], base + j, kWave));
             }
-            const Comp prev{__shfl(inc.s, base + ((lane - 1) & (kScanLanes - 1)), kWave),
-                            __shfl(inc.e, base + ((lane - 1) & (kScanLanes - 1)), kWave)};
-            const Comp total{__shfl(inc.s, base + kScanLanes - 1, kWave), __shfl(inc.e, base + kScanLanes - 1, kWave)};
-            Comp T = carry;
-            if (lane > 0) comp_merge(T, prev);
             if (live && grp >= 0) {
                 float e[4];
 #pragma unroll
@@ -241,26 +240,16 @@ __device__ __forceinline__ void k_att_scan_body(int bid, float *lds, DevGeom g, 
                     const int k = 4 * grp + q;
                     e[q] = 0.f;
                     if (k < g.nt) {
-                        const float L = g.dx * (fmaf(0.5f, m[q], T.s) + T.e);
+                        const float L = g.dx * (fmaf(0.5f, m[q], own.s) + own.e);
                         e[q] = fmaxf(expf(-L), kMinNormal);
-                        comp_add(T, m[q]);
+                        comp_add(own, m[q]);
                     }
                 }
                 buffer_st4_stream(rs, roff + 4u * att_row(g, 4 * grp), 0u, make_float4(e[0], e[1], e[2], e[3]));
             }
-            comp_merge(carry, total);
         }
-        if (E && live && lane == 0) E[cand * e_cs + ray] = expf(-g.dx * comp_value(carry));
+        if (E && live && lane == 0) E[cand * e_cs + ray] = expf(-g.dx * comp_value(T));
     }
-}
-
-#ifndef BOAC_BODIES_ONLY
-__global__ __launch_bounds__(1024) void k_att_scan(DevGeom g, Band band, int passes, int chunks, int C,
-                                                  const float *__restrict__ mu, float *__restrict__ att,
-                                                  size_t img_cs, size_t att_cs, float *__restrict__ E,
-                                                  size_t e_cs) {
-    extern __shared__ float lds[];
-    k_att_scan_body(blockIdx.x, lds, g, band, passes, chunks, C, mu, att, img_cs, att_cs, E, e_cs);
 }
 #endif
 
@@ -1160,20 +1149,17 @@ hipError_t launch_att(const DevGeom &g, const RayCfg &rc, const Bands &bands, co
                       size_t img_cs, size_t att_cs, float *E, size_t e_cs, int C, hipStream_t st) {
     if (TaskRecorder *r = task_recorder()) {
         TaskRec t{};
-        const bool scan = rc.single && rc.scan_passes > 0;
-        if ((scan ? rc.scan_block : rc.block) != kPersistThreads)
+        if (rc.block != kPersistThreads)
             return record_unsupported(r, "attenuation build planned with other than 1024 threads");
-        t.kind = scan ? T_ATT_SCAN : T_ATT;
+        t.kind = T_ATT;
         t.variant = rc.single ? 1 : 0;
-        t.u.att = {RayTask{g, bands, rc.rpt, scan ? rc.scan_chunks : rc.chunks, C}, mu, att, img_cs, att_cs, E, e_cs,
-                   rc.scan_passes};
-        t.grid = t.items = (scan ? rc.scan_chunks : rc.chunks) * C;
+        t.u.att = {RayTask{g, bands, rc.rpt, rc.chunks, C}, mu, att, img_cs, att_cs, E, e_cs};
+        t.grid = t.items = rc.chunks * C;
         t.lds = (unsigned)rc.lds;
         return record_task(r, t);
     }
     if (rc.single && rc.scan_passes > 0) {
-        if (rc.scan_block % 64 != 0) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_att_scan, dim3((unsigned)(rc.scan_chunks * C)), dim3(rc.scan_block), rc.lds, st, g,
+        hipLaunchKernelGGL(k_att_scan, dim3((unsigned)(rc.scan_chunks * C)), dim3(256), rc.lds, st, g,
                            bands.band(0, g.n), rc.scan_passes, rc.scan_chunks, C, mu, att, img_cs, att_cs, E, e_cs);
         return hipGetLastError();
     }

@@ -36,9 +36,9 @@ struct RayCfg {
                        // 256-thread workgroup, split_chunks workgroups per candidate
     bool split_nll;    // the likelihood's projection too (its partials: split_chunks per candidate)
     int nll_chunks() const { return split_nll ? split_chunks : chunks; }
-    // attenuation build with the scan over 8 lanes per ray (single stage; scan_passes 0 = one thread per
-    // ray): scan_block threads, scan_passes rays per lane group, scan_chunks workgroups per candidate
-    int scan_block, scan_passes, scan_chunks;
+    // few candidates: attenuation build with a ray over 8 lanes (single stage; scan_passes 0 = one thread per
+    // ray): scan_passes rays per lane group, scan_chunks workgroups of 256 threads per candidate
+    int scan_passes, scan_chunks;
 };
 
 enum FwdMode { FWD_PROJ = 0, FWD_RATIO = 1, FWD_NLL = 2 };
@@ -194,7 +194,7 @@ constexpr int kPersistThreads = 1024;
 constexpr int kPersistElems = 16384;  // elements per item of an elementwise task
 
 enum TaskKind : int {
-    T_RASTER = 0, T_RASTER_ADJ, T_ATT, T_ATT_SCAN, T_FWD, T_FWD_PAIR, T_SWEEP, T_TAIL, T_BACK_COL4,
+    T_RASTER = 0, T_RASTER_ADJ, T_ATT, T_FWD, T_FWD_PAIR, T_SWEEP, T_TAIL, T_BACK_COL4,
     T_FILL, T_FILL_U32, T_MUL_COPY, T_COPY, T_YBAR, T_LGAMMA, T_NLL_FINISH, T_ADJ_ELEM, T_PACK_PAIR,
     T_GRAD_FINISH, T_KINDS
 };
@@ -217,7 +217,7 @@ struct TaskRec {
     union {
         struct { DevGeom g; const float *cand; float delta_r; float *mu; size_t img_cs; uint32_t *status; float *ones; int nbx; } raster;
         struct { DevGeom g; const float *cand; float delta_r; const float *mubar; size_t img_cs; float *grad; } raster_adj;
-        struct { RayTask r; const float *mu; float *att; size_t img_cs, att_cs; float *E; size_t e_cs; int passes; } att;
+        struct { RayTask r; const float *mu; float *att; size_t img_cs, att_cs; float *E; size_t e_cs; } att;
         struct { RayTask r; FwdArgs A; } fwd;
         struct { RayTask r; SweepArgs A; } sweep;
         struct { RayTask r; TailArgs A; } tail;

@@ -591,15 +591,15 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
     // its likelihood partials, one per 32 held rays, are within the no-allocation scratch's estimate (one per 64
     // rays of every angle) only with half the angles held
     rc->split_nll = rc->split_chunks > 0 && (!ctx->arena || nah < g.n_angles);
-    // attenuation build: the scan of each ray spread over 8 lanes (single stage, up to 256 samples;
-    // BOAC_ATT_SCAN=0: one thread per ray); 1024-thread workgroups when there are rays enough, and as
-    // many rays per lane group as still give every CU two workgroups (at most 32)
-    rc->scan_block = rc->scan_passes = rc->scan_chunks = 0;
+    // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give every CU
+    // a workgroup (single stage; BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group as
+    // still give every CU two workgroups (at most 32). One candidate at 128 pixels and 128 angles: 10 us, one
+    // thread per ray 33 us; with a workgroup for every CU one thread per ray is faster (24 candidates at 120
+    // pixels and 75 angles 54 against 137 us).
+    rc->scan_passes = rc->scan_chunks = 0;
     const char *ea = std::getenv("BOAC_ATT_SCAN");
-    if (!(ea && ea[0] == '0') && comps == 1 && rc->single && g.n_samples <= 256) {
-        rc->scan_block = ((long)nrays * C >= 64L * ctx->n_cu * 128) ? 1024 : 256;
-        const int rpp = rc->scan_block / 8;
-        const long total = (nrays + rpp - 1) / rpp;
+    if (!(ea && ea[0] == '0') && comps == 1 && rc->single && (long)((nrays + 255) / 256) * C < ctx->n_cu) {
+        const long total = (nrays + 31) / 32;
         rc->scan_passes = (int)std::min<long>(32, std::max<long>(1, total * C / (2L * ctx->n_cu)));
         rc->scan_chunks = (int)((total + rc->scan_passes - 1) / rc->scan_passes);
     }
@@ -616,12 +616,7 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
         rc->chunks = (nrays + 1024 * rc->rpt - 1) / (1024 * rc->rpt);
         rc->split_chunks = 0;
         rc->split_nll = false;
-        if (rc->scan_passes > 0) {
-            const long total = (nrays + 127) / 128;
-            rc->scan_block = 1024;
-            rc->scan_passes = (int)std::min<long>(32, std::max<long>(1, total * C / (long)ctx->n_cu));
-            rc->scan_chunks = (int)((total + rc->scan_passes - 1) / rc->scan_passes);
-        }
+        rc->scan_passes = 0;
     }
 }
 
