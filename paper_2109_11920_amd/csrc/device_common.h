@@ -296,7 +296,7 @@ __device__ __forceinline__ void stage_band_strided(const float *__restrict__ img
             const int i = band.alo + rr;
             const int l = idx - rr * pitch - 1;
             const bool in = (idx < total) && (i >= 0) && (i < n) && (l >= 0) && (l < n);
-            v[u] = in ? img[((size_t)i * n + l) * stride] : 0.f;
+            v[u] = in ? img[(unsigned)((i * n + l) * stride)] : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -375,6 +375,62 @@ __device__ __forceinline__ void band_k_range(const DevGeom &g, const Band &band,
     hi = fminf(hi + 2.f, (float)(g.nt - 1));
     k0 = (int)floorf(lo);
     k1 = (int)ceilf(hi);
+}
+
+// The ray of this thread in pass j of a row-band workgroup (nrays or more: none). A candidate's waves of 64
+// rays are dealt to its workgroups in turn, rotated from one turn to the next, so that every workgroup and
+// every SIMD in it gets the same mix of angles and of detector parts: which band a ray's samples lie in, and
+// how uneven a wave's rays are, depends on both, and with consecutive rays in a workgroup the CUs were busy
+// 60 to 75% of a launch's time.
+__device__ __forceinline__ int band_ray(int chunk, int chunks, int j) {
+    const int i = j * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6);
+    const int turn = (int)((unsigned)(chunk + i + (i >> 2)) % (unsigned)chunks);
+    return ((i * chunks + turn) << 6) + (int)(threadIdx.x & 63);
+}
+
+// The samples of a ray that `band` owns, exactly: V = Vb + tau c is monotone in k (also as rounded), so they
+// are one range k0..k1 (empty: k0 > k1), the conservative one with its ends tested.
+__device__ __forceinline__ void band_own_range(const DevGeom &g, const Band &band, float Vb, float c, int &k0,
+                                               int &k1) {
+    band_k_range(g, band, Vb, c, k0, k1);
+    const float lo = band.first ? -3e38f : (float)band.alo;
+    const float hi = band.last ? 3e38f : (float)band.ahi;
+    auto own = [&](int k) {
+        const float V = fmaf(tau_of(g, k), c, Vb);
+        return V >= lo && V < hi;
+    };
+    while (k0 <= k1 && !own(k0)) ++k0;
+    while (k0 <= k1 && !own(k1)) --k1;
+}
+// A band's taps without an ownership branch: rows clamped to the staged ones. An owned sample is moved only
+// as the clamp to [-1, n] moves it (the greatest row below ahi is ahi's predecessor among the floats); any
+// other sample reads some staged value, which its user masks.
+struct BandTap {
+    float vmin, vmax;
+    int base;  // LDS element of (row 0, column 0)
+};
+__device__ __forceinline__ BandTap band_tap(const Band &band, float nf, int pitch) {
+    BandTap t;
+    t.vmin = (float)band.alo;
+    t.vmax = band.last ? nf : band.ahi > 0 ? __uint_as_float(__float_as_uint((float)band.ahi) - 1u) : -1e-30f;
+    t.base = 1 - band.alo * pitch;
+    return t;
+}
+__device__ __forceinline__ int band_off(const BandTap &t, float U, float V, float nf, int pitch, float &fu, float &fv) {
+    const float Uc = __builtin_amdgcn_fmed3f(U, -1.f, nf);
+    const float Vc = __builtin_amdgcn_fmed3f(V, t.vmin, t.vmax);
+    fu = __builtin_amdgcn_fractf(Uc);
+    fv = __builtin_amdgcn_fractf(Vc);
+    return (int)fmaf(floorf(Vc), (float)pitch, floorf(Uc)) + t.base;
+}
+// Samples kc..kc + 15 as bits: those in k0..k1.
+__device__ __forceinline__ unsigned band_bits(int kc, int k0, int k1) {
+    const int lo = max(k0 - kc, 0), hi = min(k1 - kc, 15);
+    return (hi < lo) ? 0u : (0xffffu >> (15 - hi)) & (0xffffu << lo);
+}
+// x where bit q (a compile-time constant after unrolling) of `bits` is set, +0 elsewhere.
+__device__ __forceinline__ float bit_keep(unsigned bits, int q, float x) {
+    return __uint_as_float(__float_as_uint(x) & (unsigned)((int)(bits << (31 - q)) >> 31));
 }
 
 // Bilinear read at (U, V) from a whole-image stage (rows -1..n+1, columns -1..n+1, pitch n+3):

@@ -32,15 +32,36 @@ __device__ __forceinline__ void ray_block(int bid, int chunks, int C, int &cand,
 constexpr int kMaxRpt = 4;
 constexpr int kBandChunk = 16;  // samples per load batch in the row-band paths
 
+// A ray's running sum by a run-time index: selects, so that the sums stay in registers.
+template <int N>
+__device__ __forceinline__ Comp comp_pick(const Comp (&v)[N], int j) {
+    Comp c = v[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) {
+        c.s = (i == j) ? v[i].s : c.s;
+        c.e = (i == j) ? v[i].e : c.e;
+    }
+    return c;
+}
+template <int N>
+__device__ __forceinline__ void comp_put(Comp (&v)[N], int j, const Comp &c) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        v[i].s = (i == j) ? c.s : v[i].s;
+        v[i].e = (i == j) ? c.e : v[i].e;
+    }
+}
+
 // ------------------------------------------------------------------ attenuation
 // One thread per ray, from the detector end: T the compensated suffix sum of m = W mu, att = exp(-L) of
 // L_k = dx (m_k / 2 + T), the 4 samples of a group (k a multiple of 4) as one 16-byte store, padding rows 0.
 // Bound by the stores (268M samples, 256 candidates at 128 pixels and 128 angles: 263 us, 4.1 TB/s; over 8
 // lanes per ray, with its shuffles, 381 us).
 // Row bands (!SINGLE): V is monotone along a ray, so the ray meets the bands in the order of its direction
-// and each is staged once for the rays of that direction; a ray keeps its sum, its open group and its next
-// sample in registers from band to band. (Storing m band by band and scanning it in a second pass took 562 us
-// for 32 candidates at 256 pixels and 128 angles, against 356.)
+// and each is staged once for the rays of that direction; a ray keeps its sum and its open group in registers
+// from band to band. Bound by its vector work. 32 candidates at 256 pixels and 128 angles: 262 us; with
+// consecutive rays in a workgroup (see band_ray) and a test and a branch per sample 355; storing m band by band
+// and scanning it in a second pass 562.
 template <bool SINGLE>
 __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const Bands &bands, int rpt, int chunks, int C,
                                              const float *__restrict__ mu, float *__restrict__ att, size_t img_cs,
@@ -87,81 +108,73 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
             if (E) E[cand * e_cs + ray] = expf(-g.dx * comp_value(T));
         }
     } else {
-        // directions of the workgroup's rays: V grows with k (cos >= 0: the last band first), or falls
-        const int r0 = chunk * rpt * (int)blockDim.x, r1 = min(r0 + rpt * (int)blockDim.x, nrays) - 1;
-        bool up = false, down = false;
-        for (int a = r0 / g.nb; a <= r1 / g.nb; ++a) {
-            if (g.trig[a].x >= 0.f)
-                up = true;
-            else
-                down = true;
-        }
+        // rays along which V grows with k (cos >= 0) take the last band first, the others the first; the rays
+        // of a workgroup are of both kinds, and the middle visit serves both
         Comp T[kMaxRpt];
-        float4 open[kMaxRpt];  // the open group: its samples so far, the latest first
-        int next[kMaxRpt];
+        float4 open[kMaxRpt];  // the open group: its samples so far
 #pragma unroll
         for (int j = 0; j < kMaxRpt; ++j) {
             T[j] = Comp{0.f, 0.f};
             open[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-            next[j] = g.nt - 1;
         }
-        const int visits = up && down ? 2 * bands.count - 1 : bands.count;
-        for (int v = 0; v < visits; ++v) {
-            const int bi = !up ? v : v < bands.count ? bands.count - 1 - v : v - (bands.count - 1);
-            const Band band = bands.band(bi, g.n);
+        for (int v = 0; v < 2 * bands.count - 1; ++v) {
+            const Band band = bands.band(v < bands.count ? bands.count - 1 - v : v - (bands.count - 1), g.n);
+            const BandTap bt = band_tap(band, nf, pitch);
             __syncthreads();
             stage_band<1>(img, g.n, band, lds);
             __syncthreads();
-#pragma unroll
-            for (int j = 0; j < kMaxRpt; ++j) {
-                if (j >= rpt) break;
-                const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
+#pragma unroll 1
+            for (int j = 0; j < rpt; ++j) {
+                const int ray = band_ray(chunk, chunks, j);
                 if (ray >= nrays) continue;
                 const int a = ray / g.nb, b = ray - a * g.nb;
                 const float2 cs = g.trig[a];
-                // rays of the other direction start on the last visit of these, with the same band
-                if (cs.x >= 0.f ? v >= bands.count : (up && v < bands.count - 1)) continue;
+                if (cs.x >= 0.f ? v >= bands.count : v < bands.count - 1) continue;
                 float Ub, Vb;
                 ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
+                int k0, k1;
+                band_own_range(g, band, Vb, cs.x, k0, k1);
                 float *col = out + att_base(g, a, b);
-                Comp t = T[j];
-                float4 o = open[j];
-                int k = next[j];
-                auto step = [&](const Tap &tap) {
-                    const float m = lerp2(lds + tap.off, pitch, tap.fu, tap.fv);
-                    const float L = g.dx * (fmaf(0.5f, m, t.s) + t.e);
-                    o = make_float4(fmaxf(expf(-L), kMinNormal), o.x, o.y, o.z);
-                    comp_add(t, m);
-                };
-                auto tap_at = [&](int kk) {
-                    float U, V;
-                    sample_uv(Ub, Vb, tau_of(g, kk), cs.x, cs.y, U, V);
-                    return make_tap<false>(U, V, nf, pitch, band);
-                };
-                while (k >= 0) {
-                    const Tap t0 = tap_at(k);
-                    if (!t0.mine) break;
-                    if ((k & 3) == 3) {
-                        // a whole group: in the band if its first and last samples are
-                        const Tap t3 = tap_at(k - 3);
-                        if (t3.mine) {
-                            step(t0);
-                            step(tap_at(k - 1));
-                            step(tap_at(k - 2));
-                            step(t3);
-                            *reinterpret_cast<float4 *>(col + att_row(g, k - 3)) = o;
-                            k -= 4;
-                            continue;
-                        }
-                    }
-                    step(t0);
-                    if ((k & 3) == 0) *reinterpret_cast<float4 *>(col + att_row(g, k)) = o;
-                    --k;
+                Comp t = comp_pick(T, j);
+                float4 o = open[0];
+#pragma unroll
+                for (int i = 1; i < kMaxRpt; ++i) {
+                    o.x = (i == j) ? open[i].x : o.x;
+                    o.y = (i == j) ? open[i].y : o.y;
+                    o.z = (i == j) ? open[i].z : o.z;
+                    o.w = (i == j) ? open[i].w : o.w;
                 }
-                T[j] = t;
-                open[j] = o;
-                next[j] = k;
-                if (E && k < 0) E[cand * e_cs + ray] = expf(-g.dx * comp_value(t));
+                for (int kg = (k0 <= k1) ? k1 & ~3 : -1; kg >= 0 && kg + 3 >= k0; kg -= 4) {
+                    const unsigned bits = band_bits(kg, k0, k1);
+                    float m[4], e[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float U, V, fu, fv;
+                        sample_uv(Ub, Vb, tau_of(g, kg + q), cs.x, cs.y, U, V);
+                        const int off = band_off(bt, U, V, nf, pitch, fu, fv);
+                        m[q] = bit_keep(bits, q, lerp2(lds + off, pitch, fu, fv));
+                    }
+#pragma unroll
+                    for (int q = 3; q >= 0; --q) {
+                        const float L = g.dx * (fmaf(0.5f, m[q], t.s) + t.e);
+                        e[q] = fmaxf(expf(-L), kMinNormal);
+                        comp_add(t, m[q]);
+                    }
+                    o.x = (bits & 1u) ? e[0] : o.x;
+                    o.y = (bits & 2u) ? e[1] : o.y;
+                    o.z = (bits & 4u) ? e[2] : o.z;
+                    o.w = (bits & 8u) ? e[3] : o.w;
+                    if (kg >= k0) *reinterpret_cast<float4 *>(col + att_row(g, kg)) = o;
+                }
+                comp_put(T, j, t);
+#pragma unroll
+                for (int i = 0; i < kMaxRpt; ++i) {
+                    open[i].x = (i == j) ? o.x : open[i].x;
+                    open[i].y = (i == j) ? o.y : open[i].y;
+                    open[i].z = (i == j) ? o.z : open[i].z;
+                    open[i].w = (i == j) ? o.w : open[i].w;
+                }
+                if (E && (cs.x >= 0.f ? band.first : band.last)) E[cand * e_cs + ray] = expf(-g.dx * comp_value(t));
             }
         }
     }
@@ -298,6 +311,57 @@ __device__ __forceinline__ float fwd_emit(const FwdArgs &A, size_t cand, int ray
 __device__ __forceinline__ float inv_att(float at) { return rcp_clamped(at); }
 __device__ __forceinline__ float opposed_att(float e_ray, float at) { return e_ray * inv_att(at); }
 
+// One ray's samples in one row band: its projection (c) and, PAIRED, the opposed ray's (c2).
+template <bool PAIRED>
+__device__ __forceinline__ void fwd_band_ray(const DevGeom &g, const Band &band, const float *lds, const float *att,
+                                             unsigned att_bytes, int a, int b, float2 cs, float Ub, float Vb, float e_ray,
+                                             Comp &c, Comp &c2) {
+    const int pitch = g.n + 3;
+    const float nf = (float)g.n;
+    // The ray's samples in this band, KC at a time from the 4-aligned group holding the first, the next
+    // chunk's loads (4 samples per 16-byte load) in flight meanwhile. The owned range is exact and the other
+    // samples' values are masked, so a chunk has no branch and its LDS reads overlap (a test and a branch per
+    // sample: each sample's LDS latency showed). Bound by the vector work, 28 operations a sample and a third
+    // more where a wave's rays lie unevenly in a band. 32 candidates at 256 pixels and 128 angles: 251 us with
+    // the branches, 213 without, 197 with the rays dealt out (band_ray).
+    int k0, k1;
+    band_own_range(g, band, Vb, cs.x, k0, k1);
+    const BandTap bt = band_tap(band, nf, pitch);
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(att, att_bytes);
+    const unsigned roff = 4u * (unsigned)att_base(g, a, b);
+    if (k0 <= k1) {
+        constexpr int KC = PAIRED ? 16 : 8, KG = KC / 4;
+        // groups past the last are read again (in range; masked)
+        float4 cur[KG], nxt[KG];
+#pragma unroll
+        for (int q = 0; q < KG; ++q)
+            cur[q] = buffer_ld4(rs, roff + 4u * att_row(g, min((k0 & ~3) + 4 * q, k1 & ~3)), 0u);
+        float tau = tau_of(g, k0 & ~3);
+        for (int kc = k0 & ~3; kc <= k1; kc += KC) {
+#pragma unroll
+            for (int q = 0; q < KG; ++q)
+                nxt[q] = buffer_ld4(rs, roff + 4u * att_row(g, min(kc + KC + 4 * q, k1 & ~3)), 0u);
+            const unsigned bits = band_bits(kc, k0, k1);
+            float part = 0.f, part2 = 0.f;
+#pragma unroll
+            for (int q = 0; q < KC; ++q) {
+                float U, V, fu, fv;
+                sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
+                const int off = band_off(bt, U, V, nf, pitch, fu, fv);
+                const float at = f4at(cur[q >> 2], q & 3);
+                const float w = bit_keep(bits, q, lerp2(lds + off, pitch, fu, fv));
+                part = fmaf(at, w, part);
+                if constexpr (PAIRED) part2 = fmaf(opposed_att(e_ray, at), w, part2);
+                tau += 1.f;
+            }
+            kahan_add(c, part);
+            if constexpr (PAIRED) kahan_add(c2, part2);
+#pragma unroll
+            for (int q = 0; q < KG; ++q) cur[q] = nxt[q];
+        }
+    }
+}
+
 // PAIRED (opposed-ray pairing, single stage only): each thread's ray (a, b), a < na/2, also gives the
 // projection of ray (a + na/2, nb-1-b) from the same samples and bilinear values.
 template <int MODE, bool SINGLE, bool PAIRED>
@@ -316,13 +380,38 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
 #pragma unroll
     for (int j = 0; j < (PAIRED ? kMaxRpt : 1); ++j) acc2[j] = Comp{0.f, 0.f};
 
-    for (int bi = 0; bi < bands.count; ++bi) {
-        const Band band = bands.band(bi, g.n);
+    if constexpr (!SINGLE) {
+        for (int bi = 0; bi < bands.count; ++bi) {
+            const Band band = bands.band(bi, g.n);
+            __syncthreads();
+            if (A.img_comps == 1)
+                stage_band<1>(img, g.n, band, lds);
+            else
+                stage_band_strided(img, g.n, A.img_comps, band, lds);  // component 0 of an interleaved pair
+            __syncthreads();
+            // one copy of the loop body: unrolled over the rays it would outgrow the registers
+#pragma unroll 1
+            for (int j = 0; j < rpt; ++j) {
+                const int ray = band_ray(chunk, chunks, j);
+                if (ray >= nrays) continue;
+                const int a = ray / g.nb, b = ray - a * g.nb;
+                const float2 cs = g.trig[a];
+                float Ub, Vb;
+                ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
+                Comp c = comp_pick(acc, j), c2{0.f, 0.f};
+                if constexpr (PAIRED) c2 = comp_pick(acc2, j);
+                fwd_band_ray<PAIRED>(g, band, lds, att, (unsigned)(4 * A.att_cs), a, b, cs, Ub, Vb,
+                                     PAIRED ? A.E[cand * A.e_cs + ray] : 0.f, c, c2);
+                comp_put(acc, j, c);
+                if constexpr (PAIRED) comp_put(acc2, j, c2);
+            }
+        }
+    } else {
         __syncthreads();
         if (A.img_comps == 1)
-            stage_band<1>(img, g.n, band, lds);
+            stage_band<1>(img, g.n, bands.band(0, g.n), lds);
         else
-            stage_band_strided(img, g.n, A.img_comps, band, lds);  // component 0 of an interleaved pair
+            stage_band_strided(img, g.n, A.img_comps, bands.band(0, g.n), lds);  // component 0 of an interleaved pair
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < kMaxRpt; ++j) {
@@ -334,7 +423,7 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
             float Ub, Vb;
             ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
             Comp c = acc[j];
-            if constexpr (SINGLE) {
+            {
                 // att is streamed 16 samples ahead of use: the loads of chunk k0 + 16 are in flight
                 // while chunk k0 is computed. The loads go through a buffer resource: a per-lane ray
                 // offset plus a uniform offset of the sample row. Each chunk is summed with FMAs and
@@ -375,45 +464,6 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
                     for (int q = 0; q < KG; ++q) cur[q] = nxt[q];
                 }
                 if constexpr (PAIRED) acc2[j] = c2;
-            } else {
-                // the ray's samples in this band, 16 at a time from the 4-aligned group holding the
-                // first: the chunk's att loads (4 samples per 16-byte load) are issued together, then
-                // used; samples before the range are not the band's and fail the ownership test
-                int k0 = 0, k1 = g.nt - 1;
-                band_k_range(g, band, Vb, cs.x, k0, k1);
-                const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
-                const unsigned roff = 4u * (unsigned)att_base(g, a, b);
-                const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                const int kstart = (k0 <= k1) ? (k0 & ~3) : k1 + 1;
-                const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
-                Comp c2 = PAIRED ? acc2[j] : Comp{0.f, 0.f};
-                for (int kc = kstart; kc <= k1; kc += kBandChunk) {
-                    float4 av[kBandChunk / 4];
-#pragma unroll
-                    for (int q = 0; q < kBandChunk / 4; ++q) {
-                        const int k = kc + 4 * q;
-                        av[q] = (k <= k1) ? buffer_ld4(rs, roff + 4u * att_row(g, k), 0u) : z4;
-                    }
-                    float part = 0.f, part2 = 0.f;
-#pragma unroll
-                    for (int q = 0; q < kBandChunk; ++q) {
-                        const int k = kc + q;
-                        if (k <= k1) {  // a guard, not a break: the loop stays unrolled and av in registers
-                            float U, V;
-                            sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
-                            const Tap t = make_tap<false>(U, V, nf, pitch, band);
-                            if (t.mine) {
-                                const float at = f4at(av[q >> 2], q & 3);
-                                const float w = lerp2(lds + t.off, pitch, t.fu, t.fv);
-                                part = fmaf(at, w, part);
-                                if constexpr (PAIRED) part2 = fmaf(opposed_att(e_ray, at), w, part2);
-                            }
-                        }
-                    }
-                    kahan_add(c, part);
-                    if constexpr (PAIRED) kahan_add(c2, part2);
-                }
-                if constexpr (PAIRED) acc2[j] = c2;
             }
             acc[j] = c;
         }
@@ -425,7 +475,7 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
 #pragma unroll
     for (int j = 0; j < kMaxRpt; ++j) {
         if (j >= rpt) break;
-        const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
+        const int ray = SINGLE ? (chunk * rpt + j) * (int)blockDim.x + (int)threadIdx.x : band_ray(chunk, chunks, j);
         if (ray >= nrays) continue;
         const float t0 = fwd_emit<MODE>(A, cand, ray, fwd_meas<MODE>(A, ray), g.dx * comp_value(acc[j]), zero_proj);
         if constexpr (MODE == FWD_NLL) comp_add(nll, t0);
@@ -586,6 +636,87 @@ __global__ __launch_bounds__(1024) void k_fwd_pair(DevGeom g, Bands bands, int r
 #endif
 
 // ------------------------------------------------------------------ fused reverse sweep
+// One ray's samples in one row band of a reverse step: r_bar of the ray (c) and, PAIRED, of the opposed ray
+// (c2) and the ray's E_bar part (eb); att_bar is read and written. rr, yp (rr2, yp2 opposed): dx r and dx ybar.
+template <bool PAIRED>
+__device__ __forceinline__ void sweep_band_ray(const DevGeom &g, const Band &band, const float2 *lds2, const float *att,
+                                               float *ab, unsigned att_bytes, int accumulate, int a, int b, float2 cs,
+                                               float Ub, float Vb, float e_ray, float rr, float yp, float rr2, float yp2,
+                                               Comp &c, Comp &c2, Comp &eb) {
+    const int pitch = g.n + 3;
+    const float nf = (float)g.n;
+    // The ray's samples in this band as in the projection: exact range, masked values, 8 at a time (the most
+    // whose att and att_bar, this chunk's and the next one's, fit the registers). The ray is this thread's alone
+    // and its bands run in order, so a group's samples owned by another band are written back as loaded.
+    // Bound by the vector work, as the projection; 32 candidates at 256 pixels and 128 angles: 601 us.
+    int k0, k1;
+    band_own_range(g, band, Vb, cs.x, k0, k1);
+    const BandTap btap = band_tap(band, nf, pitch);
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, att_bytes);
+    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, att_bytes);
+    const unsigned roff = 4u * (unsigned)att_base(g, a, b);
+    if (k0 <= k1) {
+        constexpr int KC = 8, KG = KC / 4;
+        const int kl = k1 & ~3;  // the last group
+        float4 av[KG], an[KG], bv[KG], bn[KG];
+#pragma unroll
+        for (int q = 0; q < KG; ++q) {
+            const unsigned o = roff + 4u * att_row(g, min((k0 & ~3) + 4 * q, kl));
+            av[q] = buffer_ld4(ra, o, 0u);
+            bv[q] = buffer_ld4(rb, o, 0u);
+        }
+        float tau = tau_of(g, k0 & ~3);
+        for (int kc = k0 & ~3; kc <= k1; kc += KC) {
+            // (the last chunk reads its last group again before it is stored: not used)
+#pragma unroll
+            for (int q = 0; q < KG; ++q) {
+                const unsigned o = roff + 4u * att_row(g, min(kc + KC + 4 * q, kl));
+                an[q] = buffer_ld4(ra, o, 0u);
+                bn[q] = buffer_ld4(rb, o, 0u);
+            }
+            const unsigned bits = band_bits(kc, k0, k1);
+            const unsigned drop = accumulate ? 0u : bits;  // first write: att_bar's old value goes
+            float part = 0.f, part2 = 0.f, epart = 0.f;
+            float ov[4];
+#pragma unroll
+            for (int q = 0; q < KC; ++q) {
+                float U, V, fu, fv;
+                sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
+                const int off = band_off(btap, U, V, nf, pitch, fu, fv);
+                float2 w = lerp2x2(lds2 + off, pitch, fu, fv);
+                w.x = bit_keep(bits, q, w.x);
+                w.y = bit_keep(bits, q, w.y);
+                const float a0 = f4at(av[q >> 2], q & 3);
+                part = fmaf(a0, w.x, part);
+                float d = fmaf(rr, w.x, yp * w.y);
+                if constexpr (PAIRED) {
+                    const float ri = inv_att(a0);
+                    const float ao = e_ray * ri;
+                    const float cv2 = fmaf(rr2, w.x, yp2 * w.y);
+                    part2 = fmaf(ao, w.x, part2);
+                    epart = fmaf(cv2, ri, epart);
+                    d = fmaf(-ao * ri, cv2, d);
+                }
+                ov[q & 3] = bit_keep(~drop, q, f4at(bv[q >> 2], q & 3)) + bit_keep(bits, q, d);
+                tau += 1.f;
+                if ((q & 3) == 3 && kc + q - 3 <= k1)
+                    buffer_st4(rb, roff + 4u * att_row(g, kc + q - 3), 0u,
+                               make_float4(ov[0], ov[1], ov[2], ov[3]));
+            }
+            kahan_add(c, part);
+            if constexpr (PAIRED) {
+                kahan_add(c2, part2);
+                kahan_add(eb, epart);
+            }
+#pragma unroll
+            for (int q = 0; q < KG; ++q) {
+                av[q] = an[q];
+                bv[q] = bn[q];
+            }
+        }
+    }
+}
+
 // One reverse MLEM step n, per ray i (pair image = (bbar^n, F^{n+1}) staged in LDS):
 //   rbar_i   = dx sum_k att_ik (W bbar^n)_ik                          (adjoint of b^n = A^T r^n)
 //   attbar_ik (+)= dx [ r^n_i (W bbar^n)_ik + ybar^{n+1}_i (W F^{n+1})_ik ]
@@ -608,198 +739,166 @@ __device__ __forceinline__ void k_adj_sweep_body(int bid, float *lds, DevGeom g,
     const float *img = A.pair + cand * A.img_cs;
     const float2 *lds2 = reinterpret_cast<const float2 *>(lds);
 
-    Comp acc[kMaxRpt], acc2[kMaxRpt], ebj[kMaxRpt];  // PAIRED: r_bar of the opposed ray, its E_bar part
+    // row bands: R rays' sums in registers at a time, the image staged again for the next ones
+    constexpr int R = SINGLE ? kMaxRpt : kSweepBandRpt;
+    int j0 = 0;
+    do {
+        Comp acc[R], acc2[R], ebj[R];  // PAIRED: r_bar of the opposed ray, its E_bar part
 #pragma unroll
-    for (int j = 0; j < kMaxRpt; ++j) acc[j] = acc2[j] = ebj[j] = Comp{0.f, 0.f};
+        for (int j = 0; j < R; ++j) acc[j] = acc2[j] = ebj[j] = Comp{0.f, 0.f};
 
-    for (int bi = 0; bi < bands.count; ++bi) {
-        const Band band = bands.band(bi, g.n);
-        __syncthreads();
-        stage_band<2>(img, g.n, band, lds);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kMaxRpt; ++j) {
-            if (j >= rpt) break;
-            const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-            if (ray >= nrays) continue;
-            const int a = ray / g.nb, b = ray - a * g.nb;
-            const float2 cs = g.trig[a];
-            float Ub, Vb;
-            ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
-            const size_t si = cand * A.sino_cs + ray;
-            const float rr = g.dx * A.r[si];
-            const float yp = g.dx * A.ybar_in[si];
-            const size_t col0 = att_base(g, a, b);
-            Comp c = acc[j];
-            if constexpr (SINGLE) {
-                // as in the forward projection: att and att_bar streamed 16 samples ahead through
-                // buffer resources (per-lane ray offset + uniform sample-row offset), chunked
-                // compensated sum, tap index formed in float
-                // samples move in groups of 4 (one 16-byte load or store); padding rows get 0
-                constexpr int KC = 16, KG = KC / 4;
-                const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
-                const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, (unsigned)(4 * A.att_cs));
-                const unsigned roff = 4u * (unsigned)col0;
-                const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                float4 at[KG], an[KG], bt[KG], bn[KG];
-#pragma unroll
-                for (int q = 0; q < KG; ++q) {
-                    const unsigned o = 4u * att_row(g, 4 * q);
-                    at[q] = (4 * q < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
-                    bt[q] = (A.accumulate && 4 * q < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
-                }
-                const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
-                const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
-                const float rr2 = PAIRED ? g.dx * A.r[si2] : 0.f;
-                const float yp2 = PAIRED ? g.dx * A.ybar_in[si2] : 0.f;
-                Comp c2 = acc2[j], eb = ebj[j];
-                float tau = -g.cT;
-                for (int k0 = 0; k0 < g.nt; k0 += KC) {
-#pragma unroll
-                    for (int q = 0; q < KG; ++q) {
-                        const int k = k0 + KC + 4 * q;
-                        const unsigned o = 4u * att_row(g, k);
-                        an[q] = (k < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
-                        bn[q] = (A.accumulate && k < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
-                    }
-                    float part = 0.f, part2 = 0.f, epart = 0.f;
-                    float ov[4];
-#pragma unroll
-                    for (int q = 0; q < KC; ++q) {
-                        const int k = k0 + q;
-                        ov[q & 3] = 0.f;
-                        if (k < g.nt) {
-                            float U, V;
-                            sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
-                            const float Uc = __builtin_amdgcn_fmed3f(U, -1.f, nf);
-                            const float Vc = __builtin_amdgcn_fmed3f(V, -1.f, nf);
-                            const int idx = (int)fmaf(floorf(Vc), (float)pitch, floorf(Uc));
-                            const float2 w = lerp2x2(lds2 + idx + (pitch + 1), pitch, __builtin_amdgcn_fractf(Uc),
-                                                     __builtin_amdgcn_fractf(Vc));
-                            const float a0 = f4at(at[q >> 2], q & 3);
-                            part = fmaf(a0, w.x, part);
-                            const float cv = fmaf(rr, w.x, yp * w.y);
-                            if constexpr (PAIRED) {
-                                const float ri = inv_att(a0);
-                                const float ao = e_ray * ri;
-                                const float cv2 = fmaf(rr2, w.x, yp2 * w.y);
-                                part2 = fmaf(ao, w.x, part2);
-                                epart = fmaf(cv2, ri, epart);
-                                ov[q & 3] = f4at(bt[q >> 2], q & 3) + fmaf(-ao * ri, cv2, cv);
-                            } else {
-                                ov[q & 3] = f4at(bt[q >> 2], q & 3) + cv;
-                            }
-                        }
-                        tau += 1.f;
-                        if ((q & 3) == 3 && k - 3 < g.nt)
-                            buffer_st4_stream(rb, roff, 4u * att_row(g, k - 3), make_float4(ov[0], ov[1], ov[2], ov[3]));
-                    }
-                    kahan_add(c, part);
+        if constexpr (!SINGLE) {
+            for (int bi = 0; bi < bands.count; ++bi) {
+                const Band band = bands.band(bi, g.n);
+                __syncthreads();
+                stage_band<2>(img, g.n, band, lds);
+                __syncthreads();
+#pragma unroll 1
+                for (int j = 0; j < min(rpt - j0, R); ++j) {
+                    const int ray = band_ray(chunk, chunks, j0 + j);
+                    if (ray >= nrays) continue;
+                    const int a = ray / g.nb, b = ray - a * g.nb;
+                    const float2 cs = g.trig[a];
+                    float Ub, Vb;
+                    ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
+                    const size_t si = cand * A.sino_cs + ray;
+                    const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
+                    Comp c = comp_pick(acc, j), c2{0.f, 0.f}, eb{0.f, 0.f};
                     if constexpr (PAIRED) {
-                        kahan_add(c2, part2);
-                        kahan_add(eb, epart);
+                        c2 = comp_pick(acc2, j);
+                        eb = comp_pick(ebj, j);
                     }
+                    sweep_band_ray<PAIRED>(g, band, lds2, att, ab, (unsigned)(4 * A.att_cs), A.accumulate, a, b, cs, Ub, Vb,
+                                           PAIRED ? A.E[cand * A.e_cs + ray] : 0.f, g.dx * A.r[si], g.dx * A.ybar_in[si],
+                                           PAIRED ? g.dx * A.r[si2] : 0.f, PAIRED ? g.dx * A.ybar_in[si2] : 0.f, c, c2, eb);
+                    comp_put(acc, j, c);
+                    if constexpr (PAIRED) {
+                        comp_put(acc2, j, c2);
+                        comp_put(ebj, j, eb);
+                    }
+                }
+            }
+        } else {
+            __syncthreads();
+            stage_band<2>(img, g.n, bands.band(0, g.n), lds);
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (j >= rpt) break;
+                const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
+                if (ray >= nrays) continue;
+                const int a = ray / g.nb, b = ray - a * g.nb;
+                const float2 cs = g.trig[a];
+                float Ub, Vb;
+                ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
+                const size_t si = cand * A.sino_cs + ray;
+                const float rr = g.dx * A.r[si];
+                const float yp = g.dx * A.ybar_in[si];
+                const size_t col0 = att_base(g, a, b);
+                Comp c = acc[j];
+                {
+                    // as in the forward projection: att and att_bar streamed 16 samples ahead through
+                    // buffer resources (per-lane ray offset + uniform sample-row offset), chunked
+                    // compensated sum, tap index formed in float
+                    // samples move in groups of 4 (one 16-byte load or store); padding rows get 0
+                    constexpr int KC = 16, KG = KC / 4;
+                    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
+                    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, (unsigned)(4 * A.att_cs));
+                    const unsigned roff = 4u * (unsigned)col0;
+                    const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+                    float4 at[KG], an[KG], bt[KG], bn[KG];
 #pragma unroll
                     for (int q = 0; q < KG; ++q) {
-                        at[q] = an[q];
-                        bt[q] = bn[q];
+                        const unsigned o = 4u * att_row(g, 4 * q);
+                        at[q] = (4 * q < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
+                        bt[q] = (A.accumulate && 4 * q < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
                     }
-                }
-                if constexpr (PAIRED) {
-                    acc2[j] = c2;
-                    ebj[j] = eb;
-                }
-            } else {
-                // the ray's samples in this band, 16 at a time (loads of att, and of att_bar when
-                // accumulating, issued together per chunk)
-                // from the 4-aligned group holding the first sample, 16-byte loads and stores; samples
-                // before the range fail the ownership test. The ray is this thread's alone and its bands
-                // run in order, so a group's samples owned by another band are written back as loaded.
-                int k0, k1;
-                band_k_range(g, band, Vb, cs.x, k0, k1);
-                const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
-                const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, (unsigned)(4 * A.att_cs));
-                const unsigned roff = 4u * (unsigned)col0;
-                const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                const int kstart = (k0 <= k1) ? (k0 & ~3) : k1 + 1;
-                const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
-                const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
-                const float rr2 = PAIRED ? g.dx * A.r[si2] : 0.f;
-                const float yp2 = PAIRED ? g.dx * A.ybar_in[si2] : 0.f;
-                Comp c2 = acc2[j], eb = ebj[j];
-                for (int kc = kstart; kc <= k1; kc += kBandChunk) {
-                    float4 av[kBandChunk / 4], bv[kBandChunk / 4];
+                    const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
+                    const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
+                    const float rr2 = PAIRED ? g.dx * A.r[si2] : 0.f;
+                    const float yp2 = PAIRED ? g.dx * A.ybar_in[si2] : 0.f;
+                    Comp c2 = acc2[j], eb = ebj[j];
+                    float tau = -g.cT;
+                    for (int k0 = 0; k0 < g.nt; k0 += KC) {
 #pragma unroll
-                    for (int q = 0; q < kBandChunk / 4; ++q) {
-                        const int k = kc + 4 * q;
-                        const unsigned o = roff + 4u * att_row(g, k);
-                        av[q] = (k <= k1) ? buffer_ld4(ra, o, 0u) : z4;
-                        bv[q] = (k <= k1) ? buffer_ld4(rb, o, 0u) : z4;
-                    }
-                    float part = 0.f, part2 = 0.f, epart = 0.f;
-                    float ov[4];
+                        for (int q = 0; q < KG; ++q) {
+                            const int k = k0 + KC + 4 * q;
+                            const unsigned o = 4u * att_row(g, k);
+                            an[q] = (k < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
+                            bn[q] = (A.accumulate && k < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
+                        }
+                        float part = 0.f, part2 = 0.f, epart = 0.f;
+                        float ov[4];
 #pragma unroll
-                    for (int q = 0; q < kBandChunk; ++q) {
-                        const int k = kc + q;
-                        ov[q & 3] = f4at(bv[q >> 2], q & 3);
-                        if (k <= k1) {
-                            float U, V;
-                            sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
-                            const Tap t = make_tap<false>(U, V, nf, pitch, band);
-                            if (t.mine) {
-                                const float2 w = lerp2x2(lds2 + t.off, pitch, t.fu, t.fv);
-                                const float a0 = f4at(av[q >> 2], q & 3);
+                        for (int q = 0; q < KC; ++q) {
+                            const int k = k0 + q;
+                            ov[q & 3] = 0.f;
+                            if (k < g.nt) {
+                                float U, V;
+                                sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
+                                const float Uc = __builtin_amdgcn_fmed3f(U, -1.f, nf);
+                                const float Vc = __builtin_amdgcn_fmed3f(V, -1.f, nf);
+                                const int idx = (int)fmaf(floorf(Vc), (float)pitch, floorf(Uc));
+                                const float2 w = lerp2x2(lds2 + idx + (pitch + 1), pitch, __builtin_amdgcn_fractf(Uc),
+                                                         __builtin_amdgcn_fractf(Vc));
+                                const float a0 = f4at(at[q >> 2], q & 3);
                                 part = fmaf(a0, w.x, part);
                                 const float cv = fmaf(rr, w.x, yp * w.y);
-                                const float base = A.accumulate ? ov[q & 3] : 0.f;
                                 if constexpr (PAIRED) {
                                     const float ri = inv_att(a0);
                                     const float ao = e_ray * ri;
                                     const float cv2 = fmaf(rr2, w.x, yp2 * w.y);
                                     part2 = fmaf(ao, w.x, part2);
                                     epart = fmaf(cv2, ri, epart);
-                                    ov[q & 3] = base + fmaf(-ao * ri, cv2, cv);
+                                    ov[q & 3] = f4at(bt[q >> 2], q & 3) + fmaf(-ao * ri, cv2, cv);
                                 } else {
-                                    ov[q & 3] = base + cv;
+                                    ov[q & 3] = f4at(bt[q >> 2], q & 3) + cv;
                                 }
                             }
+                            tau += 1.f;
+                            if ((q & 3) == 3 && k - 3 < g.nt)
+                                buffer_st4_stream(rb, roff, 4u * att_row(g, k - 3), make_float4(ov[0], ov[1], ov[2], ov[3]));
                         }
-                        if ((q & 3) == 3 && k - 3 <= k1)
-                            buffer_st4(rb, roff + 4u * att_row(g, k - 3), 0u, make_float4(ov[0], ov[1], ov[2], ov[3]));
-                    }
-                    kahan_add(c, part);
-                    if constexpr (PAIRED) {
-                        kahan_add(c2, part2);
-                        kahan_add(eb, epart);
-                    }
-                }
-                if constexpr (PAIRED) {
-                    acc2[j] = c2;
-                    ebj[j] = eb;
-                }
-            }
-            acc[j] = c;
-        }
-    }
+                        kahan_add(c, part);
+                        if constexpr (PAIRED) {
+                            kahan_add(c2, part2);
+                            kahan_add(eb, epart);
+                        }
 #pragma unroll
-    for (int j = 0; j < kMaxRpt; ++j) {
-        if (j >= rpt) break;
-        const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-        if (ray >= nrays) continue;
-        const size_t si = cand * A.sino_cs + ray;
-        const float rbar = g.dx * comp_value(acc[j]);
-        const float yn = A.y[si];
-        A.ybar_out[si] = (yn > 0.f) ? -(rbar * A.r[si]) / yn : 0.f;
-        if constexpr (PAIRED) {
-            const int a = ray / g.nb, b = ray - a * g.nb;
-            const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
-            const float rbar2 = g.dx * comp_value(acc2[j]);
-            const float yn2 = A.y[si2];
-            A.ybar_out[si2] = (yn2 > 0.f) ? -(rbar2 * A.r[si2]) / yn2 : 0.f;
-            float *eo = A.Ebar + cand * A.e_cs + ray;
-            *eo = (A.accumulate ? *eo : 0.f) + comp_value(ebj[j]);
+                        for (int q = 0; q < KG; ++q) {
+                            at[q] = an[q];
+                            bt[q] = bn[q];
+                        }
+                    }
+                    if constexpr (PAIRED) {
+                        acc2[j] = c2;
+                        ebj[j] = eb;
+                    }
+                }
+                acc[j] = c;
+            }
         }
-    }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            if (j0 + j >= rpt) break;
+            const int ray = SINGLE ? (chunk * rpt + j) * (int)blockDim.x + (int)threadIdx.x : band_ray(chunk, chunks, j0 + j);
+            if (ray >= nrays) continue;
+            const size_t si = cand * A.sino_cs + ray;
+            const float rbar = g.dx * comp_value(acc[j]);
+            const float yn = A.y[si];
+            A.ybar_out[si] = (yn > 0.f) ? -(rbar * A.r[si]) / yn : 0.f;
+            if constexpr (PAIRED) {
+                const int a = ray / g.nb, b = ray - a * g.nb;
+                const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
+                const float rbar2 = g.dx * comp_value(acc2[j]);
+                const float yn2 = A.y[si2];
+                A.ybar_out[si2] = (yn2 > 0.f) ? -(rbar2 * A.r[si2]) / yn2 : 0.f;
+                float *eo = A.Ebar + cand * A.e_cs + ray;
+                *eo = (A.accumulate ? *eo : 0.f) + comp_value(ebj[j]);
+            }
+        }
+        j0 += R;
+    } while (!SINGLE && j0 < rpt);
 }
 
 #ifndef BOAC_BODIES_ONLY
@@ -842,7 +941,7 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
 #pragma unroll
         for (int j = 0; j < kMaxRpt; ++j) {
             if (j >= rpt) break;
-            const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
+            const int ray = SINGLE ? (chunk * rpt + j) * (int)blockDim.x + (int)threadIdx.x : band_ray(chunk, chunks, j);
             if (ray >= nrays) continue;
             const int a = ray / g.nb, b = ray - a * g.nb;
             const float2 cs = g.trig[a];
@@ -986,7 +1085,7 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
 #pragma unroll
         for (int j = 0; j < kMaxRpt; ++j) {
             if (j >= rpt) break;
-            const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
+            const int ray = band_ray(chunk, chunks, j);
             if (ray >= nrays) continue;
             const int a = ray / g.nb, b = ray - a * g.nb;
             // 16 samples (4 groups, one 16-byte access each) at a time: the chunk's loads are issued

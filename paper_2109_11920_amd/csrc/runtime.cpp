@@ -550,22 +550,26 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
                 }
         }
     } else {
-        // row bands: 1024-thread workgroups, one resident per CU; the rays per thread that minimise (rounds
-        // over the CUs) x (rays per thread + a workgroup's fixed cost, about 0.6 of a ray pass). Where even one
-        // ray per thread leaves CUs without a workgroup, smaller workgroups.
+        // row bands: one workgroup per CU (the stages hold over half its LDS), and the workgroups run in rounds
+        // over the CUs: as above, fitted to sweeps at 96 to 256 pixels. 32 candidates at 192 pixels and 64
+        // angles, reverse sweep: 142 us for 256 workgroups of 768 threads against 217 for the 384 of 512 that
+        // an earlier rule of powers of two took.
+        const double lat = comps == 2 ? 1.93 : 1.31, valu = comps == 2 ? 0.45 : 0.148;
+        const double stage = comps == 2 ? 0.078 : 0.025, fixed = comps == 2 ? 0.0 : 20.8;
         double best = 0.0;
-        for (int rpt : {4, 2, 1}) {
-            const long wgs = (long)((nrays + 1024 * rpt - 1) / (1024 * rpt)) * C;
-            const double cost = (double)((wgs + ctx->n_cu - 1) / ctx->n_cu) * (rpt + 0.6);
-            if (rpt == 4 || cost < best) {
-                best = cost;
-                rc->rpt = rpt;
+        for (int block = 1024; block >= 256; block -= 64)
+            for (int rpt = 1; rpt <= (comps == 2 ? kSweepBandRpt : 4); ++rpt) {
+                const long wgs = (long)((nrays + block * rpt - 1) / (block * rpt)) * C;
+                const double w = block / 64;
+                const double cost = (double)((wgs + ctx->n_cu - 1) / ctx->n_cu) *
+                                    (rpt * (g.n_samples / 16.0) * (lat + valu * w) +
+                                     stage * bands->count * (double)rc->lds / (64.0 * w) + fixed);
+                if (best == 0.0 || cost < best) {
+                    best = cost;
+                    rc->block = block;
+                    rc->rpt = rpt;
+                }
             }
-        }
-        if ((long)((nrays + 1023) / 1024) * C < ctx->n_cu) {
-            rc->rpt = 1;
-            rc->block = ((long)((nrays + 511) / 512) * C >= ctx->n_cu) ? 512 : 256;
-        }
     }
     // plan cache entry: [threads per workgroup, rays per thread, paired forward projection]
     auto it = ctx->tune.find(shape_key("ray", g, C, comps));
