@@ -15,6 +15,8 @@
 // in device_common.h). The threads of a wave take consecutive bins of one angle, so at each k a
 // wave's loads cover whole 32-byte block rows, and a ray's offset splits into a per-lane bin part and
 // a uniform sample-row part.
+#include <type_traits>
+
 #include "launch.h"
 
 namespace boac {
@@ -31,6 +33,9 @@ __device__ __forceinline__ void ray_block(int bid, int chunks, int C, int &cand,
 
 constexpr int kMaxRpt = 4;
 constexpr int kBandChunk = 16;  // samples per load batch in the row-band paths
+constexpr int kRayChunk = 16;   // samples per load batch of the single-stage paths, in groups of 4
+constexpr int kRayGroups = kRayChunk / 4;
+__device__ __forceinline__ int ray_group(const DevGeom &g, int k0, int q) { return min(k0 + 4 * q, (g.nt - 1) & ~3); }
 
 // A ray's running sum by a run-time index: selects, so that the sums stay in registers.
 template <int N>
@@ -87,23 +92,30 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
             ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
             float *col = out + att_base(g, a, b);
             Comp T{0.f, 0.f};
-            for (int kg = (g.nt - 1) >> 2; kg >= 0; --kg) {
-                float e[4];
+            auto group = [&](auto whole, int kg) {
+                float m[4], e[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (decltype(whole)::value || 4 * kg + q < g.nt) {
+                        float U, V;
+                        sample_uv(Ub, Vb, tau_of(g, 4 * kg + q), cs.x, cs.y, U, V);
+                        m[q] = bilinear_whole(lds, U, V, nf, pitch);
+                    }
+                }
 #pragma unroll
                 for (int q = 3; q >= 0; --q) {
-                    const int k = 4 * kg + q;
                     e[q] = 0.f;
-                    if (k < g.nt) {
-                        float U, V;
-                        sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
-                        const float m = bilinear_whole(lds, U, V, nf, pitch);
-                        const float L = g.dx * (fmaf(0.5f, m, T.s) + T.e);
+                    if (decltype(whole)::value || 4 * kg + q < g.nt) {
+                        const float L = g.dx * (fmaf(0.5f, m[q], T.s) + T.e);
                         e[q] = fmaxf(expf(-L), kMinNormal);
-                        comp_add(T, m);
+                        comp_add(T, m[q]);
                     }
                 }
                 *reinterpret_cast<float4 *>(col + att_row(g, 4 * kg)) = make_float4(e[0], e[1], e[2], e[3]);
-            }
+            };
+            int kg = (g.nt - 1) >> 2;
+            if ((g.nt & 3) != 0) group(std::false_type{}, kg--);
+            for (; kg >= 0; --kg) group(std::true_type{}, kg);
             // opposed-ray pairing: exp(-T) of the whole ray, T = dx sum_k m_k
             if (E) E[cand * e_cs + ray] = expf(-g.dx * comp_value(T));
         }
@@ -232,12 +244,10 @@ __global__ __launch_bounds__(256) void k_att_scan(DevGeom g, Band band, int pass
 #pragma unroll
             for (int q = 3; q >= 0; --q) {
                 const int k = 4 * grp + q;
-                m[q] = 0.f;  // no sample: adds nothing
-                if (live && grp >= 0 && k < g.nt) {
-                    float U, V;
-                    sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
-                    m[q] = bilinear_whole(lds, U, V, nf, pitch);
-                }
+                float U, V;
+                sample_uv(Ub, Vb, tau_of(g, k), cs.x, cs.y, U, V);
+                const float w = bilinear_whole(lds, U, V, nf, pitch);
+                m[q] = (live && grp >= 0 && k < g.nt) ? w : 0.f;  // no sample: adds nothing
             }
             Comp own{0.f, 0.f};
 #pragma unroll
@@ -365,7 +375,8 @@ __device__ __forceinline__ void fwd_band_ray(const DevGeom &g, const Band &band,
 // PAIRED (opposed-ray pairing, single stage only): each thread's ray (a, b), a < na/2, also gives the
 // projection of ray (a + na/2, nb-1-b) from the same samples and bilinear values.
 template <int MODE, bool SINGLE, bool PAIRED>
-__device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevGeom g, const Bands &bands, int rpt, int chunks, int C, FwdArgs A) {
+__device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevGeom g, const Bands &bands, int rpt, int chunks,
+                                           int C, FwdArgs A) {
     int cand, chunk;
     ray_block(bid, chunks, C, cand, chunk);
     const int nrays = g.nah * g.nb;
@@ -373,14 +384,25 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
     const float nf = (float)g.n;
     const float *att = A.att + cand * A.att_cs;
     const float *img = A.img + cand * A.img_cs;
-
-    Comp acc[kMaxRpt], acc2[PAIRED ? kMaxRpt : 1];
-#pragma unroll
-    for (int j = 0; j < kMaxRpt; ++j) acc[j] = Comp{0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < (PAIRED ? kMaxRpt : 1); ++j) acc2[j] = Comp{0.f, 0.f};
+    Comp nll{0.f, 0.f};
+    bool zero_proj = false;
+    auto emit = [&](int ray, const Comp &c, const Comp &c2) {
+        const float t0 = fwd_emit<MODE>(A, cand, ray, fwd_meas<MODE>(A, ray), g.dx * comp_value(c), zero_proj);
+        if constexpr (MODE == FWD_NLL) comp_add(nll, t0);
+        if constexpr (PAIRED) {
+            const int a = ray / g.nb, b = ray - a * g.nb;
+            const int opp = (a + g.nah) * g.nb + (g.nb - 1 - b);
+            const float t1 = fwd_emit<MODE>(A, cand, opp, fwd_meas<MODE>(A, opp), g.dx * comp_value(c2), zero_proj);
+            if constexpr (MODE == FWD_NLL) comp_add(nll, t1);
+        }
+    };
 
     if constexpr (!SINGLE) {
+        Comp acc[kMaxRpt], acc2[PAIRED ? kMaxRpt : 1];
+#pragma unroll
+        for (int j = 0; j < kMaxRpt; ++j) acc[j] = Comp{0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < (PAIRED ? kMaxRpt : 1); ++j) acc2[j] = Comp{0.f, 0.f};
         for (int bi = 0; bi < bands.count; ++bi) {
             const Band band = bands.band(bi, g.n);
             __syncthreads();
@@ -406,6 +428,12 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
                 if constexpr (PAIRED) comp_put(acc2, j, c2);
             }
         }
+#pragma unroll
+        for (int j = 0; j < kMaxRpt; ++j) {
+            if (j >= rpt) break;
+            const int ray = band_ray(chunk, chunks, j);
+            if (ray < nrays) emit(ray, acc[j], acc2[PAIRED ? j : 0]);
+        }
     } else {
         __syncthreads();
         if (A.img_comps == 1)
@@ -413,77 +441,58 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
         else
             stage_band_strided(img, g.n, A.img_comps, bands.band(0, g.n), lds);  // component 0 of an interleaved pair
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kMaxRpt; ++j) {
-            if (j >= rpt) break;
+        // att is streamed 16 samples ahead of use: the loads of chunk k0 + 16 are in flight while chunk k0 is
+        // computed. The loads go through a buffer resource: a per-lane ray offset plus a uniform offset of the
+        // sample row; each 16-byte load brings 4 consecutive samples of the ray (one group of the layout).
+        // Each chunk is summed with FMAs and added to the compensated total. A whole chunk has no branch, so
+        // its samples' LDS reads overlap; the samples past the last whole chunk are tested one by one. (A test
+        // per sample showed every LDS read's latency: projection of candidate pairs, 64 at 128 pixels and 72
+        // angles 42.2 us, 39.5 without; reverse sweep of 64 at 128 angles 136, 128 without.)
+        const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
+#pragma unroll 1
+        for (int j = 0; j < rpt; ++j) {
             const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-            if (ray >= nrays) continue;
+            if (ray >= nrays) break;
             const int a = ray / g.nb, b = ray - a * g.nb;
             const float2 cs = g.trig[a];
             float Ub, Vb;
             ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
-            Comp c = acc[j];
-            {
-                // att is streamed 16 samples ahead of use: the loads of chunk k0 + 16 are in flight
-                // while chunk k0 is computed. The loads go through a buffer resource: a per-lane ray
-                // offset plus a uniform offset of the sample row. Each chunk is summed with FMAs and
-                // added to the compensated total.
-                // Each 16-byte load brings 4 consecutive samples of the ray (one group of the layout).
-                constexpr int KC = 16, KG = KC / 4;
-                const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
-                const unsigned roff = 4u * (unsigned)att_base(g, a, b);
-                const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
-                Comp c2 = PAIRED ? acc2[j] : Comp{0.f, 0.f};
-                float4 cur[KG], nxt[KG];
+            const unsigned roff = 4u * (unsigned)att_base(g, a, b);
+            const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
+            Comp c{0.f, 0.f}, c2{0.f, 0.f};
+            float4 cur[kRayGroups], nxt[kRayGroups];
+            float tau = -g.cT;
+            auto load = [&](int k0, float4 *v) {  // groups past the ray's last: that one again (not used)
 #pragma unroll
-                for (int q = 0; q < KG; ++q) cur[q] = (4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, 4 * q)) : z4;
-                float tau = -g.cT;
-                for (int k0 = 0; k0 < g.nt; k0 += KC) {
+                for (int q = 0; q < kRayGroups; ++q) v[q] = buffer_ld4_stream(rs, roff, 4u * att_row(g, ray_group(g, k0, q)));
+            };
+            auto sum = [&](auto whole, int k0) {
+                float part = 0.f, part2 = 0.f;
 #pragma unroll
-                    for (int q = 0; q < KG; ++q) {
-                        const int k = k0 + KC + 4 * q;
-                        nxt[q] = (k < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, k)) : z4;
+                for (int q = 0; q < kRayChunk; ++q) {
+                    if (decltype(whole)::value || k0 + q < g.nt) {
+                        float U, V;
+                        sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
+                        const float at = f4at(cur[q >> 2], q & 3);
+                        const float w = bilinear_whole(lds, U, V, nf, pitch);
+                        part = fmaf(at, w, part);
+                        if constexpr (PAIRED) part2 = fmaf(opposed_att(e_ray, at), w, part2);
                     }
-                    float part = 0.f, part2 = 0.f;
-#pragma unroll
-                    for (int q = 0; q < KC; ++q) {
-                        if (k0 + q < g.nt) {
-                            float U, V;
-                            sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
-                            const float at = f4at(cur[q >> 2], q & 3);
-                            const float w = bilinear_whole(lds, U, V, nf, pitch);
-                            part = fmaf(at, w, part);
-                            if constexpr (PAIRED) part2 = fmaf(opposed_att(e_ray, at), w, part2);
-                        }
-                        tau += 1.f;
-                    }
-                    kahan_add(c, part);
-                    if constexpr (PAIRED) kahan_add(c2, part2);
-#pragma unroll
-                    for (int q = 0; q < KG; ++q) cur[q] = nxt[q];
+                    tau += 1.f;
                 }
-                if constexpr (PAIRED) acc2[j] = c2;
-            }
-            acc[j] = c;
-        }
-    }
-
-    // epilogues
-    Comp nll{0.f, 0.f};
-    bool zero_proj = false;
+                kahan_add(c, part);
+                if constexpr (PAIRED) kahan_add(c2, part2);
+            };
+            load(0, cur);
+            int k0 = 0;
+            for (; k0 + kRayChunk <= g.nt; k0 += kRayChunk) {
+                if (k0 + kRayChunk < g.nt) load(k0 + kRayChunk, nxt);
+                sum(std::true_type{}, k0);
 #pragma unroll
-    for (int j = 0; j < kMaxRpt; ++j) {
-        if (j >= rpt) break;
-        const int ray = SINGLE ? (chunk * rpt + j) * (int)blockDim.x + (int)threadIdx.x : band_ray(chunk, chunks, j);
-        if (ray >= nrays) continue;
-        const float t0 = fwd_emit<MODE>(A, cand, ray, fwd_meas<MODE>(A, ray), g.dx * comp_value(acc[j]), zero_proj);
-        if constexpr (MODE == FWD_NLL) comp_add(nll, t0);
-        if constexpr (PAIRED) {
-            const int a = ray / g.nb, b = ray - a * g.nb;
-            const int opp = (a + g.nah) * g.nb + (g.nb - 1 - b);
-            const float t1 = fwd_emit<MODE>(A, cand, opp, fwd_meas<MODE>(A, opp), g.dx * comp_value(acc2[j]), zero_proj);
-            if constexpr (MODE == FWD_NLL) comp_add(nll, t1);
+                for (int q = 0; q < kRayGroups; ++q) cur[q] = nxt[q];
+            }
+            if (k0 < g.nt) sum(std::false_type{}, k0);
+            emit(ray, c, c2);
         }
     }
     if constexpr (MODE == FWD_NLL) {
@@ -524,14 +533,12 @@ __device__ __forceinline__ void k_fwd_pair_body(int bid, float *lds, float *red,
     const __amdgpu_buffer_rsrc_t r0 = buffer_rsrc(A.att + c0 * A.att_cs, (unsigned)(4 * A.att_cs));
     const __amdgpu_buffer_rsrc_t r1 = buffer_rsrc(A.att + c1 * A.att_cs, (unsigned)(4 * A.att_cs));
 
-    Comp acc0[kMaxRpt], acc1[kMaxRpt], opp0[kMaxRpt], opp1[kMaxRpt];
-#pragma unroll
-    for (int j = 0; j < kMaxRpt; ++j) acc0[j] = acc1[j] = opp0[j] = opp1[j] = Comp{0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < kMaxRpt; ++j) {
-        if (j >= rpt) break;
+    Comp nll[2] = {{0.f, 0.f}, {0.f, 0.f}};
+    bool zero_proj[2] = {false, false};
+#pragma unroll 1
+    for (int j = 0; j < rpt; ++j) {
         const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-        if (ray >= nrays) continue;
+        if (ray >= nrays) break;
         const int a = ray / g.nb, b = ray - a * g.nb;
         const float2 cs = g.trig[a];
         float Ub, Vb;
@@ -539,27 +546,25 @@ __device__ __forceinline__ void k_fwd_pair_body(int bid, float *lds, float *red,
         const unsigned roff = 4u * (unsigned)att_base(g, a, b);
         const float e0 = PAIRED ? A.E[c0 * A.e_cs + ray] : 0.f;
         const float e1 = PAIRED ? A.E[c1 * A.e_cs + ray] : 0.f;
-        constexpr int KC = 16, KG = KC / 4;
-        const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 u0[KG], u1[KG], n0[KG], n1[KG];
-#pragma unroll
-        for (int q = 0; q < KG; ++q) {
-            u0[q] = (4 * q < g.nt) ? buffer_ld4_stream(r0, roff, 4u * att_row(g, 4 * q)) : z4;
-            u1[q] = (4 * q < g.nt) ? buffer_ld4_stream(r1, roff, 4u * att_row(g, 4 * q)) : z4;
-        }
-        Comp s0 = acc0[j], s1 = acc1[j], t0 = opp0[j], t1 = opp1[j];
+        // 8 samples ahead (16 would not leave the registers for overlapping LDS reads): the first half of a
+        // chunk in x, the second in y
+        constexpr int KH = kRayChunk / 2, HG = KH / 4;
+        float4 x0[HG], x1[HG], y0[HG], y1[HG];
+        Comp s0{0.f, 0.f}, s1{0.f, 0.f}, t0{0.f, 0.f}, t1{0.f, 0.f};
         float tau = -g.cT;
-        for (int k0 = 0; k0 < g.nt; k0 += KC) {
+        auto load = [&](int k0, float4 *v0, float4 *v1) {
 #pragma unroll
-            for (int q = 0; q < KG; ++q) {
-                const int k = k0 + KC + 4 * q;
-                n0[q] = (k < g.nt) ? buffer_ld4_stream(r0, roff, 4u * att_row(g, k)) : z4;
-                n1[q] = (k < g.nt) ? buffer_ld4_stream(r1, roff, 4u * att_row(g, k)) : z4;
+            for (int q = 0; q < HG; ++q) {
+                const unsigned o = 4u * att_row(g, ray_group(g, k0, q));
+                v0[q] = buffer_ld4_stream(r0, roff, o);
+                v1[q] = buffer_ld4_stream(r1, roff, o);
             }
-            float p0 = 0.f, p1 = 0.f, o0 = 0.f, o1 = 0.f;
+        };
+        float p0, p1, o0, o1;
+        auto sum = [&](auto whole, int k0, const float4 *v0, const float4 *v1) {
 #pragma unroll
-            for (int q = 0; q < KC; ++q) {
-                if (k0 + q < g.nt) {
+            for (int q = 0; q < KH; ++q) {
+                if (decltype(whole)::value || k0 + q < g.nt) {
                     float U, V;
                     sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
                     const float Uc = __builtin_amdgcn_fmed3f(U, -1.f, nf);
@@ -567,7 +572,7 @@ __device__ __forceinline__ void k_fwd_pair_body(int bid, float *lds, float *red,
                     const int idx = (int)fmaf(floorf(Vc), (float)pitch, floorf(Uc));
                     const float2 w = lerp2x2(lds2 + idx + (pitch + 1), pitch, __builtin_amdgcn_fractf(Uc),
                                              __builtin_amdgcn_fractf(Vc));
-                    const float a0 = f4at(u0[q >> 2], q & 3), a1 = f4at(u1[q >> 2], q & 3);
+                    const float a0 = f4at(v0[q >> 2], q & 3), a1 = f4at(v1[q >> 2], q & 3);
                     p0 = fmaf(a0, w.x, p0);
                     p1 = fmaf(a1, w.y, p1);
                     if constexpr (PAIRED) {
@@ -576,51 +581,61 @@ __device__ __forceinline__ void k_fwd_pair_body(int bid, float *lds, float *red,
                     }
                 }
                 tau += 1.f;
+                if ((q & 3) == 3) {
+                    // the sums so far are due here: otherwise every sample's LDS reads of the half are issued
+                    // first, and what they return outgrows the registers
+                    if constexpr (PAIRED) asm volatile("" : "+v"(o0), "+v"(o1));
+                    asm volatile("" : "+v"(p0), "+v"(p1)::"memory");
+                }
             }
+        };
+        auto chunk_end = [&]() {
             kahan_add(s0, p0);
             kahan_add(s1, p1);
             if constexpr (PAIRED) {
                 kahan_add(t0, o0);
                 kahan_add(t1, o1);
             }
-#pragma unroll
-            for (int q = 0; q < KG; ++q) {
-                u0[q] = n0[q];
-                u1[q] = n1[q];
-            }
+        };
+        load(0, x0, x1);
+        int k0 = 0;
+        for (; k0 + kRayChunk <= g.nt; k0 += kRayChunk) {
+            p0 = p1 = o0 = o1 = 0.f;
+            load(k0 + KH, y0, y1);
+            sum(std::true_type{}, k0, x0, x1);
+            if (k0 + kRayChunk < g.nt) load(k0 + kRayChunk, x0, x1);
+            sum(std::true_type{}, k0 + KH, y0, y1);
+            chunk_end();
         }
-        acc0[j] = s0;
-        acc1[j] = s1;
-        opp0[j] = t0;
-        opp1[j] = t1;
-    }
-
-    // epilogues, candidate by candidate
+        if (k0 < g.nt) {
+            p0 = p1 = o0 = o1 = 0.f;
+            load(k0 + KH, y0, y1);
+            sum(std::false_type{}, k0, x0, x1);
+            sum(std::false_type{}, k0 + KH, y0, y1);
+            chunk_end();
+        }
+        // epilogues, candidate by candidate
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int cand = h ? c1 : c0;
-        const bool live = (h == 0) || two;
-        Comp nll{0.f, 0.f};
-        bool zero_proj = false;
-#pragma unroll
-        for (int j = 0; j < kMaxRpt; ++j) {
-            if (j >= rpt) break;
-            const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-            if (ray >= nrays || !live) continue;
-            const float t0 = fwd_emit<MODE>(A, cand, ray, fwd_meas<MODE>(A, ray), g.dx * comp_value(h ? acc1[j] : acc0[j]),
-                                            zero_proj);
-            if constexpr (MODE == FWD_NLL) comp_add(nll, t0);
+        for (int h = 0; h < 2; ++h) {
+            if (h == 1 && !two) break;
+            const int cand = h ? c1 : c0;
+            const float z0 = fwd_emit<MODE>(A, cand, ray, fwd_meas<MODE>(A, ray), g.dx * comp_value(h ? s1 : s0), zero_proj[h]);
+            if constexpr (MODE == FWD_NLL) comp_add(nll[h], z0);
             if constexpr (PAIRED) {
-                const int a = ray / g.nb, b = ray - a * g.nb;
                 const int opp = (a + g.nah) * g.nb + (g.nb - 1 - b);
-                const float t1 = fwd_emit<MODE>(A, cand, opp, fwd_meas<MODE>(A, opp),
-                                                g.dx * comp_value(h ? opp1[j] : opp0[j]), zero_proj);
-                if constexpr (MODE == FWD_NLL) comp_add(nll, t1);
+                const float z1 =
+                    fwd_emit<MODE>(A, cand, opp, fwd_meas<MODE>(A, opp), g.dx * comp_value(h ? t1 : t0), zero_proj[h]);
+                if constexpr (MODE == FWD_NLL) comp_add(nll[h], z1);
             }
         }
-        if constexpr (MODE == FWD_NLL) {
-            if (zero_proj && A.status) atomicOr(A.status + cand, 1u);
-            const Comp r = block_reduce(nll, red);
+    }
+    if constexpr (MODE == FWD_NLL) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int cand = h ? c1 : c0;
+            const bool live = (h == 0) || two;
+            if (zero_proj[h] && A.status) atomicOr(A.status + cand, 1u);
+            const Comp r = block_reduce(nll[h], red);
             if (threadIdx.x == 0 && live) A.partial[(size_t)cand * chunks + chunk] = make_float2(r.s, r.e);
         }
     }
@@ -639,8 +654,8 @@ __global__ __launch_bounds__(1024) void k_fwd_pair(DevGeom g, Bands bands, int r
 // One ray's samples in one row band of a reverse step: r_bar of the ray (c) and, PAIRED, of the opposed ray
 // (c2) and the ray's E_bar part (eb); att_bar is read and written. rr, yp (rr2, yp2 opposed): dx r and dx ybar.
 template <bool PAIRED>
-__device__ __forceinline__ void sweep_band_ray(const DevGeom &g, const Band &band, const float2 *lds2, const float *att,
-                                               float *ab, unsigned att_bytes, int accumulate, int a, int b, float2 cs,
+__device__ __forceinline__ void sweep_band_ray(const DevGeom &g, const Band &band, const float2 *lds2,
+                                               __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, int accumulate, int a, int b, float2 cs,
                                                float Ub, float Vb, float e_ray, float rr, float yp, float rr2, float yp2,
                                                Comp &c, Comp &c2, Comp &eb) {
     const int pitch = g.n + 3;
@@ -652,8 +667,6 @@ __device__ __forceinline__ void sweep_band_ray(const DevGeom &g, const Band &ban
     int k0, k1;
     band_own_range(g, band, Vb, cs.x, k0, k1);
     const BandTap btap = band_tap(band, nf, pitch);
-    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, att_bytes);
-    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, att_bytes);
     const unsigned roff = 4u * (unsigned)att_base(g, a, b);
     if (k0 <= k1) {
         constexpr int KC = 8, KG = KC / 4;
@@ -739,15 +752,30 @@ __device__ __forceinline__ void k_adj_sweep_body(int bid, float *lds, DevGeom g,
     const float *img = A.pair + cand * A.img_cs;
     const float2 *lds2 = reinterpret_cast<const float2 *>(lds);
 
-    // row bands: R rays' sums in registers at a time, the image staged again for the next ones
-    constexpr int R = SINGLE ? kMaxRpt : kSweepBandRpt;
-    int j0 = 0;
-    do {
-        Comp acc[R], acc2[R], ebj[R];  // PAIRED: r_bar of the opposed ray, its E_bar part
+    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
+    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, (unsigned)(4 * A.att_cs));
+    auto emit = [&](int ray, const Comp &c, const Comp &c2, const Comp &eb) {
+        const size_t si = cand * A.sino_cs + ray;
+        const float rbar = g.dx * comp_value(c);
+        const float yn = A.y[si];
+        A.ybar_out[si] = (yn > 0.f) ? -(rbar * A.r[si]) / yn : 0.f;
+        if constexpr (PAIRED) {
+            const int a = ray / g.nb, b = ray - a * g.nb;
+            const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
+            const float rbar2 = g.dx * comp_value(c2);
+            const float yn2 = A.y[si2];
+            A.ybar_out[si2] = (yn2 > 0.f) ? -(rbar2 * A.r[si2]) / yn2 : 0.f;
+            float *eo = A.Ebar + cand * A.e_cs + ray;
+            *eo = (A.accumulate ? *eo : 0.f) + comp_value(eb);
+        }
+    };
+    if constexpr (!SINGLE) {
+        // R rays' sums in registers at a time, the image staged again for the next ones
+        constexpr int R = kSweepBandRpt;
+        for (int j0 = 0; j0 < rpt; j0 += R) {
+            Comp acc[R], acc2[R], ebj[R];  // PAIRED: r_bar of the opposed ray, its E_bar part
 #pragma unroll
-        for (int j = 0; j < R; ++j) acc[j] = acc2[j] = ebj[j] = Comp{0.f, 0.f};
-
-        if constexpr (!SINGLE) {
+            for (int j = 0; j < R; ++j) acc[j] = acc2[j] = ebj[j] = Comp{0.f, 0.f};
             for (int bi = 0; bi < bands.count; ++bi) {
                 const Band band = bands.band(bi, g.n);
                 __syncthreads();
@@ -768,9 +796,10 @@ __device__ __forceinline__ void k_adj_sweep_body(int bid, float *lds, DevGeom g,
                         c2 = comp_pick(acc2, j);
                         eb = comp_pick(ebj, j);
                     }
-                    sweep_band_ray<PAIRED>(g, band, lds2, att, ab, (unsigned)(4 * A.att_cs), A.accumulate, a, b, cs, Ub, Vb,
+                    sweep_band_ray<PAIRED>(g, band, lds2, ra, rb, A.accumulate, a, b, cs, Ub, Vb,
                                            PAIRED ? A.E[cand * A.e_cs + ray] : 0.f, g.dx * A.r[si], g.dx * A.ybar_in[si],
-                                           PAIRED ? g.dx * A.r[si2] : 0.f, PAIRED ? g.dx * A.ybar_in[si2] : 0.f, c, c2, eb);
+                                           PAIRED ? g.dx * A.r[si2] : 0.f, PAIRED ? g.dx * A.ybar_in[si2] : 0.f, c, c2,
+                                           eb);
                     comp_put(acc, j, c);
                     if constexpr (PAIRED) {
                         comp_put(acc2, j, c2);
@@ -778,127 +807,113 @@ __device__ __forceinline__ void k_adj_sweep_body(int bid, float *lds, DevGeom g,
                     }
                 }
             }
-        } else {
-            __syncthreads();
-            stage_band<2>(img, g.n, bands.band(0, g.n), lds);
-            __syncthreads();
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                if (j >= rpt) break;
-                const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
-                if (ray >= nrays) continue;
-                const int a = ray / g.nb, b = ray - a * g.nb;
-                const float2 cs = g.trig[a];
-                float Ub, Vb;
-                ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
-                const size_t si = cand * A.sino_cs + ray;
-                const float rr = g.dx * A.r[si];
-                const float yp = g.dx * A.ybar_in[si];
-                const size_t col0 = att_base(g, a, b);
-                Comp c = acc[j];
-                {
-                    // as in the forward projection: att and att_bar streamed 16 samples ahead through
-                    // buffer resources (per-lane ray offset + uniform sample-row offset), chunked
-                    // compensated sum, tap index formed in float
-                    // samples move in groups of 4 (one 16-byte load or store); padding rows get 0
-                    constexpr int KC = 16, KG = KC / 4;
-                    const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
-                    const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, (unsigned)(4 * A.att_cs));
-                    const unsigned roff = 4u * (unsigned)col0;
-                    const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                    float4 at[KG], an[KG], bt[KG], bn[KG];
-#pragma unroll
-                    for (int q = 0; q < KG; ++q) {
-                        const unsigned o = 4u * att_row(g, 4 * q);
-                        at[q] = (4 * q < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
-                        bt[q] = (A.accumulate && 4 * q < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
-                    }
-                    const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
-                    const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
-                    const float rr2 = PAIRED ? g.dx * A.r[si2] : 0.f;
-                    const float yp2 = PAIRED ? g.dx * A.ybar_in[si2] : 0.f;
-                    Comp c2 = acc2[j], eb = ebj[j];
-                    float tau = -g.cT;
-                    for (int k0 = 0; k0 < g.nt; k0 += KC) {
-#pragma unroll
-                        for (int q = 0; q < KG; ++q) {
-                            const int k = k0 + KC + 4 * q;
-                            const unsigned o = 4u * att_row(g, k);
-                            an[q] = (k < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
-                            bn[q] = (A.accumulate && k < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
-                        }
-                        float part = 0.f, part2 = 0.f, epart = 0.f;
-                        float ov[4];
-#pragma unroll
-                        for (int q = 0; q < KC; ++q) {
-                            const int k = k0 + q;
-                            ov[q & 3] = 0.f;
-                            if (k < g.nt) {
-                                float U, V;
-                                sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
-                                const float Uc = __builtin_amdgcn_fmed3f(U, -1.f, nf);
-                                const float Vc = __builtin_amdgcn_fmed3f(V, -1.f, nf);
-                                const int idx = (int)fmaf(floorf(Vc), (float)pitch, floorf(Uc));
-                                const float2 w = lerp2x2(lds2 + idx + (pitch + 1), pitch, __builtin_amdgcn_fractf(Uc),
-                                                         __builtin_amdgcn_fractf(Vc));
-                                const float a0 = f4at(at[q >> 2], q & 3);
-                                part = fmaf(a0, w.x, part);
-                                const float cv = fmaf(rr, w.x, yp * w.y);
-                                if constexpr (PAIRED) {
-                                    const float ri = inv_att(a0);
-                                    const float ao = e_ray * ri;
-                                    const float cv2 = fmaf(rr2, w.x, yp2 * w.y);
-                                    part2 = fmaf(ao, w.x, part2);
-                                    epart = fmaf(cv2, ri, epart);
-                                    ov[q & 3] = f4at(bt[q >> 2], q & 3) + fmaf(-ao * ri, cv2, cv);
-                                } else {
-                                    ov[q & 3] = f4at(bt[q >> 2], q & 3) + cv;
-                                }
-                            }
-                            tau += 1.f;
-                            if ((q & 3) == 3 && k - 3 < g.nt)
-                                buffer_st4_stream(rb, roff, 4u * att_row(g, k - 3), make_float4(ov[0], ov[1], ov[2], ov[3]));
-                        }
-                        kahan_add(c, part);
-                        if constexpr (PAIRED) {
-                            kahan_add(c2, part2);
-                            kahan_add(eb, epart);
-                        }
-#pragma unroll
-                        for (int q = 0; q < KG; ++q) {
-                            at[q] = an[q];
-                            bt[q] = bn[q];
-                        }
-                    }
-                    if constexpr (PAIRED) {
-                        acc2[j] = c2;
-                        ebj[j] = eb;
-                    }
-                }
-                acc[j] = c;
+                if (j0 + j >= rpt) break;
+                const int ray = band_ray(chunk, chunks, j0 + j);
+                if (ray < nrays) emit(ray, acc[j], acc2[j], ebj[j]);
             }
         }
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            if (j0 + j >= rpt) break;
-            const int ray = SINGLE ? (chunk * rpt + j) * (int)blockDim.x + (int)threadIdx.x : band_ray(chunk, chunks, j0 + j);
-            if (ray >= nrays) continue;
+    } else {
+        __syncthreads();
+        stage_band<2>(img, g.n, bands.band(0, g.n), lds);
+        __syncthreads();
+        // as in the forward projection: att and att_bar streamed 8 samples ahead through buffer resources,
+        // chunked compensated sums, no branch in a whole chunk; padding rows of att_bar get 0
+#pragma unroll 1
+        for (int j = 0; j < rpt; ++j) {
+            const int ray = (chunk * rpt + j) * blockDim.x + threadIdx.x;
+            if (ray >= nrays) break;
+            const int a = ray / g.nb, b = ray - a * g.nb;
+            const float2 cs = g.trig[a];
+            float Ub, Vb;
+            ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
             const size_t si = cand * A.sino_cs + ray;
-            const float rbar = g.dx * comp_value(acc[j]);
-            const float yn = A.y[si];
-            A.ybar_out[si] = (yn > 0.f) ? -(rbar * A.r[si]) / yn : 0.f;
-            if constexpr (PAIRED) {
-                const int a = ray / g.nb, b = ray - a * g.nb;
-                const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
-                const float rbar2 = g.dx * comp_value(acc2[j]);
-                const float yn2 = A.y[si2];
-                A.ybar_out[si2] = (yn2 > 0.f) ? -(rbar2 * A.r[si2]) / yn2 : 0.f;
-                float *eo = A.Ebar + cand * A.e_cs + ray;
-                *eo = (A.accumulate ? *eo : 0.f) + comp_value(ebj[j]);
+            const size_t si2 = cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b));
+            const float rr = g.dx * A.r[si], yp = g.dx * A.ybar_in[si];
+            const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
+            const float rr2 = PAIRED ? g.dx * A.r[si2] : 0.f;
+            const float yp2 = PAIRED ? g.dx * A.ybar_in[si2] : 0.f;
+            const unsigned roff = 4u * (unsigned)att_base(g, a, b);
+            const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
+            constexpr int KH = kRayChunk / 2, HG = KH / 4;
+            float4 xa[HG], xb[HG], ya[HG], yb[HG];  // the halves of a chunk
+            Comp c{0.f, 0.f}, c2{0.f, 0.f}, eb{0.f, 0.f};
+            float tau = -g.cT;
+            auto load = [&](int k0, float4 *va, float4 *vb) {
+#pragma unroll
+                for (int q = 0; q < HG; ++q) va[q] = buffer_ld4_stream(ra, roff, 4u * att_row(g, ray_group(g, k0, q)));
+                if (A.accumulate) {
+#pragma unroll
+                    for (int q = 0; q < HG; ++q)
+                        vb[q] = buffer_ld4_stream(rb, roff, 4u * att_row(g, ray_group(g, k0, q)));
+                } else {
+#pragma unroll
+                    for (int q = 0; q < HG; ++q) vb[q] = z4;
+                }
+            };
+            float part, part2, epart;
+            auto step = [&](auto whole, int k0, const float4 *at, const float4 *bt) {
+                constexpr bool kWhole = decltype(whole)::value;
+                float ov[4];
+#pragma unroll
+                for (int q = 0; q < KH; ++q) {
+                    const int k = k0 + q;
+                    ov[q & 3] = 0.f;
+                    if (kWhole || k < g.nt) {
+                        float U, V;
+                        sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
+                        const float Uc = __builtin_amdgcn_fmed3f(U, -1.f, nf);
+                        const float Vc = __builtin_amdgcn_fmed3f(V, -1.f, nf);
+                        const int idx = (int)fmaf(floorf(Vc), (float)pitch, floorf(Uc));
+                        const float2 w = lerp2x2(lds2 + idx + (pitch + 1), pitch, __builtin_amdgcn_fractf(Uc),
+                                                 __builtin_amdgcn_fractf(Vc));
+                        const float a0 = f4at(at[q >> 2], q & 3);
+                        part = fmaf(a0, w.x, part);
+                        const float cv = fmaf(rr, w.x, yp * w.y);
+                        if constexpr (PAIRED) {
+                            const float ri = inv_att(a0);
+                            const float ao = e_ray * ri;
+                            const float cv2 = fmaf(rr2, w.x, yp2 * w.y);
+                            part2 = fmaf(ao, w.x, part2);
+                            epart = fmaf(cv2, ri, epart);
+                            ov[q & 3] = f4at(bt[q >> 2], q & 3) + fmaf(-ao * ri, cv2, cv);
+                        } else {
+                            ov[q & 3] = f4at(bt[q >> 2], q & 3) + cv;
+                        }
+                    }
+                    tau += 1.f;
+                    if ((q & 3) == 3 && (kWhole || k - 3 < g.nt))
+                        buffer_st4_stream(rb, roff, 4u * att_row(g, k - 3), make_float4(ov[0], ov[1], ov[2], ov[3]));
+                }
+            };
+            auto chunk_end = [&]() {
+                kahan_add(c, part);
+                if constexpr (PAIRED) {
+                    kahan_add(c2, part2);
+                    kahan_add(eb, epart);
+                }
+            };
+            load(0, xa, xb);
+            int k0 = 0;
+            for (; k0 + kRayChunk <= g.nt; k0 += kRayChunk) {
+                part = part2 = epart = 0.f;
+                load(k0 + KH, ya, yb);
+                step(std::true_type{}, k0, xa, xb);
+                if (k0 + kRayChunk < g.nt) load(k0 + kRayChunk, xa, xb);
+                step(std::true_type{}, k0 + KH, ya, yb);
+                chunk_end();
             }
+            if (k0 < g.nt) {
+                part = part2 = epart = 0.f;
+                load(k0 + KH, ya, yb);
+                step(std::false_type{}, k0, xa, xb);
+                step(std::false_type{}, k0 + KH, ya, yb);
+                chunk_end();
+            }
+            emit(ray, c, c2, eb);
         }
-        j0 += R;
-    } while (!SINGLE && j0 < rpt);
+    }
 }
 
 #ifndef BOAC_BODIES_ONLY
@@ -938,9 +953,8 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
         __syncthreads();
         stage_band<2>(img, g.n, band, lds);
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kMaxRpt; ++j) {
-            if (j >= rpt) break;
+#pragma unroll 1
+        for (int j = 0; j < rpt; ++j) {
             const int ray = SINGLE ? (chunk * rpt + j) * (int)blockDim.x + (int)threadIdx.x : band_ray(chunk, chunks, j);
             if (ray >= nrays) continue;
             const int a = ray / g.nb, b = ray - a * g.nb;
@@ -951,46 +965,42 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
             const size_t off = att_base(g, a, b);
             if constexpr (SINGLE) {
                 // samples move in groups of 4 (one 16-byte load or store); padding rows get 0
-                constexpr int KC = 16, KG = KC / 4;
+                // 8 ahead, and no test per sample in a whole chunk, as in the sweep
                 const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(att, (unsigned)(4 * A.att_cs));
                 const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(ab, (unsigned)(4 * A.att_cs));
                 const unsigned roff = 4u * (unsigned)off;
                 const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                float4 at[KG], an[KG], bt[KG], bn[KG];
-#pragma unroll
-                for (int q = 0; q < KG; ++q) {
-                    const unsigned o = 4u * att_row(g, 4 * q);
-                    at[q] = (4 * q < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
-                    bt[q] = (A.accumulate && 4 * q < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
-                }
+                constexpr int KH = kRayChunk / 2, HG = KH / 4;
+                float4 xa[HG], xb[HG], ya[HG], yb[HG];
                 Comp P{0.f, 0.f};
                 const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
                 const float rho2 =
                     PAIRED ? A.rho[cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b))] : 0.f;
                 Comp eb{0.f, 0.f};
-                float tau = -g.cT;
-                for (int k0 = 0; k0 < g.nt; k0 += KC) {
+                float tau = -g.cT, epart;
+                auto load = [&](int k0, float4 *va, float4 *vb) {
 #pragma unroll
-                    for (int q = 0; q < KG; ++q) {
-                        const int k = k0 + KC + 4 * q;
-                        const unsigned o = 4u * att_row(g, k);
-                        an[q] = (k < g.nt) ? buffer_ld4_stream(ra, roff, o) : z4;
-                        bn[q] = (A.accumulate && k < g.nt) ? buffer_ld4_stream(rb, roff, o) : z4;
+                    for (int q = 0; q < HG; ++q) {
+                        const unsigned o = 4u * att_row(g, ray_group(g, k0, q));
+                        va[q] = buffer_ld4_stream(ra, roff, o);
+                        vb[q] = A.accumulate ? buffer_ld4_stream(rb, roff, o) : z4;
                     }
+                };
+                auto step = [&](auto whole, int k0, const float4 *at, const float4 *bt) {
+                    constexpr bool kWhole = decltype(whole)::value;
                     float ov[4];
-                    float epart = 0.f;
 #pragma unroll
-                    for (int q = 0; q < KC; ++q) {
+                    for (int q = 0; q < KH; ++q) {
                         const int k = k0 + q;
                         ov[q & 3] = 0.f;
-                        if (k < g.nt) {
+                        if (kWhole || k < g.nt) {
                             float U, V;
                             sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
                             const float Uc = __builtin_amdgcn_fmed3f(U, -1.f, nf);
                             const float Vc = __builtin_amdgcn_fmed3f(V, -1.f, nf);
-                            const int l0 = __float2int_rd(Uc), i0 = __float2int_rd(Vc);
-                            const float2 w = lerp2x2(lds2 + (i0 + 1) * pitch + (l0 + 1), pitch,
-                                                     __builtin_amdgcn_fractf(Uc), __builtin_amdgcn_fractf(Vc));
+                            const int idx = (int)fmaf(floorf(Vc), (float)pitch, floorf(Uc));
+                            const float2 w = lerp2x2(lds2 + idx + (pitch + 1), pitch, __builtin_amdgcn_fractf(Uc),
+                                                     __builtin_amdgcn_fractf(Vc));
                             const float a0 = f4at(at[q >> 2], q & 3);
                             float abar;
                             if constexpr (PAIRED) {
@@ -1007,15 +1017,26 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
                             comp_add(P, Lbar);
                         }
                         tau += 1.f;
-                        if ((q & 3) == 3 && k - 3 < g.nt)
+                        if ((q & 3) == 3 && (kWhole || k - 3 < g.nt))
                             buffer_st4_stream(rb, roff, 4u * att_row(g, k - 3), make_float4(ov[0], ov[1], ov[2], ov[3]));
                     }
+                };
+                load(0, xa, xb);
+                int k0 = 0;
+                for (; k0 + kRayChunk <= g.nt; k0 += kRayChunk) {
+                    epart = 0.f;
+                    load(k0 + KH, ya, yb);
+                    step(std::true_type{}, k0, xa, xb);
+                    if (k0 + kRayChunk < g.nt) load(k0 + kRayChunk, xa, xb);
+                    step(std::true_type{}, k0 + KH, ya, yb);
                     if constexpr (PAIRED) kahan_add(eb, epart);
-#pragma unroll
-                    for (int q = 0; q < KG; ++q) {
-                        at[q] = an[q];
-                        bt[q] = bn[q];
-                    }
+                }
+                if (k0 < g.nt) {
+                    epart = 0.f;
+                    load(k0 + KH, ya, yb);
+                    step(std::false_type{}, k0, xa, xb);
+                    step(std::false_type{}, k0 + KH, ya, yb);
+                    if constexpr (PAIRED) kahan_add(eb, epart);
                 }
                 if constexpr (PAIRED) {
                     float *eo = A.Ebar + cand * A.e_cs + ray;
@@ -1036,7 +1057,7 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
                 const float e_ray = PAIRED ? A.E[cand * A.e_cs + ray] : 0.f;
                 const float rho2 =
                     PAIRED ? A.rho[cand * A.sino_cs + (size_t)((a + g.nah) * g.nb + (g.nb - 1 - b))] : 0.f;
-                Comp eb = ebj[j];
+                Comp eb = comp_pick(ebj, j);
                 for (int kc = kstart; kc <= k1; kc += kBandChunk) {
                     float4 av[kBandChunk / 4], bv[kBandChunk / 4];
 #pragma unroll
@@ -1076,7 +1097,7 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
                     }
                     if constexpr (PAIRED) kahan_add(eb, epart);
                 }
-                if constexpr (PAIRED) ebj[j] = eb;
+                if constexpr (PAIRED) comp_put(ebj, j, eb);
             }
         }
     }
@@ -1195,16 +1216,16 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
                           : (k0 + 4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, k0 + 4 * q)) : z4;
         float tau = (float)k0 - g.cT;
         float p = 0.f, p2 = 0.f;
+        // samples past the ray's end are masked, not branched over: the chunk's LDS reads overlap
+        const unsigned bits = band_bits(k0, 0, g.nt - 1);
 #pragma unroll
         for (int q = 0; q < KC; ++q) {
-            if (k0 + q < g.nt) {
-                float U, V;
-                sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
-                const float at = f4at(v[q >> 2], q & 3);
-                const float w = bilinear_whole(lds, U, V, nf, pitch);
-                p = fmaf(at, w, p);
-                if constexpr (PAIRED) p2 = fmaf(opposed_att(e_ray, at), w, p2);
-            }
+            float U, V;
+            sample_uv(Ub, Vb, tau, cs.x, cs.y, U, V);
+            const float at = f4at(v[q >> 2], q & 3);
+            const float w = bit_keep(bits, q, bilinear_whole(lds, U, V, nf, pitch));
+            p = fmaf(at, w, p);
+            if constexpr (PAIRED) p2 = fmaf(opposed_att(e_ray, at), w, p2);
             tau += 1.f;
         }
         part[h] = p;
