@@ -84,6 +84,7 @@ __device__ __forceinline__ size_t att_base(const DevGeom &g, int a, int b) {
 struct Band {
     int alo, ahi;
     bool first, last;
+    int pitch;  // LDS elements per staged row, n + 3 or one more
 };
 
 __device__ __forceinline__ float sigma_of(const DevGeom &g, int b) {
@@ -168,13 +169,13 @@ __device__ __forceinline__ Comp block_reduce(Comp c, float *scratch) {
 
 // ---------------------------------------------------------------- LDS image staging
 // Stage rows band.alo..band.ahi and columns -1..n+1 of an n x n image (NC = 1 scalar image, NC = 2
-// interleaved pair) into lds with row pitch n+3, zero outside the image. Eight loads per thread are
+// interleaved pair) into lds with row pitch band.pitch, zero outside the image. Eight loads per thread are
 // issued before their stores so the copy is not one memory round trip per element; the row index
 // uses an exact float reciprocal (idx < 2^20, pitch <= 1027).
 template <int NC>
 __device__ __forceinline__ void stage_band(const float *__restrict__ img, int n, const Band &band, float *lds) {
     constexpr int U = 8;
-    const int pitch = n + 3;
+    const int pitch = band.pitch;
     const int rows = band.ahi - band.alo + 1;
     const int total = rows * pitch;
     const float inv_pitch = 1.f / (float)pitch;
@@ -209,7 +210,7 @@ __device__ __forceinline__ void stage_band(const float *__restrict__ img, int n,
 }
 
 // The whole n x n image (n a multiple of 4) into lds with the layout of stage_band's single band (rows
-// and columns -1..n+1, pitch n+3, zero border): 16-byte loads, U of them in flight per thread, so a
+// and columns -1..n+1, pitch band.pitch, zero border): 16-byte loads, U of them in flight per thread, so a
 // small workgroup stages an image in a few memory round trips. Falls back to stage_band otherwise.
 template <int U = 8>
 __device__ __forceinline__ void stage_whole(const float *__restrict__ img, int n, const Band &band, float *lds) {
@@ -217,7 +218,7 @@ __device__ __forceinline__ void stage_whole(const float *__restrict__ img, int n
         stage_band<1>(img, n, band, lds);
         return;
     }
-    const int pitch = n + 3;
+    const int pitch = band.pitch;
     // zero border: rows -1, n, n+1 and columns -1, n, n+1 of every staged row
     for (int t = threadIdx.x; t < 3 * pitch; t += blockDim.x) {
         const int r = t / pitch, c = t - r * pitch;
@@ -256,7 +257,7 @@ __device__ __forceinline__ void stage_whole(const float *__restrict__ img, int n
 __device__ __forceinline__ void stage_band_pair(const float *__restrict__ img0, const float *__restrict__ img1, int n,
                                                 const Band &band, float *lds) {
     constexpr int U = 8;
-    const int pitch = n + 3;
+    const int pitch = band.pitch;
     const int rows = band.ahi - band.alo + 1;
     const int total = rows * pitch;
     const float inv_pitch = 1.f / (float)pitch;
@@ -283,7 +284,7 @@ __device__ __forceinline__ void stage_band_pair(const float *__restrict__ img0, 
 __device__ __forceinline__ void stage_band_strided(const float *__restrict__ img, int n, int stride, const Band &band,
                                                    float *lds) {
     constexpr int U = 8;
-    const int pitch = n + 3;
+    const int pitch = band.pitch;
     const int rows = band.ahi - band.alo + 1;
     const int total = rows * pitch;
     const float inv_pitch = 1.f / (float)pitch;
@@ -433,7 +434,7 @@ __device__ __forceinline__ float bit_keep(unsigned bits, int q, float x) {
     return __uint_as_float(__float_as_uint(x) & (unsigned)((int)(bits << (31 - q)) >> 31));
 }
 
-// Bilinear read at (U, V) from a whole-image stage (rows -1..n+1, columns -1..n+1, pitch n+3):
+// Bilinear read at (U, V) from a whole-image stage (rows -1..n+1, columns -1..n+1, pitch the band's):
 // the clamp to [-1, n] keeps every tap inside the zero border. The tap's index floor(V) pitch +
 // floor(U) is formed in float (exact: small integers) and converted once, which is cheaper than an
 // integer multiply.

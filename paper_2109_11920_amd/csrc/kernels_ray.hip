@@ -74,7 +74,7 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
     int cand, chunk;
     ray_block(bid, chunks, C, cand, chunk);
     const int nrays = g.nah * g.nb;
-    const int pitch = g.n + 3;
+    const int pitch = bands.pitch;
     const float nf = (float)g.n;
     const float *img = mu + cand * img_cs;
     float *out = att + cand * att_cs;
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void k_att_scan(DevGeom g, Band band, int pass
     extern __shared__ float lds[];
     int cand, chunk;
     ray_block(blockIdx.x, chunks, C, cand, chunk);
-    const int pitch = g.n + 3;
+    const int pitch = band.pitch;
     const float nf = (float)g.n;
     stage_whole<16>(mu + cand * img_cs, g.n, band, lds);
     __syncthreads();
@@ -326,7 +326,7 @@ template <bool PAIRED>
 __device__ __forceinline__ void fwd_band_ray(const DevGeom &g, const Band &band, const float *lds, const float *att,
                                              unsigned att_bytes, int a, int b, float2 cs, float Ub, float Vb, float e_ray,
                                              Comp &c, Comp &c2) {
-    const int pitch = g.n + 3;
+    const int pitch = band.pitch;
     const float nf = (float)g.n;
     // The ray's samples in this band, KC at a time from the 4-aligned group holding the first, the next
     // chunk's loads (4 samples per 16-byte load) in flight meanwhile. The owned range is exact and the other
@@ -380,7 +380,7 @@ __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevG
     int cand, chunk;
     ray_block(bid, chunks, C, cand, chunk);
     const int nrays = g.nah * g.nb;
-    const int pitch = g.n + 3;
+    const int pitch = bands.pitch;
     const float nf = (float)g.n;
     const float *att = A.att + cand * A.att_cs;
     const float *img = A.img + cand * A.img_cs;
@@ -525,7 +525,7 @@ __device__ __forceinline__ void k_fwd_pair_body(int bid, float *lds, float *red,
     const bool two = (c0 + 1 < C);
     const int c1 = two ? c0 + 1 : c0;
     const int nrays = g.nah * g.nb;
-    const int pitch = g.n + 3;
+    const int pitch = bands.pitch;
     const float nf = (float)g.n;
     stage_band_pair(A.img + c0 * A.img_cs, A.img + c1 * A.img_cs, g.n, bands.band(0, g.n), lds);
     __syncthreads();
@@ -658,7 +658,7 @@ __device__ __forceinline__ void sweep_band_ray(const DevGeom &g, const Band &ban
                                                __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, int accumulate, int a, int b, float2 cs,
                                                float Ub, float Vb, float e_ray, float rr, float yp, float rr2, float yp2,
                                                Comp &c, Comp &c2, Comp &eb) {
-    const int pitch = g.n + 3;
+    const int pitch = band.pitch;
     const float nf = (float)g.n;
     // The ray's samples in this band as in the projection: exact range, masked values, 8 at a time (the most
     // whose att and att_bar, this chunk's and the next one's, fit the registers). The ray is this thread's alone
@@ -745,7 +745,7 @@ __device__ __forceinline__ void k_adj_sweep_body(int bid, float *lds, DevGeom g,
     int cand, chunk;
     ray_block(bid, chunks, C, cand, chunk);
     const int nrays = g.nah * g.nb;
-    const int pitch = g.n + 3;
+    const int pitch = bands.pitch;
     const float nf = (float)g.n;
     const float *att = A.att + cand * A.att_cs;
     float *ab = A.attbar + cand * A.att_cs;
@@ -938,7 +938,7 @@ __device__ __forceinline__ void k_tail_body(int bid, float *lds, DevGeom g, cons
     int cand, chunk;
     ray_block(bid, chunks, C, cand, chunk);
     const int nrays = g.nah * g.nb;
-    const int pitch = g.n + 3;
+    const int pitch = bands.pitch;
     const float nf = (float)g.n;
     const float *att = A.att + cand * A.att_cs;
     float *ab = A.attbar + cand * A.att_cs;
@@ -1174,7 +1174,7 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
     int cand, chunk;
     ray_block(blockIdx.x, chunks, C, cand, chunk);
     const int nrays = g.nah * g.nb;
-    const int pitch = g.n + 3;
+    const int pitch = band.pitch;
     const float nf = (float)g.n;
     const int lane = threadIdx.x & (kSplitLanes - 1);
     const int ray = chunk * (blockDim.x / kSplitLanes) + threadIdx.x / kSplitLanes;

@@ -16,10 +16,11 @@ namespace boac {
 struct Bands {
     int count;
     int rows;
+    int pitch;  // LDS elements per staged row: n + 3, or one more to make it odd (make_bands)
     __host__ __device__ Band band(int i, int n) const {
         const int lo = -1 + i * rows;
         const int hi = lo + rows < n + 1 ? lo + rows : n + 1;
-        return Band{lo, hi, i == 0, i == count - 1};
+        return Band{lo, hi, i == 0, i == count - 1, pitch};
     }
 };
 
