@@ -127,7 +127,7 @@ __device__ void run_task(const TaskRec &T, int item, float *lds, float *red) {
             if (vb >= 0) {
                 const int cidx = vb / R.nbx;
                 raster_at(R.g, R.cand, R.delta_r, R.mu, R.img_cs, R.status, R.ones, cidx,
-                          (vb - cidx * R.nbx) * 256 + (int)(threadIdx.x & 255));
+                          (vb - cidx * R.nbx) * 256 + (int)(threadIdx.x & 255), true);
             }
             break;
         }
