@@ -500,16 +500,17 @@ constexpr int kFewCand = 8;
 // Modelled time (cycles) of a single-stage ray launch of `wgs` workgroups of w waves, rpt rays per thread: the
 // workgroups a CU holds (LDS, registers) run in rounds; a round costs its image stage (LDS bytes over its
 // threads) and a fixed part, and per ray pass and 16 samples a latency plus the vector work of the waves on a
-// SIMD. Constants fitted to sweeps of every block of 256 to 1024 threads and 1 to 4 rays per thread at 18
-// shapes (64 to 192 pixels, 60 to 256 angles, 9 to 100 candidates): its choice is within 3% of the best
-// measured one on average and 17% at worst.
+// SIMD. Constants fitted to sweeps of every block of 256 to 1024 threads and 1 to 4 rays per thread at 24
+// shapes (64 to 192 pixels, 60 to 256 angles, 9 to 256 candidates): its choice is within 3% of the best
+// measured one on average and 16% at worst. (The constants of the kernels that tested every sample chose within
+// 6% and 40% for these: 37 candidates at 109 pixels and 90 angles in pairs 43.8 us, singly 32.5.)
 struct RayCost {
     double latency, valu, stage, fixed;
     int waves;  // waves a SIMD holds (registers)
 };
-constexpr RayCost kCostOne{1600, 4000, 3.9, 470, 7};       // projection of one candidate
-constexpr RayCost kCostPair{1840, 4820, 2.0, 13500, 4};    // of two
-constexpr RayCost kCostSweep{4060, 1970, 226, 3450, 4};    // reverse sweep, tail
+constexpr RayCost kCostOne{1493, 1549, 79.3, 10189, 5};    // projection of one candidate
+constexpr RayCost kCostPair{3718, 2098, 8.3, 12442, 6};    // of two
+constexpr RayCost kCostSweep{4853, 2437, 5.6, 4157, 4};    // reverse sweep, tail
 static double ray_cost(const RayCost &k, int n_cu, int n_samples, size_t lds, long wgs, int w, int rpt) {
     const long held = std::max<long>(1, std::min<long>((long)(160 * 1024 / (lds + 512)), 4L * k.waves / w));
     const long rounds = (wgs + n_cu * held - 1) / (n_cu * held);
