@@ -600,14 +600,16 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
     // its likelihood partials, one per 32 held rays, are within the no-allocation scratch's estimate (one per 64
     // rays of every angle) only with half the angles held
     rc->split_nll = rc->split_chunks > 0 && (!ctx->arena || nah < g.n_angles);
-    // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give every CU
-    // a workgroup (single stage; BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group as
-    // still give every CU two workgroups (at most 32). One candidate at 128 pixels and 128 angles: 10 us, one
-    // thread per ray 33 us; with a workgroup for every CU one thread per ray is faster (24 candidates at 120
-    // pixels and 75 angles 54 against 137 us).
+    // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give half the
+    // CUs a workgroup of 256, a quarter where an image takes over half the LDS, which each of the many small
+    // workgroups stages (single stage; BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group
+    // as still give every CU two workgroups (at most 32). With the projection that follows, at 96 pixels and 96
+    // angles: 6 candidates 25 us, one thread per ray 33; 13 candidates 43 against 36. 128 pixels, 128 angles: 4
+    // candidates 36 against 41, 6 candidates 67 against 51. 192 pixels, 96 angles: 2 candidates 76 against 68.
     rc->scan_passes = rc->scan_chunks = 0;
     const char *ea = std::getenv("BOAC_ATT_SCAN");
-    if (!(ea && ea[0] == '0') && comps == 1 && rc->single && (long)((nrays + 255) / 256) * C < ctx->n_cu) {
+    if (!(ea && ea[0] == '0') && comps == 1 && rc->single &&
+        (long)((nrays + 255) / 256) * C * (rc->lds > kLdsBudget / 2 ? 4 : 2) <= ctx->n_cu) {
         const long total = (nrays + 31) / 32;
         rc->scan_passes = (int)std::min<long>(32, std::max<long>(1, total * C / (2L * ctx->n_cu)));
         rc->scan_chunks = (int)((total + rc->scan_passes - 1) / rc->scan_passes);
