@@ -1283,10 +1283,11 @@ hipError_t launch_att(const DevGeom &g, const RayCfg &rc, const Bands &bands, co
                            bands.band(0, g.n), rc.scan_passes, rc.scan_chunks, C, mu, att, img_cs, att_cs, E, e_cs);
         return hipGetLastError();
     }
-    if (rc.single)
-        hipLaunchKernelGGL(k_att<true>, ray_grid(rc, C), dim3(rc.block), rc.lds, st, g, bands, rc.rpt, rc.chunks, C,
-                           mu, att, img_cs, att_cs, E, e_cs);
-    else
+    if (rc.single) {
+        const int per = rc.att_block * rc.att_rpt, chunks = (g.nah * g.nb + per - 1) / per;
+        hipLaunchKernelGGL(k_att<true>, dim3((unsigned)chunks * (unsigned)C), dim3(rc.att_block), rc.lds, st, g, bands,
+                           rc.att_rpt, chunks, C, mu, att, img_cs, att_cs, E, e_cs);
+    } else
         hipLaunchKernelGGL(k_att<false>, ray_grid(rc, C), dim3(rc.block), rc.lds, st, g, bands, rc.rpt, rc.chunks,
                            C, mu, att, img_cs, att_cs, E, e_cs);
     return hipGetLastError();

@@ -42,6 +42,7 @@ struct RayCfg {
     // few candidates: attenuation build with a ray over 8 lanes (single stage; scan_passes 0 = one thread per
     // ray): scan_passes rays per lane group, scan_chunks workgroups of 256 threads per candidate
     int scan_passes, scan_chunks;
+    int att_block, att_rpt;  // single stage: the attenuation build's own workgroups
 };
 
 enum FwdMode { FWD_PROJ = 0, FWD_RATIO = 1, FWD_NLL = 2 };

@@ -511,6 +511,7 @@ struct RayCost {
 constexpr RayCost kCostOne{1493, 1549, 79.3, 10189, 5};    // projection of one candidate
 constexpr RayCost kCostPair{3718, 2098, 8.3, 12442, 6};    // of two
 constexpr RayCost kCostSweep{4853, 2437, 5.6, 4157, 4};    // reverse sweep, tail
+constexpr RayCost kCostAtt{1500, 4100, 3.9, 470, 8};       // attenuation build (not fitted: its operations)
 static double ray_cost(const RayCost &k, int n_cu, int n_samples, size_t lds, long wgs, int w, int rpt) {
     const long held = std::max<long>(1, std::min<long>((long)(160 * 1024 / (lds + 512)), 4L * k.waves / w));
     const long rounds = (wgs + n_cu * held - 1) / (n_cu * held);
@@ -600,6 +601,25 @@ static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg
     // its likelihood partials, one per 32 held rays, are within the no-allocation scratch's estimate (one per 64
     // rays of every angle) only with half the angles held
     rc->split_nll = rc->split_chunks > 0 && (!ctx->arena || nah < g.n_angles);
+    // the attenuation build is bound by its vector work (twice a projection's per sample), so it has workgroups of
+    // its own: 13 candidates at 96 pixels and 96 angles 21.7 us in 234 workgroups of 256 threads, 24.2 in the
+    // projection's 156 of 384, which load two SIMDs of a CU twice and leave CUs without any
+    rc->att_block = rc->block;
+    rc->att_rpt = rc->rpt;
+    if (rc->single && comps == 1) {
+        double best = 0.0;
+        for (int block = 1024; block >= 256; block -= 64)
+            for (int rpt = 1; rpt <= 4; ++rpt) {
+                const long wgs = (long)((nrays + block * rpt - 1) / (block * rpt)) * C;
+                const double cost = ray_cost(kCostAtt, ctx->n_cu, g.n_samples, rc->lds, wgs, block / 64, rpt);
+                if (best == 0.0 || cost < best) {
+                    best = cost;
+                    rc->att_block = block;
+                    rc->att_rpt = rpt;
+                }
+                if (wgs <= ctx->n_cu) break;
+            }
+    }
     // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give half the
     // CUs a workgroup of 256, a quarter where an image takes over half the LDS, which each of the many small
     // workgroups stages (single stage; BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group
