@@ -608,6 +608,25 @@ __device__ __forceinline__ void back_epilogue(const DevGeom &g, const BackArgs &
     }
 }
 
+// Offset (du0, dv0) of the window's centre sample (sig, tau) from the pixel at (xc, yc) from the centre. Wider
+// windows (HB > 1) take the projector's own sequence of roundings, as the general kernel does: at a fit's end
+// (200 iterations, 4e6 counts per bin, 62 bins on 48 pixels) the gradient at the fixed image is the small
+// difference that the two operators' roundings leave.
+template <int HB>
+__device__ __forceinline__ void window_offset(const DevGeom &g, float sig, float tau, float c, float s, float xc, float yc,
+                                              float &du0, float &dv0) {
+    if constexpr (HB > 1) {
+        float Ub, Vb, U0, V0;
+        ray_base(g, sig, c, s, Ub, Vb);
+        sample_uv(Ub, Vb, tau, c, s, U0, V0);
+        du0 = U0 - (xc + g.cN);  // the pixel's index, exactly
+        dv0 = V0 - (yc + g.cN);
+    } else {
+        du0 = fmaf(sig, c, fmaf(tau, -s, -xc));
+        dv0 = fmaf(sig, s, fmaf(tau, c, -yc));
+    }
+}
+
 // Column-group variant of the slid-block gather, for bin half windows HB of 1 to 3 (detectors up to twice as
 // fine as the pixels): blocks of col4_bins(HB) bins, two per staging thread where they are more than 32 (the
 // general kernel took those, one candidate per workgroup and without opposed-ray pairing: 47 iterations of 7
@@ -841,8 +860,8 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
             const float bcf = __builtin_amdgcn_fmed3f(floorf(Sj5), f0.x, f0.z);
             const float kcf = __builtin_amdgcn_fmed3f(floorf(Tj5), f0.y, f0.w);
             const float sig = (bcf - g.cB) * g.bscale, tau = kcf - g.cT;
-            const float du0 = fmaf(sig, c, fmaf(tau, -s, -xc));
-            const float dv0 = fmaf(sig, s, fmaf(tau, c, -yc));
+            float du0, dv0;
+            window_offset<HB>(g, sig, tau, c, s, xc, yc, du0, dv0);
             // window tap (-HB, -1): (kcf - k0 - 1) PL + bcf - b0 - HB, exact in FP32
             const int corner = (int)(fmaf(kcf, (float)PL, bcf) - f1.x);
             const float *base = lds + corner * V;
@@ -850,6 +869,19 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
             for (int db = -HB; db <= HB; ++db) {
                 const float dub = (db == 0) ? du0 : db == -1 ? du0 - ub : db == 1 ? du0 + ub : fmaf((float)db, ub, du0);
                 const float dvb = (db == 0) ? dv0 : db == -1 ? dv0 - vb : db == 1 ? dv0 + vb : fmaf((float)db, vb, dv0);
+                // wider windows sum a bin's samples first, as the general kernel does: a third of the roundings at
+                // the block sum's size (image after 200 iterations, 76 bins on 40 pixels: 9.7e-6 off with one
+                // running sum over the window, 7.2e-6 so and with the general kernel)
+                float part[HB > 1 ? CG : 1];
+                if constexpr (HB > 1)
+#pragma unroll
+                    for (int q = 0; q < CG; ++q) part[q] = 0.f;
+                auto &sum = [&]() -> auto & {
+                    if constexpr (HB > 1)
+                        return part;
+                    else
+                        return blk;
+                }();
 #pragma unroll
                 for (int dk = -1; dk <= 1; ++dk) {
                     const float du = (dk == 0) ? dub : (dk < 0 ? dub + s : dub - s);
@@ -860,9 +892,12 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
                         Vec<V> gv;
                         gv.load(base + h * PLANE + ((dk + 1) * PL + (db + HB)) * V);
 #pragma unroll
-                        for (int q = 0; q < V; ++q) blk[h * V + q] = fmaf(w, gv.v[q], blk[h * V + q]);
+                        for (int q = 0; q < V; ++q) sum[h * V + q] = fmaf(w, gv.v[q], sum[h * V + q]);
                     }
                 }
+                if constexpr (HB > 1)
+#pragma unroll
+                    for (int q = 0; q < CG; ++q) blk[q] += part[q];
                 // keep the next window row's LDS reads after this row's FMAs: 12 registers of taps in
                 // flight instead of 36 (71 VGPRs, one more wave per SIMD)
                 if (db < HB) __builtin_amdgcn_sched_barrier(0);
@@ -1006,19 +1041,22 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
             const float bcf = __builtin_amdgcn_fmed3f(floorf(Sj5), fb1, fb1 + (float)(PB - 1 - 2 * HB));
             const float kcf = __builtin_amdgcn_fmed3f(floorf(Tj5), fk1, fk1 + (float)(kWavePK - 3));
             const float sig = (bcf - g.cB) * g.bscale, tau = kcf - g.cT;
-            const float du0 = fmaf(sig, c, fmaf(tau, -s, -xc));
-            const float dv0 = fmaf(sig, s, fmaf(tau, c, -yc));
+            float du0, dv0;
+            window_offset<HB>(g, sig, tau, c, s, xc, yc, du0, dv0);
             const float *base = st + (int)fmaf(kcf - fk1, (float)PL, bcf - fb1);  // window tap (-HB, -1)
 #pragma unroll
             for (int db = -HB; db <= HB; ++db) {
                 const float dub = (db == 0) ? du0 : db == -1 ? du0 - ub : db == 1 ? du0 + ub : fmaf((float)db, ub, du0);
                 const float dvb = (db == 0) ? dv0 : db == -1 ? dv0 - vb : db == 1 ? dv0 + vb : fmaf((float)db, vb, dv0);
+                float part = 0.f;
+                float &sum = HB > 1 ? part : blk;
 #pragma unroll
                 for (int dk = -1; dk <= 1; ++dk) {
                     const float du = (dk == 0) ? dub : (dk < 0 ? dub + s : dub - s);
                     const float dv = (dk == 0) ? dvb : (dk < 0 ? dvb - c : dvb + c);
-                    blk = fmaf(hat2(du, dv), base[(dk + 1) * PL + (db + HB)], blk);
+                    sum = fmaf(hat2(du, dv), base[(dk + 1) * PL + (db + HB)], sum);
                 }
+                if (HB > 1) blk += part;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
