@@ -40,11 +40,11 @@
  *     with compensated (error-free transformation) summation.
  *   - With an even n_angles, ray (a, b) and ray (a + n_angles/2, n_bins-1-b) share their samples in
  *     reverse order, and under the half-self rule their attenuations multiply to exp(-T), T the ray's
- *     total. Where the backprojection runs on its column-group kernel, the library then stores the
- *     attenuation of the first n_angles/2 angles plus exp(-T) per ray and derives the rest ("opposed-
- *     ray pairing"). Results equal those of holding every angle up to FP32 rounding for optical path
- *     lengths below ~87 (attenuations above the smallest normal float). Setting the environment
- *     variable BOAC_OPPOSED_RAYS=0 holds every angle.
+ *     total. Where the backprojection runs on its column-group kernel, n_samples is a multiple of 4 and
+ *     n_bins at most 1.06 n, the library then stores the attenuation of the first n_angles/2 angles plus
+ *     exp(-T) per ray and derives the rest ("opposed-ray pairing"). Results equal those of holding every
+ *     angle up to FP32 rounding for optical path lengths below ~87 (attenuations above the smallest normal
+ *     float). Elsewhere every angle is held, as it is with the environment variable BOAC_OPPOSED_RAYS=0.
  */
 #ifndef BOAC_H
 #define BOAC_H

@@ -629,20 +629,18 @@ __device__ __forceinline__ void window_offset(const DevGeom &g, float sig, float
 
 // Column-group variant of the slid-block gather, for bin half windows HB of 1 to 3 (detectors up to twice as
 // fine as the pixels): blocks of col4_bins(HB) bins, two per staging thread where they are more than 32 (the
-// general kernel took those, one candidate per workgroup and without opposed-ray pairing: 47 iterations of 7
-// candidates at 223 pixels, 262 bins and 168 angles 34.3 ms against 16.6 ms). The host aligns the block's first sample row to a
-// multiple of 4, so the 4 samples k..k+3 (k = first row + 4 j) of a bin
-// are one aligned 16-byte load in the attenuation layout (sample fastest inside a 4 x 8 block): thread
-// t stages bin t % 32 of rows 4 (t / 32) .. + 3 with one 16-byte load per candidate, a quarter of the
-// vector-memory instructions of the slot variant (which is bound by its vector-memory pipeline), and
+// general kernel took those, one candidate per workgroup: 7 candidates at 223 pixels, 262 bins and 168 angles 468 us
+// per launch against 264). The host aligns the block's first sample row to a multiple of 4, so the 4 samples
+// k..k+3 (k = first row + 4 j) of a bin are one aligned 16-byte load in the attenuation layout (sample fastest
+// inside a 4 x 8 block): thread t stages bin t % 32 of rows 4 (t / 32) .. + 3 with one 16-byte load per candidate, a
+// quarter of the vector-memory instructions of the slot variant (which is bound by its vector-memory pipeline), and
 // 8 lanes on consecutive bins read one whole 128-byte line. All 4 samples share the bin's ray weight,
 // folded in while staging as in the slot variant. A group is loaded unless all of it lies outside the
 // union of the tile pixels' supports (tested at its centre with half widths grown by 1.5 samples); a
 // skipped group keeps finite values, gathered only with weight 0. Where n_samples is no multiple of 4, a
 // block at the rays' end also stages the layout's padding rows; they hold no sample, so their slots are
-// set to 0 (TAIL; a variant of its own, as even the untaken branch costs the gather 6%). Such sizes once took
-// the slot variant without opposed-ray pairing, twice the bytes and angles: 110 us per launch for 109 x 109
-// images, 90 angles and 37 candidates, against 60 us, and 94 us against 36 us in the projection.
+// set to 0 (TAIL; a variant of its own, as even the untaken branch costs the gather 6%). 37 candidates at 109
+// pixels and 90 angles: 102 us per launch, 111 with the slot variant.
 // PAIRED (opposed-ray pairing, g.nah = na/2): the slab of angle a < na/2 also stands for angle
 // a + na/2, whose sample (nb-1-b, nt-1-k) sits at sample (b, k) of angle a with attenuation
 // exp(-T_ab) / att and the same bilinear weights; each staged slot holds both contributions,
@@ -871,7 +869,7 @@ __device__ __forceinline__ void k_back_col4_body(int bid, int tid, float *lds, b
                 const float dvb = (db == 0) ? dv0 : db == -1 ? dv0 - vb : db == 1 ? dv0 + vb : fmaf((float)db, vb, dv0);
                 // wider windows sum a bin's samples first, as the general kernel does: a third of the roundings at
                 // the block sum's size (image after 200 iterations, 76 bins on 40 pixels: 9.7e-6 off with one
-                // running sum over the window, 7.2e-6 so and with the general kernel)
+                // running sum over the window, 7.7e-6 so and with the general kernel)
                 float part[HB > 1 ? CG : 1];
                 if constexpr (HB > 1)
 #pragma unroll
@@ -1073,77 +1071,66 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
 #endif
 
 #ifndef BOAC_BODIES_ONLY
-template <int CG, bool TAIL, int HB>
+// Opposed-ray pairing is for half the angles, a one-bin window and whole groups of 4 samples only.
+static bool pairs_ok(const DevGeom &g, const BackCfg &bc) {
+    return g.nah * 2 == g.na && bc.hb == 1 && (g.nt & 3) == 0;
+}
+
+template <int CG, bool PAIRED, bool TAIL, int HB>
 static void back_col4_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     const int ngroups = (a.C + CG - 1) / CG;
     const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * ngroups));
-    const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
-    if (a.E) {
-        if (weighted)
-            hipLaunchKernelGGL((k_back_col4<CG, true, true, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
-        else
-            hipLaunchKernelGGL((k_back_col4<CG, false, true, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
-    } else if (weighted) {
-        hipLaunchKernelGGL((k_back_col4<CG, true, false, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
-    } else {
-        hipLaunchKernelGGL((k_back_col4<CG, false, false, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
-    }
-}
-
-template <int CG, int HB>
-static void back_col4_tail(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    // wider windows take the variant with the padding rows' test at every sample count
-    if (HB > 1 || (g.nt & 3))
-        back_col4_go<CG, true, HB>(g, bc, a, mode, st);
+    if (mode == BACK_SENS || mode == BACK_FIELD)
+        hipLaunchKernelGGL((k_back_col4<CG, false, PAIRED, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
     else
-        back_col4_go<CG, HB != 1, HB>(g, bc, a, mode, st);
+        hipLaunchKernelGGL((k_back_col4<CG, true, PAIRED, TAIL, HB>), grid, dim3(256), bc.lds, st, g, bc, a, mode);
 }
 
 template <int CG>
 static hipError_t back_col4(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    if ((a.E && g.nah * 2 != g.na) || bc.tw != 16 || bc.th != 16) return hipErrorInvalidValue;
-    if (bc.hb == 1)
-        back_col4_tail<CG, 1>(g, bc, a, mode, st);
+    if ((a.E && !pairs_ok(g, bc)) || bc.tw != 16 || bc.th != 16) return hipErrorInvalidValue;
+    // wider windows take the variant with the padding rows' test at every sample count
+    if (a.E)
+        back_col4_go<CG, true, false, 1>(g, bc, a, mode, st);
+    else if (bc.hb == 1 && !(g.nt & 3))
+        back_col4_go<CG, false, false, 1>(g, bc, a, mode, st);
+    else if (bc.hb == 1)
+        back_col4_go<CG, false, true, 1>(g, bc, a, mode, st);
     else if constexpr (CG > 4)
         return hipErrorInvalidValue;
     else if (bc.hb == 2)
-        back_col4_tail<CG, 2>(g, bc, a, mode, st);
+        back_col4_go<CG, false, true, 2>(g, bc, a, mode, st);
     else if (bc.hb == 3)
-        back_col4_tail<CG, 3>(g, bc, a, mode, st);
+        back_col4_go<CG, false, true, 3>(g, bc, a, mode, st);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-template <bool TAIL, int HB>
+template <bool PAIRED, bool TAIL, int HB>
 static void back_wave_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     const int nblk = (g.nah + 7) / 8;
     const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * a.C)), block((unsigned)(64 * std::min(nblk, kWaveBlocks)));
-    const bool weighted = !(mode == BACK_SENS || mode == BACK_FIELD);
-    if (a.E) {
-        if (weighted)
-            hipLaunchKernelGGL((k_back_wave<true, true, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
-        else
-            hipLaunchKernelGGL((k_back_wave<false, true, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
-    } else if (weighted) {
-        hipLaunchKernelGGL((k_back_wave<true, false, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
-    } else {
-        hipLaunchKernelGGL((k_back_wave<false, false, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
-    }
+    if (mode == BACK_SENS || mode == BACK_FIELD)
+        hipLaunchKernelGGL((k_back_wave<false, PAIRED, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
+    else
+        hipLaunchKernelGGL((k_back_wave<true, PAIRED, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
 }
 
 static hipError_t back_wave(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    if (bc.tw != 8 || bc.th != 8 || bc.cg != 1 || (a.E && g.nah * 2 != g.na) ||
+    if (bc.tw != 8 || bc.th != 8 || bc.cg != 1 || (a.E && !pairs_ok(g, bc)) ||
         bc.lds < (size_t)256 * ((g.nah + 7) / 8))
         return hipErrorInvalidValue;
-    if (bc.hb == 1 && !(g.nt & 3))
-        back_wave_go<false, 1>(g, bc, a, mode, st);
+    if (a.E)
+        back_wave_go<true, false, 1>(g, bc, a, mode, st);
+    else if (bc.hb == 1 && !(g.nt & 3))
+        back_wave_go<false, false, 1>(g, bc, a, mode, st);
     else if (bc.hb == 1)
-        back_wave_go<true, 1>(g, bc, a, mode, st);
+        back_wave_go<false, true, 1>(g, bc, a, mode, st);
     else if (bc.hb == 2)
-        back_wave_go<true, 2>(g, bc, a, mode, st);
+        back_wave_go<false, true, 2>(g, bc, a, mode, st);
     else if (bc.hb == 3)
-        back_wave_go<true, 3>(g, bc, a, mode, st);
+        back_wave_go<false, true, 3>(g, bc, a, mode, st);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
