@@ -933,18 +933,20 @@ __global__ __launch_bounds__(256) void k_back_col4(DevGeom g, BackCfg T, BackArg
 // that). A wave's lanes are the tile's pixels; it stages the tile's footprint of each of its angles, a block
 // of wave_bins(HB) bins x kWavePK samples with an origin as k_back_col4's, in LDS of its own: 4 samples of a bin
 // per lane and load, all 8 angles' loads in flight before the first is used, and no barrier until the
-// blocks' sums meet in LDS, where the first wave adds them in order. The window, its weights, the staged
-// values and the order of every sum are k_back_col4's, so the results are too, bit for bit.
+// blocks' sums meet in LDS, where the first wave adds them in order. ROUNDS: more than kWaveSums blocks
+// (4096 angles), that many at a time; a variant of its own, as the loop costs 2 to 10%.
+// The window, its weights, the staged values and the order of every sum are k_back_col4's, so the results are too,
+// bit for bit.
 // Bound by latency: one memory round trip, 8 short gathers and one barrier (one candidate, 128 x 128, 128
 // angles: 8.8 us a launch; the split over workgroups it replaces, with its second pass over the block sums, 14.3).
 #ifndef BOAC_BODIES_ONLY
-template <bool WEIGHTED, bool PAIRED, bool TAIL, int HB>
+template <bool WEIGHTED, bool PAIRED, bool TAIL, int HB, bool ROUNDS>
 __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackCfg T, BackArgs A, int mode) {
     constexpr int PB = wave_bins(HB), PL = PB + 1;   // staged bins, LDS pitch of a staged row
     constexpr int RPL = 64 / PB;                     // 4-sample groups a load covers
     constexpr int NG = kWavePK / 4, NL = (NG + RPL - 1) / RPL;
     __shared__ float stage[kWaveBlocks][kWavePK * PL];
-    extern __shared__ float sums[];  // [8-angle blocks][64 pixels]
+    extern __shared__ float sums[];  // [8-angle blocks, of one round][64 pixels]
     const int ntiles = T.tiles_x * T.tiles_y;
     const int total = ntiles * A.C;
     int id = blockIdx.x;
@@ -974,98 +976,104 @@ __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackC
     float *st = stage[wave];
 
     const int nblk = (g.nah + 7) / 8;
-    for (int b = wave; b < nblk; b += nwaves) {
-        float4 v[8][NL];
-        float lz[8], le[8], lo[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int a = min(8 * b + j, g.nah - 1);  // past the last angle: loaded, not gathered
-            const int2 r = const_ld(orgs, a);
-            const unsigned org =
-                4u * (unsigned)a * (unsigned)g.slab + (unsigned)(r.y >> 2) * line_bytes + 16u * (unsigned)r.x;
-#pragma unroll
-            for (int m = 0; m < NL; ++m) {
-                v[j][m] = make_float4(1.f, 1.f, 1.f, 1.f);
-                if (kb + RPL * m < NG) v[j][m] = buffer_ld4(rs, off0, org + (unsigned)(RPL * m) * line_bytes);
-            }
-            lz[j] = 1.f;
-            le[j] = lo[j] = 0.f;
-            if constexpr (WEIGHTED) lz[j] = buffer_ld(rz, 4u * (unsigned)bb, 4u * (unsigned)(a * g.nb + r.x));
-            if constexpr (PAIRED) {
-                // exp(-T) of ray (a, bin); the opposed ray (a + na/2, nb-1-bin) takes its weight
-                le[j] = buffer_ld(re, 4u * (unsigned)bb, 4u * (unsigned)(a * g.nb + r.x));
-                if constexpr (WEIGHTED)
-                    lo[j] = buffer_ld(rz, 4u * (unsigned)((a + g.nah) * g.nb + (g.nb - 1 - r.x) - bb), 0u);
-            }
-        }
-        float blk = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int a = 8 * b + j;
-            if (a >= g.nah) break;  // uniform
-            const float4 t0 = const_ld(T.angt, 2 * a), t1 = const_ld(T.angt, 2 * a + 1);
-            const int2 r = const_ld(orgs, a);
-            const float fb1 = (float)(r.x + HB), fk1 = (float)(r.y + 1);
-            const float ez = WEIGHTED ? le[j] * lo[j] : le[j];
-            auto put = [&](const float4 &x4, int kg) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float x = f4at(x4, t);
-                    float y;
-                    if constexpr (PAIRED) {
-                        const float ri = __builtin_amdgcn_rcpf(x);
-                        if constexpr (WEIGHTED)
-                            y = fmaf(ri, ez, x * lz[j]);
-                        else
-                            y = field ? x + ez : fmaf(ri, ez, x);
-                    } else {
-                        y = WEIGHTED ? x * lz[j] : x;
-                    }
-                    if constexpr (TAIL) y = (r.y + 4 * kg + t < g.nt) ? y : 0.f;  // the layout's padding rows
-                    st[(4 * kg + t) * PL + bb] = y;
-                }
-            };
-#pragma unroll
-            for (int m = 0; m < NL; ++m)
-                if (kb + RPL * m < NG) put(v[j][m], kb + RPL * m);
-            // the wave's own LDS: its operations run in order; the fences keep the compiler's order too
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const float c = t0.x, s = t0.y;
-            const float ub = t0.z, vb = t0.w;
-            const float Sj5 = fmaf(xc, t1.x, fmaf(yc, t1.y, cB5));
-            const float Tj5 = fmaf(yc, c, fmaf(xc, -s, cT5));
-            const float bcf = __builtin_amdgcn_fmed3f(floorf(Sj5), fb1, fb1 + (float)(PB - 1 - 2 * HB));
-            const float kcf = __builtin_amdgcn_fmed3f(floorf(Tj5), fk1, fk1 + (float)(kWavePK - 3));
-            const float sig = (bcf - g.cB) * g.bscale, tau = kcf - g.cT;
-            float du0, dv0;
-            window_offset<HB>(g, sig, tau, c, s, xc, yc, du0, dv0);
-            const float *base = st + (int)fmaf(kcf - fk1, (float)PL, bcf - fb1);  // window tap (-HB, -1)
-#pragma unroll
-            for (int db = -HB; db <= HB; ++db) {
-                const float dub = (db == 0) ? du0 : db == -1 ? du0 - ub : db == 1 ? du0 + ub : fmaf((float)db, ub, du0);
-                const float dvb = (db == 0) ? dv0 : db == -1 ? dv0 - vb : db == 1 ? dv0 + vb : fmaf((float)db, vb, dv0);
-                float part = 0.f;
-                float &sum = HB > 1 ? part : blk;
-#pragma unroll
-                for (int dk = -1; dk <= 1; ++dk) {
-                    const float du = (dk == 0) ? dub : (dk < 0 ? dub + s : dub - s);
-                    const float dv = (dk == 0) ? dvb : (dk < 0 ? dvb - c : dvb + c);
-                    sum = fmaf(hat2(du, dv), base[(dk + 1) * PL + (db + HB)], sum);
-                }
-                if (HB > 1) blk += part;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        sums[64 * b + lane] = blk;
-    }
-    __syncthreads();
-    if (wave > 0 || !pv) return;
     Comp acc{0.f, 0.f};
-    for (int b = 0; b < nblk; ++b) comp_add(acc, sums[64 * b + lane]);
+    for (int b0 = 0; b0 < nblk; b0 += kWaveSums) {
+        const int b1 = ROUNDS ? min(b0 + kWaveSums, nblk) : nblk;
+        for (int b = b0 + wave; b < b1; b += nwaves) {
+            float4 v[8][NL];
+            float lz[8], le[8], lo[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int a = min(8 * b + j, g.nah - 1);  // past the last angle: loaded, not gathered
+                const int2 r = const_ld(orgs, a);
+                const unsigned org =
+                    4u * (unsigned)a * (unsigned)g.slab + (unsigned)(r.y >> 2) * line_bytes + 16u * (unsigned)r.x;
+#pragma unroll
+                for (int m = 0; m < NL; ++m) {
+                    v[j][m] = make_float4(1.f, 1.f, 1.f, 1.f);
+                    if (kb + RPL * m < NG) v[j][m] = buffer_ld4(rs, off0, org + (unsigned)(RPL * m) * line_bytes);
+                }
+                lz[j] = 1.f;
+                le[j] = lo[j] = 0.f;
+                if constexpr (WEIGHTED) lz[j] = buffer_ld(rz, 4u * (unsigned)bb, 4u * (unsigned)(a * g.nb + r.x));
+                if constexpr (PAIRED) {
+                    // exp(-T) of ray (a, bin); the opposed ray (a + na/2, nb-1-bin) takes its weight
+                    le[j] = buffer_ld(re, 4u * (unsigned)bb, 4u * (unsigned)(a * g.nb + r.x));
+                    if constexpr (WEIGHTED)
+                        lo[j] = buffer_ld(rz, 4u * (unsigned)((a + g.nah) * g.nb + (g.nb - 1 - r.x) - bb), 0u);
+                }
+            }
+            float blk = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int a = 8 * b + j;
+                if (a >= g.nah) break;  // uniform
+                const float4 t0 = const_ld(T.angt, 2 * a), t1 = const_ld(T.angt, 2 * a + 1);
+                const int2 r = const_ld(orgs, a);
+                const float fb1 = (float)(r.x + HB), fk1 = (float)(r.y + 1);
+                const float ez = WEIGHTED ? le[j] * lo[j] : le[j];
+                auto put = [&](const float4 &x4, int kg) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float x = f4at(x4, t);
+                        float y;
+                        if constexpr (PAIRED) {
+                            const float ri = __builtin_amdgcn_rcpf(x);
+                            if constexpr (WEIGHTED)
+                                y = fmaf(ri, ez, x * lz[j]);
+                            else
+                                y = field ? x + ez : fmaf(ri, ez, x);
+                        } else {
+                            y = WEIGHTED ? x * lz[j] : x;
+                        }
+                        if constexpr (TAIL) y = (r.y + 4 * kg + t < g.nt) ? y : 0.f;  // the layout's padding rows
+                        st[(4 * kg + t) * PL + bb] = y;
+                    }
+                };
+#pragma unroll
+                for (int m = 0; m < NL; ++m)
+                    if (kb + RPL * m < NG) put(v[j][m], kb + RPL * m);
+                // the wave's own LDS: its operations run in order; the fences keep the compiler's order too
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const float c = t0.x, s = t0.y;
+                const float ub = t0.z, vb = t0.w;
+                const float Sj5 = fmaf(xc, t1.x, fmaf(yc, t1.y, cB5));
+                const float Tj5 = fmaf(yc, c, fmaf(xc, -s, cT5));
+                const float bcf = __builtin_amdgcn_fmed3f(floorf(Sj5), fb1, fb1 + (float)(PB - 1 - 2 * HB));
+                const float kcf = __builtin_amdgcn_fmed3f(floorf(Tj5), fk1, fk1 + (float)(kWavePK - 3));
+                const float sig = (bcf - g.cB) * g.bscale, tau = kcf - g.cT;
+                float du0, dv0;
+                window_offset<HB>(g, sig, tau, c, s, xc, yc, du0, dv0);
+                const float *base = st + (int)fmaf(kcf - fk1, (float)PL, bcf - fb1);  // window tap (-HB, -1)
+#pragma unroll
+                for (int db = -HB; db <= HB; ++db) {
+                    const float dub = (db == 0) ? du0 : db == -1 ? du0 - ub : db == 1 ? du0 + ub : fmaf((float)db, ub, du0);
+                    const float dvb = (db == 0) ? dv0 : db == -1 ? dv0 - vb : db == 1 ? dv0 + vb : fmaf((float)db, vb, dv0);
+                    float part = 0.f;
+                    float &sum = HB > 1 ? part : blk;
+#pragma unroll
+                    for (int dk = -1; dk <= 1; ++dk) {
+                        const float du = (dk == 0) ? dub : (dk < 0 ? dub + s : dub - s);
+                        const float dv = (dk == 0) ? dvb : (dk < 0 ? dvb - c : dvb + c);
+                        sum = fmaf(hat2(du, dv), base[(dk + 1) * PL + (db + HB)], sum);
+                    }
+                    if (HB > 1) blk += part;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            sums[64 * (b - b0) + lane] = blk;
+        }
+        __syncthreads();
+        if (wave == 0)
+            for (int b = b0; b < b1; ++b) comp_add(acc, sums[64 * (b - b0) + lane]);
+        if (b1 == nblk) break;
+        __syncthreads();  // the sums are read
+    }
+    if (wave > 0 || !pv) return;
     back_epilogue(g, A, mode, o, comp_value(acc));
 }
 #endif
@@ -1107,33 +1115,37 @@ static hipError_t back_col4(const DevGeom &g, const BackCfg &bc, const BackArgs 
     return hipGetLastError();
 }
 
-template <bool PAIRED, bool TAIL, int HB>
+template <bool PAIRED, bool TAIL, int HB, bool ROUNDS>
 static void back_wave_go(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     const int nblk = (g.nah + 7) / 8;
     const dim3 grid((unsigned)(bc.tiles_x * bc.tiles_y * a.C)), block((unsigned)(64 * std::min(nblk, kWaveBlocks)));
     if (mode == BACK_SENS || mode == BACK_FIELD)
-        hipLaunchKernelGGL((k_back_wave<false, PAIRED, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_wave<false, PAIRED, TAIL, HB, ROUNDS>), grid, block, bc.lds, st, g, bc, a, mode);
     else
-        hipLaunchKernelGGL((k_back_wave<true, PAIRED, TAIL, HB>), grid, block, bc.lds, st, g, bc, a, mode);
+        hipLaunchKernelGGL((k_back_wave<true, PAIRED, TAIL, HB, ROUNDS>), grid, block, bc.lds, st, g, bc, a, mode);
 }
 
-static hipError_t back_wave(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
-    if (bc.tw != 8 || bc.th != 8 || bc.cg != 1 || (a.E && !pairs_ok(g, bc)) ||
-        bc.lds < (size_t)256 * ((g.nah + 7) / 8))
-        return hipErrorInvalidValue;
+template <bool ROUNDS>
+static hipError_t back_wave_window(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
     if (a.E)
-        back_wave_go<true, false, 1>(g, bc, a, mode, st);
+        back_wave_go<true, false, 1, ROUNDS>(g, bc, a, mode, st);
     else if (bc.hb == 1 && !(g.nt & 3))
-        back_wave_go<false, false, 1>(g, bc, a, mode, st);
+        back_wave_go<false, false, 1, ROUNDS>(g, bc, a, mode, st);
     else if (bc.hb == 1)
-        back_wave_go<false, true, 1>(g, bc, a, mode, st);
+        back_wave_go<false, true, 1, ROUNDS>(g, bc, a, mode, st);
     else if (bc.hb == 2)
-        back_wave_go<false, true, 2>(g, bc, a, mode, st);
+        back_wave_go<false, true, 2, ROUNDS>(g, bc, a, mode, st);
     else if (bc.hb == 3)
-        back_wave_go<false, true, 3>(g, bc, a, mode, st);
+        back_wave_go<false, true, 3, ROUNDS>(g, bc, a, mode, st);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+static hipError_t back_wave(const DevGeom &g, const BackCfg &bc, const BackArgs &a, int mode, hipStream_t st) {
+    if (bc.tw != 8 || bc.th != 8 || bc.cg != 1 || (a.E && !pairs_ok(g, bc)) || bc.lds != wave_lds(g.nah))
+        return hipErrorInvalidValue;
+    return g.nah > 8 * kWaveSums ? back_wave_window<true>(g, bc, a, mode, st) : back_wave_window<false>(g, bc, a, mode, st);
 }
 
 template <int CG>

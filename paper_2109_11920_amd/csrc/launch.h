@@ -120,11 +120,17 @@ constexpr int kSlidPitch = 34;  // its LDS row pitch, in slots
 // Staged bins of the column-group gather by its bin half window: a 16 x 16 tile's footprint is at most
 // ceil(15 sqrt(2) n_bins / n) + 2 hb + 4 bins wide, n_bins / n at most 1.06, 1.76 and 2.
 constexpr int col4_bins(int hb) { return hb == 1 ? kSlidBlock : hb == 2 ? 48 : 64; }
-// Few candidates (8 x 8 tiles): staged samples, staged bins (ceil(7 sqrt(2) n_bins / n) + 2 hb + 3 at most), and
-// waves per workgroup at most (one per 8 held angles).
+// Few candidates (8 x 8 tiles): staged samples, staged bins (ceil(7 sqrt(2) n_bins / n) + 2 hb + 3 at most),
+// waves per workgroup at most (one per 8 held angles), and the 8-angle blocks at most whose sums (64 pixels each) are
+// in LDS at a time (128 KiB, with the staged blocks 149 at most).
 constexpr int kWavePK = 20;
 constexpr int wave_bins(int hb) { return hb == 1 ? 16 : 32; }
 constexpr int kWaveBlocks = 8;
+constexpr int kWaveSums = 512;
+constexpr size_t wave_lds(int nah) {
+    const int blocks = (nah + 7) / 8;
+    return sizeof(float) * 64 * (size_t)(blocks < kWaveSums ? blocks : kWaveSums);
+}
 
 struct BackArgs {
     const float *att;     // [C] attenuation tensors (4 x 8-block slabs)

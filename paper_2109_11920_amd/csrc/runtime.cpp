@@ -773,7 +773,7 @@ static void back_plan(boac_ctx *ctx, const boac_geom &g, int C, BackCfg *bc, int
         bc->cg = 1;
         bc->slid = 3;
         back_fill(g, bc);
-        bc->lds = (size_t)256 * ((nah + 7) / 8);  // the 8-angle blocks' sums of 64 pixels
+        bc->lds = wave_lds(nah);
     }
 }
 
