@@ -79,6 +79,7 @@ static boac_status noalloc_base(int device, void **out) {
 
 // ------------------------------------------------------------------ validation (no HIP calls)
 static constexpr size_t kLdsBudget = 160 * 1024 - 256;  // gfx950: 160 KiB of LDS per workgroup
+static constexpr size_t kPersistLds = kLdsBudget - 1024;  // the same for an item of the persistent executor
 
 // Elements per angle of an attenuation tensor stored in 4 x 8 (sample x bin) blocks.
 static size_t att_slab(const boac_geom &g) {
@@ -471,7 +472,8 @@ static constexpr int band_count(int n, int comps) {
     const int rows = (int)(kLdsBudget / pitch_bytes) - 1;  // assigned rows per band (staged = rows + 1)
     return (n + 2 + rows - 1) / rows;                     // assigned range [-1, n+1)
 }
-static void make_bands(int n, int comps, RayCfg *rc, Bands *bands) {
+// budget: the LDS that a stage with an odd pitch may take (the persistent executor keeps some for itself).
+static void make_bands(int n, int comps, size_t budget, RayCfg *rc, Bands *bands) {
     const int count = band_count(n, comps);
     const int span = n + 2;  // assigned range [-1, n+1)
     // the same number of bands with rows spread evenly: the last band is not empty and no band
@@ -480,10 +482,10 @@ static void make_bands(int n, int comps, RayCfg *rc, Bands *bands) {
     bands->rows = (span + count - 1) / count;
     rc->single = count == 1;
     // an odd pitch where it fits: the lanes of a wave that run across the rows (a ray's neighbours, at angles
-    // along the image's columns) then read different LDS banks. 37 candidates at 109 pixels and 90 angles
+    // along the image's columns) then read different LDS banks. 37 candidates at 109 pixels and 45 held angles
     // (pitch 112: every other row in the same banks), projection of pairs: 60.7 us, 40.4 with 113.
     const size_t odd = (size_t)((n + 3) | 1);
-    bands->pitch = odd * 4 * comps * (size_t)(bands->rows + 1) <= kLdsBudget ? (int)odd : n + 3;
+    bands->pitch = odd * 4 * comps * (size_t)(bands->rows + 1) <= budget ? (int)odd : n + 3;
     rc->lds = (size_t)bands->pitch * 4 * comps * (size_t)(bands->rows + 1);
 }
 
@@ -525,7 +527,7 @@ static double ray_cost(const RayCost &k, int n_cu, int n_samples, size_t lds, lo
 
 // nah: angles whose rays the kernels walk (n_angles, or half of them with opposed-ray pairing).
 static void ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, RayCfg *rc, Bands *bands, int nah) {
-    make_bands(g.n, comps, rc, bands);
+    make_bands(g.n, comps, ctx->persist_plans ? kPersistLds : kLdsBudget, rc, bands);
     const int nrays = nah * g.n_bins;
     // the paired forward projection where both images fit one stage
     const bool pair_fits = comps == 1 && rc->single && 2 * rc->lds <= kLdsBudget && C >= 2;
@@ -2115,7 +2117,7 @@ static boac_status persist_record(boac_ctx *ctx, const boac_slice *h_in, int32_t
         }
         if (!any) break;
     }
-    if (lds > kLdsBudget - 1024)
+    if (lds > kPersistLds)
         return fail(BOAC_ENOTSUP, "persistent batch: an item needs %u bytes of LDS", lds);
     return BOAC_OK;
 }
