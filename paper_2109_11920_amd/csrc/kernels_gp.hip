@@ -594,7 +594,8 @@ __global__ __launch_bounds__(1024) void k_greedy(const double *__restrict__ pts,
     __shared__ double wv[2][16];
     __shared__ int wi[2][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float reach = sqrtf((float)ex2) * 1.00001f;
+    // the root in doubles (ex2 may be below the floats), with a floor for coordinates that are
+    const float reach = (float)sqrt(ex2) * 1.00001f + 1e-30f;
     double val[E];  // -infinity: dropped, or past the end
     unsigned alive = 0xffffffffu;
     double mx = -INFINITY;
