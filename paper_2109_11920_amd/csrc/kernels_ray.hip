@@ -204,13 +204,52 @@ __global__ __launch_bounds__(1024) void k_att(DevGeom g, Bands bands, int rpt, i
 
 // The same for few candidates: a ray's samples over kScanLanes lanes of one wave (single-stage images). The
 // ray is walked from the detector end in rounds of kScanLanes 4-sample groups, lane j sampling the j-th group
-// of the round; every lane then runs the round's compensated sum sample by sample (the other lanes' values by
-// shuffles), noting it where its own group begins, so every att has k_att's bits. The exponentials and stores
-// are spread again; the 8 lanes of a ray and the 8 rays of a wave (consecutive bins) write whole 128-byte
-// lines. passes: rays per lane group handled in turn, so that one image stage serves many rays.
+// of the round; every lane then runs the round's compensated sum sample by sample, noting it where its own group
+// begins, so every att has k_att's bits. The exponentials and stores are spread again; the 8 lanes of a ray and the
+// 8 rays of a wave (consecutive bins) write whole 128-byte lines. passes: rays per lane group handled in turn, so
+// that one image stage serves many rays.
 constexpr int kScanLanes = 8;
 
 #ifndef BOAC_BODIES_ONLY
+// x of another lane by the data-parallel path; dpp_banks: in the 4-lane banks of BANKS only, elsewhere this lane's.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL, int BANKS>
+__device__ __forceinline__ float dpp_banks(float x) {
+    const int v = (int)__float_as_uint(x);
+    return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, BANKS, false));
+}
+// sum + x of the ray's samples one by one, lane 0's x[3] to x[0] first, lane 7's last; returned: the sum before this
+// lane's own. An addition reads the sample from its lane through the data-parallel path, which reaches the four lanes
+// of a quad: the other quad's samples are brought to the same places first. (Each sample by a shuffle through the LDS
+// unit, with its whole compensated step in every lane: one candidate at 128 pixels and 128 angles 12.8 us, 10.4 so;
+// four 22.7, 19.1; eight at 64 and 64 9.2, 8.5.)
+__device__ __forceinline__ float scan_run(float &sum, const float (&x)[4], int lane) {
+    float half[2][4];  // the samples of lanes 0..3 and 4..7, by place in the quad
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        half[0][q] = dpp_banks<0x114, 0xa>(x[q]);  // lanes 4..7 of each 8: from 4 lanes below
+        half[1][q] = dpp_banks<0x104, 0x5>(x[q]);  // lanes 0..3: from 4 lanes above
+    }
+    float own = sum;
+    auto lane4 = [&](auto place, int h) {
+        constexpr int p = decltype(place)::value;
+        own = (lane == 4 * h + p) ? sum : own;
+#pragma unroll
+        for (int q = 3; q >= 0; --q) sum += dpp<p * 0x55>(half[h][q]);
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        lane4(std::integral_constant<int, 0>{}, h);
+        lane4(std::integral_constant<int, 1>{}, h);
+        lane4(std::integral_constant<int, 2>{}, h);
+        lane4(std::integral_constant<int, 3>{}, h);
+    }
+    return own;
+}
+
 __global__ __launch_bounds__(256) void k_att_scan(DevGeom g, Band band, int passes, int chunks, int C,
                                                   const float *__restrict__ mu, float *__restrict__ att,
                                                   size_t img_cs, size_t att_cs, float *__restrict__ E,
@@ -225,7 +264,6 @@ __global__ __launch_bounds__(256) void k_att_scan(DevGeom g, Band band, int pass
     const int nrays = g.nah * g.nb;
     const int rpp = blockDim.x / kScanLanes;
     const int lane = threadIdx.x & (kScanLanes - 1);
-    const int base = (threadIdx.x & (kWave - 1)) & ~(kScanLanes - 1);
     const int ng = (g.nt + 3) >> 2;
     const int rounds = (ng + kScanLanes - 1) / kScanLanes;
     const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(att + cand * att_cs, (unsigned)(4 * att_cs));
@@ -249,24 +287,22 @@ __global__ __launch_bounds__(256) void k_att_scan(DevGeom g, Band band, int pass
                 const float w = bilinear_whole(lds, U, V, nf, pitch);
                 m[q] = (live && grp >= 0 && k < g.nt) ? w : 0.f;  // no sample: adds nothing
             }
-            Comp own{0.f, 0.f};
+            // comp_add sample by sample in two runs: the sums s, whose roundings each lane finds for its own samples,
+            // then the sums e of those
+            float before[4], err[4], t = scan_run(T.s, m, lane);
 #pragma unroll
-            for (int j = 0; j < kScanLanes; ++j) {
-                if (lane == j) own = T;
-#pragma unroll
-                for (int q = 3; q >= 0; --q) comp_add(T, __shfl(m[q], base + j, kWave));
+            for (int q = 3; q >= 0; --q) {
+                before[q] = t;
+                two_sum(before[q], m[q], t, err[q]);
             }
+            float own_e = scan_run(T.e, err, lane);
             if (live && grp >= 0) {
                 float e[4];
 #pragma unroll
                 for (int q = 3; q >= 0; --q) {
-                    const int k = 4 * grp + q;
-                    e[q] = 0.f;
-                    if (k < g.nt) {
-                        const float L = g.dx * (fmaf(0.5f, m[q], own.s) + own.e);
-                        e[q] = fmaxf(expf(-L), kMinNormal);
-                        comp_add(own, m[q]);
-                    }
+                    const float L = g.dx * (fmaf(0.5f, m[q], before[q]) + own_e);
+                    e[q] = (4 * grp + q < g.nt) ? fmaxf(expf(-L), kMinNormal) : 0.f;
+                    own_e += err[q];
                 }
                 buffer_st4_stream(rs, roff + 4u * att_row(g, 4 * grp), 0u, make_float4(e[0], e[1], e[2], e[3]));
             }

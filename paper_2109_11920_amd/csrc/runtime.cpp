@@ -637,16 +637,18 @@ static void new_ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, Ra
                 if (wgs <= ctx->n_cu) break;
             }
     }
-    // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give half the
-    // CUs a workgroup of 256, a quarter where an image takes over half the LDS, which each of the many small
+    // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give three fifths of
+    // the CUs a workgroup of 256, a quarter where an image takes over half the LDS, which each of the many small
     // workgroups stages (single stage; BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group
-    // as still give every CU two workgroups (at most 32). With the projection that follows, at 96 pixels and 96
-    // angles: 6 candidates 25 us, one thread per ray 33; 13 candidates 43 against 36. 128 pixels, 128 angles: 4
-    // candidates 36 against 41, 6 candidates 67 against 51. 192 pixels, 96 angles: 2 candidates 76 against 68.
+    // as still give every CU two workgroups (at most 32). By the workgroups that one thread per ray would give, against
+    // it: 120 (64 pixels, 45 angles, 10 candidates) 12.3 us against 14.1, 144 (61, 36, 16) 15.4 against 16.3, 160 (128,
+    // 160, 4) 26.9 against 24.6, 180 (80, 45, 12) 17.5 against 16.1; large images: 32 (160, 24, 4) 12.9 against 25.3,
+    // 72 (160, 8, 24) 22.4 against 25.4, 90 (150, 25, 6) 50.8 against 35.6.
     rc->scan_passes = rc->scan_chunks = 0;
     const char *ea = std::getenv("BOAC_ATT_SCAN");
+    const long wide = (long)((nrays + 255) / 256) * C;
     if (!(ea && ea[0] == '0') && comps == 1 && rc->single &&
-        (long)((nrays + 255) / 256) * C * (rc->lds > kLdsBudget / 2 ? 4 : 2) <= ctx->n_cu) {
+        (rc->lds > kLdsBudget / 2 ? 4 * wide <= ctx->n_cu : 5 * wide <= 3L * ctx->n_cu)) {
         const long total = (nrays + 31) / 32;
         rc->scan_passes = (int)std::min<long>(32, std::max<long>(1, total * C / (2L * ctx->n_cu)));
         rc->scan_chunks = (int)((total + rc->scan_passes - 1) / rc->scan_passes);
