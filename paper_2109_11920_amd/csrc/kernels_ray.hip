@@ -1203,8 +1203,9 @@ constexpr int kSplitLanes = 8;
 constexpr int kSplitCpl = 2;  // chunks per lane
 
 #ifndef BOAC_BODIES_ONLY
-template <int MODE, bool PAIRED>
-__global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chunks, int C, FwdArgs A) {
+// AHEAD: the first loads go out before the image is staged, and more of the image at a time (see the plan).
+template <int MODE, bool PAIRED, bool AHEAD>
+__global__ __launch_bounds__(256, AHEAD ? 1 : 6) void k_fwd_split(DevGeom g, Band band, int chunks, int C, FwdArgs A) {
     extern __shared__ float lds[];
     __shared__ float red[32];
     int cand, chunk;
@@ -1227,15 +1228,16 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
     const int nck = (g.nt + KC - 1) / KC;
     // the kernel is one chain of memory round trips: the first chunk of att, exp(-T) and the counts are on
     // their way while the image is staged
-    float4 v0[KG];
+    float4 v0[AHEAD ? KG : 1];
     const bool has0 = live && lane < nck;
+    if constexpr (AHEAD)
 #pragma unroll
-    for (int q = 0; q < KG; ++q)
-        v0[q] = (has0 && lane * KC + 4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, lane * KC + 4 * q)) : z4;
+        for (int q = 0; q < KG; ++q)
+            v0[q] = (has0 && lane * KC + 4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, lane * KC + 4 * q)) : z4;
     const float e_ray = (PAIRED && live) ? A.E[cand * A.e_cs + ray] : 0.f;
     const float S = live ? fwd_meas<MODE>(A, ray) : 0.f;
     const float S2 = (PAIRED && live) ? fwd_meas<MODE>(A, opp) : 0.f;
-    stage_whole<16>(A.img + cand * A.img_cs, g.n, band, lds);
+    stage_whole<AHEAD ? 16 : 8>(A.img + cand * A.img_cs, g.n, band, lds);
     __syncthreads();
 
     float part[kSplitCpl], part2[kSplitCpl];
@@ -1248,7 +1250,7 @@ __global__ __launch_bounds__(256) void k_fwd_split(DevGeom g, Band band, int chu
         float4 v[KG];
 #pragma unroll
         for (int q = 0; q < KG; ++q)
-            v[q] = h == 0 ? v0[q]
+            v[q] = (AHEAD && h == 0) ? v0[AHEAD ? q : 0]
                           : (k0 + 4 * q < g.nt) ? buffer_ld4_stream(rs, roff, 4u * att_row(g, k0 + 4 * q)) : z4;
         float tau = (float)k0 - g.cT;
         float p = 0.f, p2 = 0.f;
@@ -1333,8 +1335,13 @@ template <int MODE, bool PAIRED>
 static void fwd_mode(const DevGeom &g, const RayCfg &rc, const Bands &bands, const FwdArgs &a, int C,
                      hipStream_t st) {
     if (rc.split_chunks > 0 && (MODE != FWD_NLL || rc.split_nll)) {
-        hipLaunchKernelGGL((k_fwd_split<MODE, PAIRED>), dim3((unsigned)(rc.split_chunks * C)), dim3(256), rc.lds, st, g,
-                           bands.band(0, g.n), rc.split_chunks, C, a);
+        const dim3 grid((unsigned)(rc.split_chunks * C));
+        if (rc.split_ahead)
+            hipLaunchKernelGGL((k_fwd_split<MODE, PAIRED, true>), grid, dim3(256), rc.lds, st, g, bands.band(0, g.n),
+                               rc.split_chunks, C, a);
+        else
+            hipLaunchKernelGGL((k_fwd_split<MODE, PAIRED, false>), grid, dim3(256), rc.lds, st, g, bands.band(0, g.n),
+                               rc.split_chunks, C, a);
         return;
     }
     if (rc.pair && rc.single && a.img_comps == 1 && C >= 2)

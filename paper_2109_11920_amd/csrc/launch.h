@@ -37,6 +37,7 @@ struct RayCfg {
     bool pair;   // forward projection of two candidates per workgroup (single stage, 2 lds bytes)
     int split_chunks;  // > 0: few candidates: the projection splits each ray over 8 lanes, 32 rays per
                        // 256-thread workgroup, split_chunks workgroups per candidate
+    bool split_ahead;  // with its first loads ahead of the image stage
     bool split_nll;    // the likelihood's projection too (its partials: split_chunks per candidate)
     int nll_chunks() const { return split_nll ? split_chunks : chunks; }
     // few candidates: attenuation build with a ray over 8 lanes (single stage; scan_passes 0 = one thread per

@@ -615,6 +615,11 @@ static void new_ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, Ra
     if (split_on && C <= kFewCand && comps == 1 && rc->single && g.n_samples <= 256 &&
         (long)((nrays + 255) / 256) * C < ctx->n_cu)
         rc->split_chunks = (nrays + 31) / 32;
+    // its first loads ahead of the image stage where its workgroups (8 to one of 256 rays) are two to a CU at most: the
+    // variant takes 140 registers, three waves a SIMD, the other 62 to 68. By the workgroups of 256 rays, ahead against
+    // not: 24 (128 pixels, 96 angles, 1 candidate) 9.4 us against 9.7, 55 (109, 25, 5) 14.2 against 14.1, 90 (96, 96, 5)
+    // 11.9 against 11.2, 128 (64, 128, 8) 12.8 against 10.4, 224 (32, 217, 8) 14.0 against 10.2
+    rc->split_ahead = 4L * ((nrays + 255) / 256) * C <= ctx->n_cu;
     // its likelihood partials, one per 32 held rays, are within the no-allocation scratch's estimate (one per 64
     // rays of every angle) only with half the angles held
     rc->split_nll = rc->split_chunks > 0 && (!ctx->arena || nah < g.n_angles);
