@@ -139,10 +139,10 @@ __device__ void run_task(const TaskRec &T, int item, float *lds, float *red) {
         case T_ATT: {
             const auto &A = T.u.att;
             if (T.variant & 1)
-                k_att_body<true>(item, lds, A.r.g, A.r.bands, A.r.rpt, A.r.chunks, A.r.C, A.mu, A.att, A.img_cs,
+                k_att_body<true>(item, lds, A.r.g, A.r.bands, A.r.rpt, A.r.chunks, A.up, A.r.C, A.mu, A.att, A.img_cs,
                                  A.att_cs, A.E, A.e_cs);
             else
-                k_att_body<false>(item, lds, A.r.g, A.r.bands, A.r.rpt, A.r.chunks, A.r.C, A.mu, A.att, A.img_cs,
+                k_att_body<false>(item, lds, A.r.g, A.r.bands, A.r.rpt, A.r.chunks, A.up, A.r.C, A.mu, A.att, A.img_cs,
                                   A.att_cs, A.E, A.e_cs);
             break;
         }

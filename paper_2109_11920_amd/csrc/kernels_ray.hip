@@ -62,13 +62,15 @@ __device__ __forceinline__ void comp_put(Comp (&v)[N], int j, const Comp &c) {
 // L_k = dx (m_k / 2 + T), the 4 samples of a group (k a multiple of 4) as one 16-byte store, padding rows 0.
 // Bound by the stores (268M samples, 256 candidates at 128 pixels and 128 angles: 263 us, 4.1 TB/s; over 8
 // lanes per ray, with its shuffles, 381 us).
-// Row bands (!SINGLE): V is monotone along a ray, so the ray meets the bands in the order of its direction
-// and each is staged once for the rays of that direction; a ray keeps its sum and its open group in registers
-// from band to band. Bound by its vector work. 32 candidates at 256 pixels and 128 angles: 262 us; with
-// consecutive rays in a workgroup (see band_ray) and a test and a branch per sample 355; storing m band by band
-// and scanning it in a second pass 562.
+// Row bands (!SINGLE): V is monotone along a ray, so the ray meets the bands in the order of its direction, and a
+// workgroup takes rays of one direction (the first `up` of a candidate's chunks those along which V grows), dealt to
+// the workgroups of that direction by waves: each band is staged once, and a ray keeps its sum and its open group in
+// registers from band to band. Bound by its vector work; few rays by the stages' latency. 32 candidates at 256 pixels and
+// 128 angles: 265 us; with both directions in a workgroup, so 2 bands - 1 stages of which a ray sits out all but `bands`,
+// 277; storing m band by band and scanning it in a second pass 556. One candidate at 400 pixels and 20 angles: 283 us,
+// 447 and 347.
 template <bool SINGLE>
-__device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const Bands &bands, int rpt, int chunks, int C,
+__device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const Bands &bands, int rpt, int chunks, int up, int C,
                                              const float *__restrict__ mu, float *__restrict__ att, size_t img_cs,
                                              size_t att_cs, float *__restrict__ E, size_t e_cs) {
     int cand, chunk;
@@ -120,8 +122,12 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
             if (E) E[cand * e_cs + ray] = expf(-g.dx * comp_value(T));
         }
     } else {
-        // rays along which V grows with k (cos >= 0) take the last band first, the others the first; the rays
-        // of a workgroup are of both kinds, and the middle visit serves both
+        // rays along which V grows with k (cos >= 0) take the last band first, the others the first
+        const bool grows = chunk < up;
+        const int mine = grows ? chunk : chunk - up, of = grows ? up : chunks - up;
+        const AttAngles angles = att_angles(g.na, g.nah);
+        const int rays = (grows ? angles.up : g.nah - angles.up) * g.nb;
+        const int first = grows ? angles.first_up : angles.first_down;
         Comp T[kMaxRpt];
         float4 open[kMaxRpt];  // the open group: its samples so far
 #pragma unroll
@@ -129,19 +135,19 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
             T[j] = Comp{0.f, 0.f};
             open[j] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        for (int v = 0; v < 2 * bands.count - 1; ++v) {
-            const Band band = bands.band(v < bands.count ? bands.count - 1 - v : v - (bands.count - 1), g.n);
+        for (int v = 0; v < bands.count; ++v) {
+            const Band band = bands.band(grows ? bands.count - 1 - v : v, g.n);
             const BandTap bt = band_tap(band, nf, pitch);
             __syncthreads();
             stage_band<1>(img, g.n, band, lds);
             __syncthreads();
 #pragma unroll 1
             for (int j = 0; j < rpt; ++j) {
-                const int ray = band_ray(chunk, chunks, j);
-                if (ray >= nrays) continue;
-                const int a = ray / g.nb, b = ray - a * g.nb;
+                const int i = band_ray(mine, of, j);
+                if (i >= rays) continue;
+                const int p = i / g.nb, b = i - p * g.nb;
+                const int a = first + p < g.nah ? first + p : first + p - g.nah, ray = a * g.nb + b;
                 const float2 cs = g.trig[a];
-                if (cs.x >= 0.f ? v >= bands.count : v < bands.count - 1) continue;
                 float Ub, Vb;
                 ray_base(g, sigma_of(g, b), cs.x, cs.y, Ub, Vb);
                 int k0, k1;
@@ -186,7 +192,7 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
                     open[i].z = (i == j) ? o.z : open[i].z;
                     open[i].w = (i == j) ? o.w : open[i].w;
                 }
-                if (E && (cs.x >= 0.f ? band.first : band.last)) E[cand * e_cs + ray] = expf(-g.dx * comp_value(t));
+                if (E && v == bands.count - 1) E[cand * e_cs + ray] = expf(-g.dx * comp_value(t));
             }
         }
     }
@@ -194,11 +200,11 @@ __device__ __forceinline__ void k_att_body(int bid, float *lds, DevGeom g, const
 
 #ifndef BOAC_BODIES_ONLY
 template <bool SINGLE>
-__global__ __launch_bounds__(1024) void k_att(DevGeom g, Bands bands, int rpt, int chunks, int C,
+__global__ __launch_bounds__(1024) void k_att(DevGeom g, Bands bands, int rpt, int chunks, int up, int C,
                                              const float *__restrict__ mu, float *__restrict__ att, size_t img_cs,
                                              size_t att_cs, float *__restrict__ E, size_t e_cs) {
     extern __shared__ float lds[];
-    k_att_body<SINGLE>(blockIdx.x, lds, g, bands, rpt, chunks, C, mu, att, img_cs, att_cs, E, e_cs);
+    k_att_body<SINGLE>(blockIdx.x, lds, g, bands, rpt, chunks, up, C, mu, att, img_cs, att_cs, E, e_cs);
 }
 #endif
 
@@ -1311,8 +1317,10 @@ hipError_t launch_att(const DevGeom &g, const RayCfg &rc, const Bands &bands, co
             return record_unsupported(r, "attenuation build planned with other than 1024 threads");
         t.kind = T_ATT;
         t.variant = rc.single ? 1 : 0;
-        t.u.att = {RayTask{g, bands, rc.rpt, rc.chunks, C}, mu, att, img_cs, att_cs, E, e_cs};
-        t.grid = t.items = rc.chunks * C;
+        int up = 0;
+        const int chunks = rc.single ? rc.chunks : att_band_chunks(g.na, g.nah, g.nb, rc.block * rc.rpt, up);
+        t.u.att = {RayTask{g, bands, rc.rpt, chunks, C}, mu, att, img_cs, att_cs, E, e_cs, up};
+        t.grid = t.items = chunks * C;
         t.lds = (unsigned)rc.lds;
         return record_task(r, t);
     }
@@ -1324,10 +1332,13 @@ hipError_t launch_att(const DevGeom &g, const RayCfg &rc, const Bands &bands, co
     if (rc.single) {
         const int per = rc.att_block * rc.att_rpt, chunks = (g.nah * g.nb + per - 1) / per;
         hipLaunchKernelGGL(k_att<true>, dim3((unsigned)chunks * (unsigned)C), dim3(rc.att_block), rc.lds, st, g, bands,
-                           rc.att_rpt, chunks, C, mu, att, img_cs, att_cs, E, e_cs);
-    } else
-        hipLaunchKernelGGL(k_att<false>, ray_grid(rc, C), dim3(rc.block), rc.lds, st, g, bands, rc.rpt, rc.chunks,
-                           C, mu, att, img_cs, att_cs, E, e_cs);
+                           rc.att_rpt, chunks, 0, C, mu, att, img_cs, att_cs, E, e_cs);
+    } else {
+        int up;
+        const int chunks = att_band_chunks(g.na, g.nah, g.nb, rc.att_block * rc.att_rpt, up);
+        hipLaunchKernelGGL(k_att<false>, dim3((unsigned)chunks * (unsigned)C), dim3(rc.att_block), rc.lds, st, g, bands, rc.att_rpt,
+                           chunks, up, C, mu, att, img_cs, att_cs, E, e_cs);
+    }
     return hipGetLastError();
 }
 

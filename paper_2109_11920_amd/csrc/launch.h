@@ -43,8 +43,28 @@ struct RayCfg {
     // few candidates: attenuation build with a ray over 8 lanes (single stage; scan_passes 0 = one thread per
     // ray): scan_passes rays per lane group, scan_chunks workgroups of 256 threads per candidate
     int scan_passes, scan_chunks;
-    int att_block, att_rpt;  // single stage: the attenuation build's own workgroups
+    int att_block, att_rpt;  // the attenuation build's own workgroups
 };
+
+// The held angles (the first nah of na over the full circle) by the sign of their cosine: `up` of them have a positive
+// one, from first_up on (around the circle), the others from first_down. A cosine of 0 may be in either.
+struct AttAngles {
+    int up, first_up, first_down;
+};
+__host__ __device__ __forceinline__ AttAngles att_angles(int na, int nah) {
+    const int low = (na + 3) / 4, high = (3 * na + 3) / 4;  // cos > 0: a < na / 4 or a > 3 na / 4
+    AttAngles r;
+    r.up = (low < nah ? low : nah) + (high < nah ? nah - high : 0);
+    r.first_up = high < nah ? high : 0;
+    r.first_down = low;
+    return r;
+}
+// Chunks of `per` rays for a candidate's attenuation build by row bands; up: the first ones, of the angles of `up`.
+inline int att_band_chunks(int na, int nah, int nb, int per, int &up) {
+    const AttAngles a = att_angles(na, nah);
+    up = (a.up * nb + per - 1) / per;
+    return up + ((nah - a.up) * nb + per - 1) / per;
+}
 
 enum FwdMode { FWD_PROJ = 0, FWD_RATIO = 1, FWD_NLL = 2 };
 
@@ -228,7 +248,7 @@ struct TaskRec {
     union {
         struct { DevGeom g; const float *cand; float delta_r; float *mu; size_t img_cs; uint32_t *status; float *ones; int nbx; } raster;
         struct { DevGeom g; const float *cand; float delta_r; const float *mubar; size_t img_cs; float *grad; } raster_adj;
-        struct { RayTask r; const float *mu; float *att; size_t img_cs, att_cs; float *E; size_t e_cs; } att;
+        struct { RayTask r; const float *mu; float *att; size_t img_cs, att_cs; float *E; size_t e_cs; int up; } att;
         struct { RayTask r; FwdArgs A; } fwd;
         struct { RayTask r; SweepArgs A; } sweep;
         struct { RayTask r; TailArgs A; } tail;

@@ -641,14 +641,33 @@ static void new_ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, Ra
                 }
                 if (wgs <= ctx->n_cu) break;
             }
+    } else if (comps == 1) {
+        // row bands, rays of one direction to a workgroup: the projection's model with constants of its own, fitted to
+        // sweeps of every block of 256 to 1024 threads and 1 to 4 rays per thread at 22 shapes (200 to 512 pixels, 8
+        // to 256 angles, 1 to 50 candidates): within 4% of the best measured choice on average, 18% at worst
+        double best = 0.0;
+        for (int block = 1024; block >= 256; block -= 64)
+            for (int rpt = 1; rpt <= 4; ++rpt) {
+                int up;
+                const long wgs = (long)att_band_chunks(g.n_angles, nah, g.n_bins, block * rpt, up) * C;
+                const double w = block / 64;
+                const double cost = (double)((wgs + ctx->n_cu - 1) / ctx->n_cu) *
+                                    (rpt * (g.n_samples / 16.0) * (3.87 + 1.18 * w) +
+                                     0.094 * bands->count * (double)rc->lds / (64.0 * w));
+                if (best == 0.0 || cost < best) {
+                    best = cost;
+                    rc->att_block = block;
+                    rc->att_rpt = rpt;
+                }
+            }
     }
     // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give three fifths of
-    // the CUs a workgroup of 256, a quarter where an image takes over half the LDS, which each of the many small
-    // workgroups stages (single stage; BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group
-    // as still give every CU two workgroups (at most 32). By the workgroups that one thread per ray would give, against
-    // it: 120 (64 pixels, 45 angles, 10 candidates) 12.3 us against 14.1, 144 (61, 36, 16) 15.4 against 16.3, 160 (128,
-    // 160, 4) 26.9 against 24.6, 180 (80, 45, 12) 17.5 against 16.1; large images: 32 (160, 24, 4) 12.9 against 25.3,
-    // 72 (160, 8, 24) 22.4 against 25.4, 90 (150, 25, 6) 50.8 against 35.6.
+    // the CUs a workgroup of 256, a quarter where an image takes over half the LDS, which each of the many small workgroups stages (single stage;
+    // BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group as still give every CU two workgroups (at
+    // most 32). By the workgroups that one thread per ray would give, against it: 120 (64 pixels, 45 angles, 10
+    // candidates) 12.3 us against 14.1, 160 (128, 160, 4) 26.9 against 24.6, 180 (80, 45, 12) 17.5 against 16.1; off 4
+    // 144 (61, 36, 16) 15.4 against 16.3, 186 (109, 72, 6) 25.8 against 29.2, 264 (109, 24, 24) 33.6 against 27.4; large
+    // images 32 (160, 24, 4) 12.9 against 25.3, 72 (160, 8, 24) 22.4 against 25.4, 90 (150, 25, 6) 50.8 against 35.6.
     rc->scan_passes = rc->scan_chunks = 0;
     const char *ea = std::getenv("BOAC_ATT_SCAN");
     const long wide = (long)((nrays + 255) / 256) * C;
