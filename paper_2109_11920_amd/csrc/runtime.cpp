@@ -662,7 +662,8 @@ static void new_ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, Ra
             }
     }
     // attenuation build for few candidates: a ray over 8 lanes where one thread per ray would not give three fifths of
-    // the CUs a workgroup of 256, a quarter where an image takes over half the LDS, which each of the many small workgroups stages (single stage;
+    // the CUs a workgroup of 256, three quarters at image sizes off 4, which are staged element by element, a quarter
+    // where an image takes over half the LDS, which each of the many small workgroups stages (single stage;
     // BOAC_ATT_SCAN=0: always one thread per ray), as many rays per lane group as still give every CU two workgroups (at
     // most 32). By the workgroups that one thread per ray would give, against it: 120 (64 pixels, 45 angles, 10
     // candidates) 12.3 us against 14.1, 160 (128, 160, 4) 26.9 against 24.6, 180 (80, 45, 12) 17.5 against 16.1; off 4
@@ -672,7 +673,9 @@ static void new_ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, Ra
     const char *ea = std::getenv("BOAC_ATT_SCAN");
     const long wide = (long)((nrays + 255) / 256) * C;
     if (!(ea && ea[0] == '0') && comps == 1 && rc->single &&
-        (rc->lds > kLdsBudget / 2 ? 4 * wide <= ctx->n_cu : 5 * wide <= 3L * ctx->n_cu)) {
+        (rc->lds > kLdsBudget / 2 ? 4 * wide <= ctx->n_cu
+         : g.n % 4 == 0           ? 5 * wide <= 3L * ctx->n_cu
+                                  : 4 * wide <= 3L * ctx->n_cu)) {
         const long total = (nrays + 31) / 32;
         rc->scan_passes = (int)std::min<long>(32, std::max<long>(1, total * C / (2L * ctx->n_cu)));
         rc->scan_chunks = (int)((total + rc->scan_passes - 1) / rc->scan_passes);
