@@ -12,7 +12,8 @@ The committed cache holds the default workloads, the 72-angle slice (--workloads
 every slice shape of uneven48 (--workloads uneven48).
 
 Keys follow the library: "ray:<n>x<na>x<nb>x<nt>:<C>:<image components>" -> [block, rays per thread,
-paired forward projection (one-component entries)]
+paired forward projection (one-component entries)] of the projection (one component) and of the reverse sweep and
+tail (two); the attenuation build's workgroups are the library's own choice;
 and "back:<n>x<na>x<nb>x<nt>:<C>:0" -> [tile width, tile height, candidates per workgroup, XCD remap,
 slid-block kernel]. A slid-block entry the geometry does not admit falls back to the library's default.
 """

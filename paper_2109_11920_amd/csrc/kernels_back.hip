@@ -938,7 +938,7 @@ __global__ __launch_bounds__(256) void k_back_col4(DevGeom g, BackCfg T, BackArg
 // The window, its weights, the staged values and the order of every sum are k_back_col4's, so the results are too,
 // bit for bit.
 // Bound by latency: one memory round trip, 8 short gathers and one barrier (one candidate, 128 x 128, 128
-// angles: 8.8 us a launch; the split over workgroups it replaces, with its second pass over the block sums, 14.3).
+// angles: 7.9 us a launch; the split over workgroups before it, with its second pass over the block sums, 14.3).
 #ifndef BOAC_BODIES_ONLY
 template <bool WEIGHTED, bool PAIRED, bool TAIL, int HB, bool ROUNDS>
 __global__ __launch_bounds__(64 * kWaveBlocks) void k_back_wave(DevGeom g, BackCfg T, BackArgs A, int mode) {

@@ -414,7 +414,7 @@ __device__ __forceinline__ void fwd_band_ray(const DevGeom &g, const Band &band,
     }
 }
 
-// PAIRED (opposed-ray pairing, single stage only): each thread's ray (a, b), a < na/2, also gives the
+// PAIRED (opposed-ray pairing): each thread's ray (a, b), a < na/2, also gives the
 // projection of ray (a + na/2, nb-1-b) from the same samples and bilinear values.
 template <int MODE, bool SINGLE, bool PAIRED>
 __device__ __forceinline__ void k_fwd_body(int bid, float *lds, float *red, DevGeom g, const Bands &bands, int rpt, int chunks,
@@ -778,7 +778,7 @@ __device__ __forceinline__ void sweep_band_ray(const DevGeom &g, const Band &ban
 //   ybar^n_i = -rbar_i r^n_i / y^n_i   (0 where y^n_i <= 0)               (adjoint of r = S / y)
 // The ybar^{n+1} term is the y^{n+1} = A F^{n+1} adjoint left pending by the previous step (or the
 // objective's adjoint for the first step), so each step sweeps the rays once.
-// PAIRED (opposed-ray pairing, single stage): the held ray i also carries the opposed ray i', whose
+// PAIRED (opposed-ray pairing): the held ray i also carries the opposed ray i', whose
 // attenuation at the shared sample is att' = exp(-T) / att; its r_bar and ybar are formed the same
 // way, and its attenuation adjoint c' = dx [ r^n_i' W bbar + ybar^{n+1}_i' W F^{n+1} ] reaches the
 // held tensors through att' = E / att: att_bar += -att' c' / att, E_bar += c' / att.
@@ -971,7 +971,7 @@ __global__ __launch_bounds__(1024) void k_adj_sweep(DevGeom g, Bands bands, int 
 // (the sensitivity adjoint and the last pending projection adjoint); then
 // L_bar = -att * att_bar and m_bar_k = dx (L_bar_k / 2 + sum_{k'<k} L_bar_k') (the scan's transpose),
 // written in place of att_bar.
-// PAIRED (opposed-ray pairing, single stage): the opposed ray's part c' = dx (W G1 + rho_i' W G2)
+// PAIRED (opposed-ray pairing): the opposed ray's part c' = dx (W G1 + rho_i' W G2)
 // reaches att_bar and E_bar as in the sweep; at the ray's end Tbar = -E E_bar (E = exp(-T)), and
 // since T = dx sum_k m_k every sample's m_bar gains dx Tbar, written per ray in place of E_bar (the
 // field gather adds it).

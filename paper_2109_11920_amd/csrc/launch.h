@@ -24,10 +24,10 @@ struct Bands {
     }
 };
 
-// A ray-kernel launch covers `cand` candidates of one slice, each with n_angles * n_bins rays split
-// in chunks of block * rpt rays.
 constexpr int kSweepBandRpt = 2;  // the row-band reverse sweep's rays in registers at a time (of rpt)
 
+// A ray-kernel launch covers `cand` candidates of one slice, each with n_angles * n_bins rays split
+// in chunks of block * rpt rays.
 struct RayCfg {
     int block;   // threads per workgroup (64..1024, multiple of 64)
     int rpt;     // rays per thread (1..4)

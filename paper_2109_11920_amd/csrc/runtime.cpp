@@ -510,8 +510,8 @@ static std::string shape_key(const char *kind, const boac_geom &g, int C, int ex
     return buf;
 }
 
-// Candidate counts up to this one get the few-candidate plans (ray-split projection, angle-split
-// gather): the unbatched evaluation and small calls, where a plan for many candidates leaves CUs idle.
+// Candidate counts up to this one get the few-candidate plans (ray-split projection, the gather with a wave per
+// 8 angles): the unbatched evaluation and small calls, where a plan for many candidates leaves CUs idle.
 constexpr int kFewCand = 8;
 
 // Modelled time (cycles) of a single-stage ray launch of `wgs` workgroups of w waves, rpt rays per thread: the
@@ -520,7 +520,7 @@ constexpr int kFewCand = 8;
 // SIMD. Constants fitted to sweeps of every block of 256 to 1024 threads and 1 to 4 rays per thread at 24
 // shapes (64 to 192 pixels, 60 to 256 angles, 9 to 256 candidates): its choice is within 3% of the best
 // measured one on average and 16% at worst. (The constants of the kernels that tested every sample chose within
-// 6% and 40% for these: 37 candidates at 109 pixels and 90 angles in pairs 43.8 us, singly 32.5.)
+// 6% and 40% for these: 37 candidates at 109 pixels and 45 held angles in pairs 43.8 us, singly 32.5.)
 struct RayCost {
     double latency, valu, stage, fixed;
     int waves;  // waves a SIMD holds (registers)
@@ -594,7 +594,8 @@ static void new_ray_plan(boac_ctx *ctx, const boac_geom &g, int C, int comps, Ra
                 }
             }
     }
-    // plan cache entry: [threads per workgroup, rays per thread, paired forward projection]
+    // plan cache entry: [threads per workgroup, rays per thread, paired forward projection], for the projection, the
+    // reverse sweep and the tail (the attenuation build has a plan of its own)
     auto it = ctx->tune.find(shape_key("ray", g, C, comps));
     if (it != ctx->tune.end() && it->second.size() >= 2) {
         const int blk = it->second[0], rpt = it->second[1];
